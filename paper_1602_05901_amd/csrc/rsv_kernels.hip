@@ -168,51 +168,162 @@ __global__ __launch_bounds__(RED_T) void k_reduce(const double *__restrict__ par
     if (threadIdx.x == 0) out[kk] = s;
 }
 
-__global__ __launch_bounds__(BS) void k_nat_to_tl(Geo g, const double *__restrict__ nat, double *__restrict__ tl)
+// Block b of nb as a block of one contiguous range per XCD (workgroups are
+// dealt to the eight XCDs in turn, each with its own L2): neighbouring blocks
+// of a kernel whose blocks share cache lines then meet in one L2.
+__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb)
 {
-    const int64_t slot = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (slot >= g.nslot) return;
-    int gx, gy, k;
-    const bool real = cell_of(g, slot, gx, gy, k);
-    const int64_t row = real ? row_of(g, gx, gy, k) : 0;
-    for (int p = 0; p < 3; ++p) tl[vidx(slot, p)] = real ? nat[3 * row + p] : 0.0;
+    const int64_t x = b & 7, q = nb >> 3, rem = nb & 7;
+    return x * q + (x < rem ? x : rem) + (b >> 3);
 }
 
-__global__ __launch_bounds__(BS) void k_tl_to_nat(Geo g, const double *__restrict__ tl, double *__restrict__ nat,
-                                                  double alpha, double beta)
+// Caller order -> tile-lane order and back.  A tile-lane row holds 64 cells of
+// one hyperplane, 64 separate 24-byte pieces of the caller's vector, so one
+// lane per cell made 64 requests of every load or store (567 us in and 1100 us
+// out at 512x512x128; 315 and 315 us, 5.1 TB/s, in runs).  A workgroup takes PR rows of a tile and moves the caller's
+// side in x-runs: cells i = 0..7 of a grid line (j, k) are 192 contiguous
+// bytes, and run (j, u) with u = k + j - r0 holds the cells of rows r0 + u + i.
+// LDS turns runs into rows.  Ranges of workgroups are contiguous per XCD: a run
+// cut between two workgroups of a column shares its lines in one L2.
+constexpr int PR = 16;                       // rows per workgroup
+constexpr int PR_U = PR + 7;                 // runs of one grid line that meet them
+constexpr int PR_IT = (8 * PR_U + BS / 24 - 1) / (BS / 24);
+
+// v mod nz for v in [-15, nz + 15]
+__device__ __forceinline__ int wrap_near(int v, int nz)
 {
-    const int64_t slot = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (slot >= g.nslot) return;
-    int gx, gy, k;
-    if (!cell_of(g, slot, gx, gy, k)) return;
-    const int64_t row = row_of(g, gx, gy, k);
-    for (int p = 0; p < 3; ++p) {
-        double v = alpha * tl[vidx(slot, p)];
-        if (beta != 0.0) v += beta * nat[3 * row + p];
-        nat[3 * row + p] = v;
+    if (nz < 16) return wrap_nz(v, nz);
+    v += v < 0 ? nz : 0;
+    return v - (v >= nz ? nz : 0);
+}
+
+// Thread part of the runs: entry e of the runs it = 0, 1, ..., eight or more
+// threads' groups taking one run each.  Every index fits 32 bits (a grid has
+// at most 2^31 / 3 padded cells).
+struct Runs {
+    int e, i, first, nr, r0, nx, ny, nz, gx0, gy0, ntop;
+    bool ok;
+    __device__ __forceinline__ Runs(const Geo &g, int T, int r0_, int nr_)
+    {
+        e = threadIdx.x % 24;
+        i = e / 3;
+        first = threadIdx.x / 24;
+        r0 = r0_; nr = nr_;
+        nx = g.nx; ny = g.ny; nz = g.nz;
+        gx0 = (T % g.ntx) * 8;
+        gy0 = (T / g.ntx) * 8;
+        ntop = g.ordering == RSV_TOP_DOWN ? nz - 1 : -1;
+        ok = threadIdx.x < BS / 24 * 24 && gx0 + i < nx;
+    }
+    // place of the entry of iteration `it` in the rows' LDS copy [row][cell 8 j + i][3]
+    // and in the caller's vector; false outside the rows or the grid
+    __device__ __forceinline__ bool at(int it, int &lds, int &nat) const
+    {
+        const int q = it * (BS / 24) + first, j = q / PR_U, u = q - j * PR_U - 7, v = u + i;
+        int k = wrap_near(r0 + u - j, nz);
+        if (ntop >= 0) k = ntop - k;
+        lds = (v * 64 + j * 8) * 3 + e;
+        nat = 3 * ((k * ny + gy0 + j) * nx + gx0) + e;
+        return ok && j < 8 && v >= 0 && v < nr && gy0 + j < ny;
+    }
+};
+
+__global__ __launch_bounds__(BS) void k_nat_to_tl(Geo g, int nchunk, const double *__restrict__ nat,
+                                                  double *__restrict__ tl)
+{
+    __shared__ double rows[PR * 64 * 3];
+    const int64_t wg = xcd_block(blockIdx.x, gridDim.x);
+    const int T = (int)(wg / nchunk), r0 = (int)(wg - (int64_t)T * nchunk) * PR, nr = min(PR, g.nz - r0);
+    const Runs R(g, T, r0, nr);
+    double v[PR_IT];
+    int at[PR_IT];
+#pragma unroll
+    for (int q = 0; q < PR_IT; ++q) {
+        int src, a;
+        const bool in = R.at(q, a, src);
+        at[q] = in ? a : -1;
+        v[q] = in ? nat[src] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < PR_IT; ++q)
+        if (at[q] >= 0) rows[at[q]] = v[q];
+    __syncthreads();
+    const int L = threadIdx.x & 63;
+    int i, j;
+    lane_ij(L, i, j);
+    const bool real = R.gx0 + i < g.nx && R.gy0 + j < g.ny;
+    for (int r = threadIdx.x >> 6; r < nr; r += BS / 64)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            tl[((int64_t)T * g.nz + r0 + r) * 192 + c * 64 + L] = real ? rows[(r * 64 + j * 8 + i) * 3 + c] : 0.0;
+}
+
+__global__ __launch_bounds__(BS) void k_tl_to_nat(Geo g, int nchunk, const double *__restrict__ tl,
+                                                  double *__restrict__ nat, double alpha, double beta)
+{
+    __shared__ double rows[PR * 64 * 3];
+    const int64_t wg = xcd_block(blockIdx.x, gridDim.x);
+    const int T = (int)(wg / nchunk), r0 = (int)(wg - (int64_t)T * nchunk) * PR, nr = min(PR, g.nz - r0);
+    const int L = threadIdx.x & 63;
+    int i, j;
+    lane_ij(L, i, j);
+#pragma unroll
+    for (int q = 0; q < PR / (BS / 64); ++q) {
+        const int r = (threadIdx.x >> 6) + q * (BS / 64);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (r < nr) rows[(r * 64 + j * 8 + i) * 3 + c] = tl[((int64_t)T * g.nz + r0 + r) * 192 + c * 64 + L];
+    }
+    __syncthreads();
+    const Runs R(g, T, r0, nr);
+#pragma unroll 5
+    for (int q = 0; q < PR_IT; ++q) {
+        int dst, a;
+        if (!R.at(q, a, dst)) continue;
+        double v = alpha * rows[a];
+        if (beta != 0.0) v += beta * nat[dst];
+        nat[dst] = v;
     }
 }
 
+// Caller blocks [row][63] -> tile-lane rows, one row of 64 cells per
+// workgroup.  A wave reads one cell's 504 contiguous bytes per load (lane e
+// takes entry e; 16 cells per wave, all in flight together) and puts them in
+// LDS transposed, then writes whole 512-byte rows.  With one cell per lane
+// every load touched 64 lines 504 bytes apart and a wave's 32 KB of them did
+// not stay in the L1 (4.19 ms at 256x256x128; 1.50 ms, 5.6 TB/s, transposed).
+constexpr int AS_PAD = 65;   // LDS row of one entry: 64 cells and a word of padding
 __global__ __launch_bounds__(BS) void k_assemble(Geo g, const double *__restrict__ blocks, double *__restrict__ A,
                                                  int32_t *flags)
 {
-    const int64_t slot = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (slot >= g.nslot) return;
+    __shared__ double t[63 * AS_PAD];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t rowi = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t slot = rowi * 64 + lane;
     int gx, gy, k;
     const bool real = cell_of(g, slot, gx, gy, k);
-    const int64_t row = real ? row_of(g, gx, gy, k) : 0;
+    const int32_t row = real ? (int32_t)row_of(g, gx, gy, k) : -1;   // fewer than 2^31 / 3 cells
+    constexpr int NC = 64 / (BS / 64);
+    double v[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        const int32_t rq = __shfl(row, w * NC + q, 64);
+        v[q] = (rq >= 0 && lane < 63) ? blocks[(int64_t)rq * 63 + lane] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+        if (lane < 63) t[lane * AS_PAD + w * NC + q] = v[q];
+    __syncthreads();
     int bad = 0;
-    for (int s = 0; s < 7; ++s) {
+    for (int e = w; e < 63; e += BS / 64) {
         int di, dj, dk;
-        dir_off(s, di, dj, dk);
+        dir_off(e / 9, di, dj, dk);
         const bool exists = real && gx + di >= 0 && gx + di < g.nx && gy + dj >= 0 && gy + dj < g.ny &&
                             k + dk >= 0 && k + dk < g.nz;
-        for (int e = 0; e < 9; ++e) {
-            const double v = real ? blocks[row * 63 + s * 9 + e] : 0.0;
-            if (!isfinite(v)) bad |= FLAG_NAN;
-            if (real && !exists && v != 0.0) bad |= FLAG_PATTERN;
-            A[aidx(slot, s * 9 + e)] = exists ? v : 0.0;
-        }
+        const double x = t[e * AS_PAD + lane];
+        if (!isfinite(x)) bad |= FLAG_NAN;
+        if (real && !exists && x != 0.0) bad |= FLAG_PATTERN;
+        A[(rowi * 63 + e) * 64 + lane] = exists ? x : 0.0;
     }
     if (bad) atomicOr(&flags[0], bad);
 }
@@ -553,21 +664,23 @@ rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, cons
 
 rsv_status launch_nat_to_tl(rsv_ctx *c, const Geo &g, const double *nat, double *tl)
 {
-    hipLaunchKernelGGL(k_nat_to_tl, dim3(spmv_blocks(g)), dim3(BS), 0, c->stream, g, nat, tl);
+    const int nchunk = (g.nz + PR - 1) / PR;
+    hipLaunchKernelGGL(k_nat_to_tl, dim3((unsigned)(g.ntx * g.nty * nchunk)), dim3(BS), 0, c->stream, g, nchunk, nat, tl);
     RSV_LAUNCH(c);
     return RSV_OK;
 }
 
 rsv_status launch_tl_to_nat(rsv_ctx *c, const Geo &g, const double *tl, double *nat, double alpha, double beta)
 {
-    hipLaunchKernelGGL(k_tl_to_nat, dim3(spmv_blocks(g)), dim3(BS), 0, c->stream, g, tl, nat, alpha, beta);
+    const int nchunk = (g.nz + PR - 1) / PR;
+    hipLaunchKernelGGL(k_tl_to_nat, dim3((unsigned)(g.ntx * g.nty * nchunk)), dim3(BS), 0, c->stream, g, nchunk, tl, nat, alpha, beta);
     RSV_LAUNCH(c);
     return RSV_OK;
 }
 
 rsv_status launch_assemble(rsv_ctx *c, const Geo &g, const double *blocks, double *A)
 {
-    hipLaunchKernelGGL(k_assemble, dim3(spmv_blocks(g)), dim3(BS), 0, c->stream, g, blocks, A, c->d_flags);
+    hipLaunchKernelGGL(k_assemble, dim3((unsigned)(g.nslot / 64)), dim3(BS), 0, c->stream, g, blocks, A, c->d_flags);
     RSV_LAUNCH(c);
     return RSV_OK;
 }
