@@ -258,6 +258,7 @@ void rsv_destroy(rsv_ctx *c)
     dev_free(c->d_partials);
     dev_free(c->d_tickets);
     dev_free(c->d_flags);
+    dev_free(c->d_trie);
     delete c;
 }
 

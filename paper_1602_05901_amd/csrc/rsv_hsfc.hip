@@ -11,7 +11,10 @@
 //
 // Partition: the cells in (key, index) order are cut into nparts runs of
 // sizes differing by at most one (the cell of rank r goes to part
-// floor(r nparts / n)).  The order comes from a stable least-significant-
+// floor(r nparts / n)).  Up to 4096 parts the cut is found without ordering the
+// cells: a digit trie over (key, index) counts the cells under each prefix,
+// most significant digit first, and follows only the prefixes that a cut goes
+// through.  More parts take the order itself, from a stable least-significant-
 // digit radix sort over the 3*levels key bits, 8 bits per pass: per-tile
 // digit histograms, one exclusive scan, and a scatter in which each tile
 // ranks its elements by digit with wave ballots (eight ballots match the
@@ -206,6 +209,176 @@ __global__ __launch_bounds__(256) void k_assign_parts(const uint32_t *__restrict
         part[idx[r]] = (int32_t)((r * (int64_t)nparts) / n);
 }
 
+// ---------------------------------------------------------------- the cut by a digit trie
+// A node stands for the cells that share a prefix of the word (key, index); its
+// entries, one per value of the next digit, hold how many cells follow that
+// digit.  Ranks are prefix sums of the counts, so an entry whose cells all lie
+// in one part is a leaf with that part, and one that a cut goes through has a
+// child node: at most nparts - 1 nodes per level, since a cut goes through one
+// node of a level only.  Index digits follow the key's, so equal keys are cut
+// in index order and every path ends.  A level without nodes costs two empty
+// launches; nothing is read back.
+//
+// Each level that has nodes reads the keys once (8 bytes a cell) and the last
+// pass writes the parts, against 4 x 32 bytes a cell and scattered writes for
+// the sort of a 30-bit key, whose 0.8 GB of buffers were allocated and freed in
+// every call: keys and cut of 33.5 M cells into 64 parts 4.23 -> 0.44 ms, of
+// which the keys are 0.22 (there every cut falls on an octant and the root
+// decides it; each further level that is reached adds about 0.06).
+constexpr int TRIE_PARTS = 4096;      // most parts the trie takes
+constexpr int TRIE_TOP = 12;          // digit bits of the root
+constexpr int TRIE_ROWS_BITS = 20;    // log2 of the most entries a level may have
+constexpr int TRIE_MAXLEV = 14;
+
+struct Trie {
+    int nlev;                         // levels, the root first
+    int width[TRIE_MAXLEV];           // digit bits
+    int shift[TRIE_MAXLEV];           // lowest bit of the digit in its word
+    int of_index[TRIE_MAXLEV];        // the digit is the index's, not the key's
+    int32_t *entry[TRIE_MAXLEV];      // [node][2^width]: part, or ~child node
+    uint32_t *first;                  // [2][nparts]: rank of a node's first cell, by level parity
+    uint32_t *nodes;                  // [nlev + 1]: nodes per level
+    uint32_t *stray;                  // set when a key has bits above the ones its levels give it
+    int kbits;
+    uint32_t *count;                  // [node][2^width] of the level at hand; all zero between levels
+};
+
+__device__ __forceinline__ uint32_t trie_digit(const Trie &t, int l, uint64_t key, uint32_t idx)
+{
+    const uint64_t w = t.of_index[l] ? (uint64_t)idx : key;
+    return (uint32_t)(w >> t.shift[l]) & ((1u << t.width[l]) - 1u);
+}
+
+// entry of (key, idx) at level `to`, or the leaf met before it
+__device__ __forceinline__ int32_t trie_walk(const Trie &t, int to, uint64_t key, uint32_t idx)
+{
+    int32_t e = t.entry[0][trie_digit(t, 0, key, idx)];
+    for (int l = 1; l <= to && e < 0; ++l)
+        e = t.entry[l][((int64_t)~e << t.width[l]) + trie_digit(t, l, key, idx)];
+    return e;
+}
+
+__global__ __launch_bounds__(256) void k_trie_reset(Trie t, int64_t words)
+{
+    const int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    for (int64_t e = e0; e < words; e += (int64_t)gridDim.x * 256) t.count[e] = 0;
+    if (e0 <= t.nlev) t.nodes[e0] = e0 == 0 ? 1u : 0u;
+    if (e0 == 0) t.first[0] = *t.stray = 0;
+}
+
+// The cells' counts at level l.  Cells in grid order change their leading
+// digits rarely, so neighbouring lanes mostly count the same entry: the first
+// lane of each run of equal entries adds the run's length.  The root's 4096
+// entries are counted in LDS first.
+template <bool ROOT>
+__global__ __launch_bounds__(512) void k_trie_count(Trie t, int l, int64_t n, const uint64_t *__restrict__ keys)
+{
+    __shared__ uint32_t h[ROOT ? 1 << TRIE_TOP : 1];
+    if (!ROOT && t.nodes[l] == 0) return;
+    if (ROOT) {
+        for (int e = threadIdx.x; e < 1 << TRIE_TOP; e += 512) h[e] = 0;
+        __syncthreads();
+    }
+    const int lane = threadIdx.x & 63;
+    const uint64_t after = lane == 63 ? 0ull : ~0ull << (lane + 1);
+    constexpr int U = 4;
+    uint64_t above = 0;
+    const int64_t stride = (int64_t)gridDim.x * 512;
+    for (int64_t e0 = (int64_t)blockIdx.x * 512; e0 < n; e0 += U * stride) {   // whole waves stay together
+        uint64_t key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * stride + threadIdx.x;
+            key[u] = e < n ? keys[e] : 0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * stride + threadIdx.x;
+            int32_t at = -1;   // entry counted (at most 2^20 of them)
+            if (e < n) {
+                if (ROOT) {
+                    above |= key[u] >> t.kbits;
+                    at = (int32_t)trie_digit(t, 0, key[u], (uint32_t)e);
+                } else {
+                    const int32_t w = trie_walk(t, l - 1, key[u], (uint32_t)e);
+                    if (w < 0) at = (int32_t)(((uint32_t)~w << t.width[l]) + trie_digit(t, l, key[u], (uint32_t)e));
+                }
+            }
+            const int32_t prev = __shfl_up(at, 1, 64);
+            const bool head = lane == 0 || prev != at;
+            const uint64_t heads = __ballot(head) & after;
+            const uint32_t len = (uint32_t)((heads ? __ffsll((unsigned long long)heads) - 1 : 64) - lane);
+            if (head && at >= 0) {
+                if (ROOT) atomicAdd(&h[at], len);
+                else atomicAdd(&t.count[at], len);
+            }
+        }
+    }
+    if (ROOT) {
+        if (above) *t.stray = 1;
+        __syncthreads();
+        for (int e = threadIdx.x; e < 1 << TRIE_TOP; e += 512)
+            if (h[e]) atomicAdd(&t.count[e], h[e]);
+    }
+}
+
+// Entries of a level from its counts, one workgroup per node: ranks by an
+// exclusive scan, leaves and children; the counts are left zero.
+__global__ __launch_bounds__(256) void k_trie_split(Trie t, int l, int64_t n, int64_t nparts)
+{
+    if (blockIdx.x >= t.nodes[l]) return;
+    __shared__ uint32_t sums[256];
+    const int bins = 1 << t.width[l], per = (bins + 255) / 256;
+    uint32_t *c = t.count + ((int64_t)blockIdx.x << t.width[l]);
+    int32_t *out = t.entry[l] + ((int64_t)blockIdx.x << t.width[l]);
+    uint32_t s = 0;
+    for (int q = 0; q < per; ++q) {
+        const int b = (int)threadIdx.x * per + q;
+        s += b < bins ? c[b] : 0u;
+    }
+    sums[threadIdx.x] = s;
+    __syncthreads();
+    for (int off = 1; off < 256; off <<= 1) {
+        const uint32_t a = (int)threadIdx.x >= off ? sums[threadIdx.x - off] : 0u;
+        __syncthreads();
+        sums[threadIdx.x] += a;
+        __syncthreads();
+    }
+    int64_t r = (int64_t)t.first[(l & 1) * nparts + blockIdx.x] + (sums[threadIdx.x] - s);
+    for (int q = 0; q < per; ++q) {
+        const int b = (int)threadIdx.x * per + q;
+        if (b >= bins) break;
+        const int64_t k = c[b];
+        c[b] = 0;
+        const int64_t p0 = k ? (r * nparts) / n : 0, p1 = k ? ((r + k - 1) * nparts) / n : 0;
+        int32_t v = (int32_t)p0;
+        if (p0 != p1) {
+            const uint32_t child = atomicAdd(&t.nodes[l + 1], 1u);
+            t.first[((l + 1) & 1) * nparts + child] = (uint32_t)r;
+            v = ~(int32_t)child;
+        }
+        out[b] = v;
+        r += k;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_trie_assign(Trie t, int64_t n, const uint64_t *__restrict__ keys,
+                                                     int32_t *__restrict__ part)
+{
+    constexpr int U = 4;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t e0 = (int64_t)blockIdx.x * 256 + threadIdx.x; e0 < n; e0 += U * stride) {
+        uint64_t key[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) key[u] = e0 + u * stride < n ? keys[e0 + u * stride] : 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = e0 + u * stride;
+            if (e < n) part[e] = trie_walk(t, t.nlev - 1, key[u], (uint32_t)e);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- partition quality
 // per part: cnt[p] = {|G_p|, f_p, b_p}; adjacency bit (p, q) set when a face
 // joins parts p and q.  A face inside a part is counted by its lower cell.
@@ -354,6 +527,78 @@ rsv_status scan_counts(rsv_ctx *c, const uint32_t *in, uint32_t *out, int64_t m,
     return RSV_OK;
 }
 
+// The cut by the trie.  The context keeps the workspace (at most 2^20 entries a
+// level: 4 MiB x 13 levels and the counts); every call waits for its last
+// kernel, so the next one, on whatever stream, finds it idle.
+// *stray: some key has bits above its 3*levels, which the sort's whole bytes
+// count in part; those keys are left to it.
+rsv_status trie_partition(rsv_ctx *c, int64_t n, const uint64_t *keys, int levels, int32_t nparts, int32_t *part,
+                          uint32_t *stray)
+{
+    Trie t{};
+    t.kbits = 3 * levels;
+    int pbits = 0, ibits = 0;
+    while (((int64_t)1 << pbits) < nparts) ++pbits;
+    while (((int64_t)1 << ibits) < n) ++ibits;
+    const int w = std::min(TRIE_TOP, TRIE_ROWS_BITS - pbits);   // 8 to 12 bits below the root
+    int kbits = 3 * levels, top = std::min(kbits, TRIE_TOP);
+    auto level = [&](int width, int shift, int of_index) {
+        t.width[t.nlev] = width;
+        t.shift[t.nlev] = shift;
+        t.of_index[t.nlev] = of_index;
+        ++t.nlev;
+    };
+    level(top, kbits - top, 0);
+    for (int left = kbits - top; left > 0;) {
+        const int q = std::min(w, left);
+        left -= q;
+        level(q, left, 0);
+    }
+    for (int left = ibits; left > 0;) {
+        const int q = std::min(w, left);
+        left -= q;
+        level(q, left, 1);
+    }
+    const int64_t rows = std::max<int64_t>(1, nparts - 1);
+    int64_t words = 0, cnt = 0, at[TRIE_MAXLEV];
+    for (int l = 0; l < t.nlev; ++l) {
+        const int64_t e = (l ? rows : 1) << t.width[l];
+        at[l] = words;
+        words += e;
+        cnt = std::max(cnt, e);
+    }
+    const int64_t total = words + cnt + 2 * (int64_t)nparts + TRIE_MAXLEV + 2;
+    if (total > c->trie_cap) {
+        dev_free(c->d_trie);
+        c->d_trie = nullptr;
+        c->trie_cap = 0;
+        rsv_status s = dev_alloc(c, (void **)&c->d_trie, (size_t)total * 4);
+        if (s != RSV_OK) return s;
+        c->trie_cap = total;
+    }
+    for (int l = 0; l < t.nlev; ++l) t.entry[l] = c->d_trie + at[l];
+    t.count = (uint32_t *)(c->d_trie + words);
+    t.first = t.count + cnt;
+    t.nodes = t.first + 2 * nparts;
+    t.stray = t.nodes + TRIE_MAXLEV + 1;
+    hipLaunchKernelGGL(k_trie_reset, dim3((unsigned)std::min<int64_t>((cnt + 255) / 256, 1024)), dim3(256), 0, c->stream,
+                       t, cnt);
+    const unsigned nb = (unsigned)std::min<int64_t>((n + 2047) / 2048, 1024);
+    for (int l = 0; l < t.nlev; ++l) {
+        if (l == 0) hipLaunchKernelGGL(k_trie_count<true>, dim3(nb), dim3(512), 0, c->stream, t, l, n, keys);
+        else hipLaunchKernelGGL(k_trie_count<false>, dim3(nb), dim3(512), 0, c->stream, t, l, n, keys);
+        hipLaunchKernelGGL(k_trie_split, dim3((unsigned)(l ? rows : 1)), dim3(256), 0, c->stream, t, l, n,
+                           (int64_t)nparts);
+        RSV_LAUNCH(c);
+    }
+    hipLaunchKernelGGL(k_trie_assign, dim3((unsigned)std::min<int64_t>((n + 1023) / 1024, 8192)), dim3(256), 0, c->stream,
+                       t, n, keys, part);
+    RSV_LAUNCH(c);
+    RSV_HIP(c, hipMemcpyAsync(stray, t.stray, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
+    RSV_HIP(c, hipStreamSynchronize(c->stream));
+    return RSV_OK;
+}
+
 struct Tmp {
     std::vector<void *> p;
     ~Tmp() { for (void *q : p) dev_free(q); }
@@ -394,6 +639,14 @@ rsv_status rsv_hsfc_partition(rsv_ctx *c, int64_t n, const uint64_t *keys, int32
     if (nparts < 1) return set_err(c, RSV_ERR_ARG, "nparts must be >= 1");
     if (n > ((int64_t)1 << 31)) return set_err(c, RSV_ERR_ARG, "at most 2^31 keys");
     if (n == 0) return RSV_OK;
+    // Up to 4096 parts a node of the trie keeps at least 8 digit bits within
+    // 2^20 entries a level; each level reads all keys once, so with more parts
+    // (fewer bits, more levels) the sort's fixed passes are the better choice.
+    if (nparts <= TRIE_PARTS) {
+        uint32_t stray = 0;
+        const rsv_status st = trie_partition(c, n, keys, levels, nparts, part, &stray);
+        if (st != RSV_OK || !stray) return st;
+    }
     const int64_t ntile = (n + RS_TILE - 1) / RS_TILE;
     Tmp t;
     uint64_t *k2[2] = {nullptr, nullptr};

@@ -135,6 +135,8 @@ struct rsv_ctx {
     uint64_t ticket_base[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int32_t *d_flags = nullptr;   // [0] error flags, [1] bad cell (min)
     double *d_scratch = nullptr;  // this device's fixed scratch (rsv_spmv_noalloc), not owned
+    int32_t *d_trie = nullptr;    // workspace of the Hilbert cut (rsv_hsfc.hip), 4-byte words
+    int64_t trie_cap = 0;
     int num_cu = 256;
     int lds_max = 65536;               // dynamic LDS bytes a workgroup may use
     int lds_per_cu = 0;

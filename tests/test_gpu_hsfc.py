@@ -165,3 +165,35 @@ def test_C5_grid_partition_full_size(rsv, ctx, nparts):
     assert np.array_equal(per, pero)
     check_q(q, qo, nparts)
     g.close()
+
+
+@pytest.mark.parametrize("n,levels,nparts,kind", [
+    (1, 1, 1, "random"), (1, 21, 4096, "random"), (7, 3, 19, "random"), (513, 4, 512, "random"),
+    (100_003, 2, 97, "random"),                       # 64 keys: every cut inside a run of equal keys
+    (65_537, 5, 4096, "equal"), (65_537, 21, 3, "equal"), (262_145, 21, 4095, "random"),
+    (300_007, 10, 4096, "clustered"), (300_007, 10, 4097, "clustered"),   # either side of the sort
+    (50_000, 10, 64, "stray"),                        # bits above 3 * levels
+])
+def test_cut_equals_a_stable_sort(rsv, ctx, n, levels, nparts, kind):
+    """The cut against numpy's stable order of the keys: part floor(r nparts / n)
+    for the cell of rank r, whole numbers, no tolerance."""
+    log("cut", n, levels, nparts, kind)
+    r = np.random.default_rng(n + levels)
+    top = 1 << (3 * levels)
+    if kind == "equal":
+        k = np.full(n, top - 1, np.uint64)
+    elif kind == "clustered":   # long runs under a few prefixes
+        k = (r.integers(0, 5, n) * (top // 7) + r.integers(0, 40, n)).astype(np.uint64)
+    else:
+        k = r.integers(0, top, n, dtype=np.uint64)
+    bits = 3 * levels
+    if kind == "stray":
+        k[::3] |= np.uint64(1 << bits)
+        bits = (bits + 7) // 8 * 8
+    keys = torch.from_numpy(k.view(np.int64)).cuda()
+    part = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    rsv.hsfc_partition(ctx, keys, levels, nparts, part)
+    order = np.argsort(k & np.uint64((1 << bits) - 1), kind="stable")
+    ref = np.empty(n, np.int32)
+    ref[order] = (np.arange(n, dtype=np.int64) * nparts) // n
+    assert np.array_equal(part.cpu().numpy(), ref)
