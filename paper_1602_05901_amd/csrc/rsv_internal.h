@@ -234,6 +234,7 @@ rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, cons
                        const double *aux1, double alpha, double beta, int k0);
 
 rsv_status launch_reduce(rsv_ctx *c, int nblocks, int K, int k0);    // partials[nblocks][K] -> d_scal[k0..]
+rsv_status launch_reduce_to(rsv_ctx *c, int nblocks, int K, double *out);   // the same into out[K]
 
 // scalar systems (rsv_scalar.hip): the product with the same modes, and the
 // matrix-independent front ends the Krylov drivers use

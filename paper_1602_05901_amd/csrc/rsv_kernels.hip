@@ -628,12 +628,17 @@ int mvec_blocks(int64_t n)
     return (int)std::min<int64_t>(std::max<int64_t>(b, 1), RSV_MVEC_BLOCKS);
 }
 
-rsv_status launch_reduce(rsv_ctx *c, int nblocks, int K, int k0)
+rsv_status launch_reduce_to(rsv_ctx *c, int nblocks, int K, double *out)
 {
     if (K <= 0) return RSV_OK;
-    hipLaunchKernelGGL(k_reduce, dim3(K), dim3(RED_T), 0, c->stream, c->d_partials, nblocks, K, c->d_scal + k0);
+    hipLaunchKernelGGL(k_reduce, dim3(K), dim3(RED_T), 0, c->stream, c->d_partials, nblocks, K, out);
     RSV_LAUNCH(c);
     return RSV_OK;
+}
+
+rsv_status launch_reduce(rsv_ctx *c, int nblocks, int K, int k0)
+{
+    return launch_reduce_to(c, nblocks, K, c->d_scal + k0);
 }
 
 rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, const double *x, double *y,

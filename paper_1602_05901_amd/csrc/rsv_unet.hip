@@ -12,7 +12,7 @@
 //   y = conv10(d1)  (1x1x1 linear to 3 channels),  z = s * y
 // pool = 2x2x2 average, up = nearest-neighbour x2.  Activations and weights
 // are BF16; every convolution is an implicit GEMM on the CDNA matrix cores
-// (v_mfma_f32_16x16x16_bf16, FP32 accumulation).  Training: the backward
+// (v_mfma_f32_16x16x32_bf16, FP32 accumulation).  Training: the backward
 // data pass is the same kernel on transposed, tap-flipped weights; the weight
 // gradient is a split-K MFMA GEMM over voxels with a fixed-order reduction;
 // Adam keeps FP32 master weights.
@@ -22,6 +22,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <type_traits>
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
@@ -71,23 +72,62 @@ struct Arch {
     int kbt(int l) const { return (27 * cout[l] + (cout[l] % 8 ? 15 : 31)) / (cout[l] % 8 ? 16 : 32); }
 };
 
+// A level of a batch: the samples' voxels follow one another, so the batch is
+// one grid of nz = samples x nzs layers in which no stencil crosses a multiple
+// of nzs.
 struct ConvGeo {
-    int nx, ny, nz;   // output resolution
+    int nx, ny, nz;   // output resolution, all samples
+    int nzs;          // layers of one sample
     int up;           // input is the half-resolution tensor, read nearest-up-sampled
     int cin, cout;
-    int64_t V;
+    int64_t V;        // voxels of all samples
 };
 
-__device__ inline int64_t src_voxel(const ConvGeo &g, int x, int y, int z, int dx, int dy, int dz)
+// Bricks of 16 (x) x 4 (y) x TZ (z) output voxels; none spans two samples.
+struct Brick {
+    int x0, y0, z0;   // first voxel
+    int zlo, zhi;     // layers of its sample
+};
+__host__ __device__ inline int brick_count(const ConvGeo &g, int tz)
+{
+    return ((g.nx + 15) / 16) * ((g.ny + 3) / 4) * ((g.nzs + tz - 1) / tz) * (g.nz / g.nzs);
+}
+__device__ inline Brick brick_of(const ConvGeo &g, int b, int tz)
+{
+    const int ntx = (g.nx + 15) / 16, nty = (g.ny + 3) / 4, ntz = (g.nzs + tz - 1) / tz;
+    const int bz = b / (ntx * nty), smp = bz / ntz;
+    Brick k;
+    k.x0 = (b % ntx) * 16;
+    k.y0 = ((b / ntx) % nty) * 4;
+    k.zlo = smp * g.nzs;
+    k.zhi = k.zlo + g.nzs;
+    k.z0 = k.zlo + (bz - smp * ntz) * tz;
+    return k;
+}
+
+// input voxel of (x, y, z) + (dx, dy, dz), or -1 outside the sample zlo .. zhi - 1
+__device__ inline int64_t src_voxel(const ConvGeo &g, int x, int y, int z, int dx, int dy, int dz, int zlo, int zhi)
 {
     const int a = x + dx, b = y + dy, c = z + dz;
-    if (a < 0 || a >= g.nx || b < 0 || b >= g.ny || c < 0 || c >= g.nz) return -1;
+    if (a < 0 || a >= g.nx || b < 0 || b >= g.ny || c < zlo || c >= zhi) return -1;
     if (g.up) {
         const int hx = g.nx >> 1, hy = g.ny >> 1;
         return (a >> 1) + (int64_t)hx * ((b >> 1) + (int64_t)hy * (c >> 1));
     }
     return a + (int64_t)g.nx * (b + (int64_t)g.ny * c);
 }
+
+// What a convolution does with its FP32 sums: + bias (+ skip), ReLU; or, for a
+// data gradient, the ReLU mask of the activations the gradient belongs to
+// (zero where mask <= 0), with an optional FP32 copy of the masked gradient.
+struct Epilogue {
+    const float *bias;
+    const uint16_t *skip;
+    int relu;
+    const uint16_t *mask;
+    float *copy;
+    void *out;
+};
 
 // ---------------------------------------------------------------- convolution as implicit GEMM
 // K per MFMA: 32 (v_mfma_f32_16x16x32_bf16, 8 k per lane) when the input has a
@@ -105,6 +145,8 @@ __device__ inline v4f mfma_k(v8s a, v8s b, v4f c)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
+// Any multiple of 4 input channels, operands from global memory (the single
+// layers of rsv_conv3d whose channel count has no staged kernel below).
 // One wavefront: 16*MB output voxels x (16*NB) output channels.  GEMM row m =
 // voxel, column n = output channel, k = tap*cin + ci.  Operand fragments
 // (KW = 16 or 32, w = KW / 4 k per lane): lane l holds A[m = l%16][k = w*(l/16)
@@ -112,10 +154,9 @@ __device__ inline v4f mfma_k(v8s a, v8s b, v4f c)
 // D[m = 4*(l/16) + i][n = l%16].  Weights are pre-packed so that B fragments
 // are one load per lane; an A fragment's lane reads w consecutive channels of
 // one voxel.  Each B fragment feeds MB products and each A fragment NB.
-template <int MB, int NB, bool OUT_BF16, bool K32>
+template <int MB, int NB, bool K32>
 __global__ __launch_bounds__(256) void k_conv(ConvGeo g, const uint16_t *__restrict__ X, const void *__restrict__ Wfv,
-                                              int KB, const float *__restrict__ bias,
-                                              const uint16_t *__restrict__ skip, int relu, void *__restrict__ out)
+                                              int KB, const float *__restrict__ bias, float *__restrict__ out)
 {
     using FT = typename Frag<K32>::T;
     constexpr int KW = Frag<K32>::KW;
@@ -150,7 +191,7 @@ __global__ __launch_bounds__(256) void k_conv(ConvGeo g, const uint16_t *__restr
         for (int mb = 0; mb < MB; ++mb) {
             a[mb] = FT{};
             if (kin && live[mb]) {
-                const int64_t u = src_voxel(g, px[mb], py[mb], pz[mb], dx, dy, dz);
+                const int64_t u = src_voxel(g, px[mb], py[mb], pz[mb], dx, dy, dz, 0, g.nz);
                 if (u >= 0) a[mb] = *(const FT *)(X + u * g.cin + ci);
             }
         }
@@ -171,209 +212,188 @@ __global__ __launch_bounds__(256) void k_conv(ConvGeo g, const uint16_t *__restr
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t vo = v0 + mb * 16 + mr + i;
-                if (vo >= g.V) continue;
-                float val = acc[mb][nb][i] + bb;
-                if (skip) val += bf2f(skip[vo * g.cout + co]);
-                if (relu) val = val > 0.f ? val : 0.f;
-                if (OUT_BF16) ((uint16_t *)out)[vo * g.cout + co] = f2bf(val);
-                else ((float *)out)[vo * g.cout + co] = val;
+                if (vo < g.V) out[vo * g.cout + co] = acc[mb][nb][i] + bb;
             }
     }
 }
 
-// LDS-tiled variant for inputs of at most 32 channels: a workgroup computes a
-// 16 (x) x 4 (y) x 4 (z) output block; the 18 x 6 x 6 input halo (zero outside
-// the grid, nearest-up-sampled when `up`) and the packed weights are staged in
-// LDS once, so every MFMA operand comes from LDS.  Wave w owns output plane
-// z0 + w; its voxel block mb is the x-run at y0 + mb.
-constexpr int CT_X = 16, CT_Y = 4, CT_Z = 4, CH_X = CT_X + 2, CH_Y = CT_Y + 2, CH_Z = CT_Z + 2;
-constexpr int CH_N = CH_X * CH_Y * CH_Z;   // 648 halo voxels
+// The convolution of the network's channel counts (4, 16, 32 or 64 inputs).  A
+// workgroup takes bricks of 16 (x) x 4 (y) x TZ (z) output voxels (brick b,
+// b + gridDim.x, ...): a brick's input halo (zero outside the sample, nearest
+// up-sampled when `up`) goes to LDS from registers that were loaded during the
+// previous brick's MFMAs.  Wave w owns the brick's plane w % TZ and the output
+// channels of its split w / TZ: four x-rows of 16 voxels x 16 NBW channels.
+// blockIdx.y and the splits divide the output channels.
+//
+// The weights are the MFMA's rows (m = output channel) and the voxels its
+// columns (n = voxel), so a lane ends with 4 consecutive channels of one voxel
+// and stores them, and reads bias, skip and mask, in one access; a wave's
+// store covers 16 whole neighbouring voxels.  The K order (tap, channel) is the
+// packed weights'.
+//
+// The K loop is unrolled: with 32 and 64 channels every operand address is one
+// per-lane base and an immediate, and the x-rows that two taps of one (z, x)
+// offset share are read once; with 4 and 16, where a K block spans taps, the
+// per-lane offsets of the blocks are kept in registers.  (Decoding the tap of
+// every K block cost about as many cycles as its MFMAs, and an epilogue through
+// LDS as many again.  Measured at 128x128x64, before and after: 4->16 33 -> 22
+// us, 16->16 67 -> 37, up-sampled 32->16 118 -> 58 (500 TFLOP/s); at 64x64x32:
+// 16->32 18 -> 13, up-sampled 64->32 75 -> 28.  The bound is the LDS reads: one
+// 16-byte operand per lane and MFMA with 16 output channels.)  The weights are
+// staged in LDS once per workgroup; those of 64 channels do not fit beside a
+// halo and come through the L1 from the L2.  VS, the LDS stride of a voxel, is
+// an odd number of 16-byte units, so that the 16 voxels of a fragment read
+// fall on distinct banks.
+template <int CIN, int NBW, int NSPLIT, int TZ> struct ConvCfg {
+    static constexpr int NT = 64 * TZ * NSPLIT;
+    static constexpr int KB = conv_kblocks(CIN);
+    static constexpr int FB = conv_frag_bytes(CIN);
+    static constexpr bool WLDS = CIN <= 32;
+    static constexpr int HN = 18 * 6 * (TZ + 2);
+    static constexpr int VS = CIN == 4 ? 4 : CIN + 8;   // shorts
+    static constexpr size_t WBYTES = WLDS ? (size_t)KB * NSPLIT * NBW * 64 * FB : 0;
+    static constexpr size_t LDS = WBYTES + (size_t)HN * VS * 2;
+};
 
-// the epilogue of one or two output blocks stages each wave's results in the
-// halo area ([64 voxels][16 NB + 1] floats per wave), made larger if needed
-__host__ __device__ constexpr size_t conv_stage_bytes(int nb) { return nb <= 2 ? (size_t)4 * 64 * (16 * nb + 1) * 4 : 0; }
-inline size_t conv_lds_bytes(int cin, int KB, int NB)
-{
-    return std::max((size_t)CH_N * cin * 2, conv_stage_bytes(NB)) + (size_t)KB * NB * 64 * conv_frag_bytes(cin);
-}
+typedef short v8su __attribute__((ext_vector_type(8), aligned(8)));    // a caller's input is at least 8-byte aligned
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t v4hu __attribute__((ext_vector_type(4), aligned(4)));
 
-// Global -> LDS copy of n 16-byte words by the workgroup, eight loads in
-// flight per thread before their stores.
-__device__ inline void stage_words(const v4s *__restrict__ src, v4s *dst, int n)
+template <int CIN, int NBW, int NSPLIT, int TZ, bool OUT_BF16>
+__global__ __launch_bounds__(64 * TZ * NSPLIT) void k_conv_lds(ConvGeo g, const uint16_t *__restrict__ X,
+                                                               const void *__restrict__ Wfv, Epilogue ep)
 {
-    for (int e0 = 0; e0 < n; e0 += 8 * 256) {
-        v4s v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int e = e0 + i * 256 + (int)threadIdx.x;
-            if (e < n) v[i] = src[e];
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int e = e0 + i * 256 + (int)threadIdx.x;
-            if (e < n) dst[e] = v[i];
-        }
-    }
-}
-
-// LDS-tiled variant for inputs of CIN = 4, 16 or 32 channels.  A workgroup
-// stages the packed weights in LDS once and then walks bricks of 16 (x) x 4
-// (y) x 4 (z) output voxels (brick b, b + gridDim.x, ...): the brick's
-// 18 x 6 x 6 input halo (zero outside the grid, nearest-up-sampled when `up`)
-// goes to LDS from registers that were loaded during the previous brick's
-// MFMAs, so every MFMA operand comes from LDS and no load waits on the
-// critical path.  Wave w owns output plane z0 + w; its voxel block mb is the
-// x-run at y0 + mb.
-template <int NB, bool OUT_BF16, int CIN>
-__global__ __launch_bounds__(256) void k_conv_lds(ConvGeo g, const uint16_t *__restrict__ X, const void *__restrict__ Wfv,
-                                                  int KB, const float *__restrict__ bias,
-                                                  const uint16_t *__restrict__ skip, int relu, void *__restrict__ out)
-{
-    constexpr bool K32 = CIN % 8 == 0;
-    using FT = typename Frag<K32>::T;
-    constexpr int KW = Frag<K32>::KW;
-    constexpr int C4 = CIN / 4, NI = (CH_N * C4 + 255) / 256;   // halo words (4 channels) per thread
+    using C = ConvCfg<CIN, NBW, NSPLIT, TZ>;
+    using FT = typename Frag<CIN % 8 == 0>::T;
+    constexpr int NT = C::NT, KB = C::KB, VS = C::VS, NBG = NSPLIT * NBW;
+    constexpr int WPT = CIN == 4 ? 4 : 8, CW = CIN / WPT;       // channels per halo word, words per voxel
+    constexpr int NI = (C::HN * CW + NT - 1) / NT;
     extern __shared__ __align__(16) unsigned char cl[];
-    FT *wl = (FT *)cl;                                          // [KB][NB][64]
-    uint16_t *xl = (uint16_t *)(cl + (size_t)KB * NB * 64 * sizeof(FT));   // [648][CIN]
+    FT *wl = (FT *)cl;                                          // [KB][NBG][64]
+    uint16_t *xl = (uint16_t *)(cl + C::WBYTES);                // [HN][VS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ntx = (g.nx + CT_X - 1) / CT_X, nty = (g.ny + CT_Y - 1) / CT_Y, ntz = (g.nz + CT_Z - 1) / CT_Z;
-    const int nbricks = ntx * nty * ntz;
-    stage_words((const v4s *)Wfv, (v4s *)wl, KB * NB * 64 * (int)(sizeof(FT) / sizeof(v4s)));
-    v4s hv[NI];
-    auto load = [&](int b) {
-        const int x0 = (b % ntx) * CT_X, y0 = ((b / ntx) % nty) * CT_Y, z0 = (b / (ntx * nty)) * CT_Z;
+    const int plane = wave % TZ, split = wave / TZ;
+    const int NB = g.cout / 16;
+    const int nbw0 = blockIdx.y * NBG + split * NBW;            // this wave's first channel block
+    const FT *Wf = (const FT *)Wfv;
+    if constexpr (C::WLDS)
+        for (int e = tid; e < KB * NBG * 64; e += NT)
+            wl[e] = Wf[((int64_t)(e / (NBG * 64)) * NB + blockIdx.y * NBG + (e / 64) % NBG) * 64 + (e & 63)];
+    // halo words of this thread: voxel (hx, hy, hz) packed, and its input voxel from the brick's
+    int hpos[NI], hrel[NI];
+    const int sx = g.up ? g.nx >> 1 : g.nx, sy = g.up ? g.ny >> 1 : g.ny;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int h = (tid + NT * i) / CW;
+        const int hx = h % 18, hy = (h / 18) % 6, hz = h / 108;
+        hpos[i] = hx | hy << 8 | hz << 16;
+        hrel[i] = g.up ? ((hx - 1) >> 1) + sx * (((hy - 1) >> 1) + sy * ((hz - 1) >> 1))
+                       : (hx - 1) + sx * ((hy - 1) + sy * (hz - 1));
+    }
+    using WT = std::conditional_t<CIN == 4, v4s, v8s>;
+    WT hv[NI];
+    auto load = [&](const Brick &k) {
+        const int64_t base = g.up ? (k.x0 >> 1) + (int64_t)sx * ((k.y0 >> 1) + (int64_t)sy * (k.z0 >> 1))
+                                  : k.x0 + (int64_t)sx * (k.y0 + (int64_t)sy * k.z0);
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int e = tid + 256 * i;
-            const int h = e / C4, q = e - h * C4;
-            const int hx = h % CH_X, hy = (h / CH_X) % CH_Y, hz = h / (CH_X * CH_Y);
-            hv[i] = v4s{0, 0, 0, 0};
-            if (e < CH_N * C4) {
-                const int64_t u = src_voxel(g, x0, y0, z0, hx - 1, hy - 1, hz - 1);
-                if (u >= 0) hv[i] = *(const v4s *)(X + u * CIN + 4 * q);
+            const int e = tid + NT * i, ha = hpos[i];
+            const int a = k.x0 + (ha & 255) - 1, b = k.y0 + ((ha >> 8) & 255) - 1, c = k.z0 + (ha >> 16) - 1;
+            hv[i] = WT{};
+            if (e < C::HN * CW && (unsigned)a < (unsigned)g.nx && (unsigned)b < (unsigned)g.ny && c >= k.zlo && c < k.zhi) {
+                const uint16_t *src = X + (base + hrel[i]) * CIN + WPT * (e % CW);
+                if constexpr (CIN == 4) hv[i] = *(const v4s *)src;
+                else hv[i] = *(const v8su *)src;
             }
         }
     };
-    const int m = lane & 15, kq = (KW / 4) * (lane >> 4);
-    const int n = lane & 15, mr = 4 * (lane >> 4);
-    const int K = 27 * CIN;
-    if ((int)blockIdx.x < nbricks) load(blockIdx.x);
+    const int n = lane & 15, quad = lane >> 4;
+    // LDS offset (shorts) of K block kb for this lane, row 0 of its plane
+    auto tap_off = [](int t) { return ((t / 9) * 108 + ((t / 3) % 3) * 18 + t % 3) * VS; };
+    const int lane_base = (plane * 108 + n) * VS + (CIN >= 32 ? 8 * quad : CIN == 16 ? 8 * (quad & 1) : 0);
+    int koff[CIN <= 16 ? KB : 1];
+    if constexpr (CIN <= 16)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const int t = CIN == 16 ? 2 * kb + (quad >> 1) : 4 * kb + quad;
+            koff[kb] = lane_base + tap_off(t < 27 ? t : 26);
+        }
+    const bool last_in = CIN == 16 ? quad < 2 : CIN == 4 ? quad < 3 : true;   // the last K block ends at tap 27
+    v4f bias[NBW];
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bias[nb][i] = ep.bias ? ep.bias[(nbw0 + nb) * 16 + 4 * quad + i] : 0.f;
+    const int nbricks = brick_count(g, TZ);
+    Brick cur = brick_of(g, blockIdx.x, TZ);
+    if ((int)blockIdx.x < nbricks) load(cur);
     for (int b = blockIdx.x; b < nbricks; b += gridDim.x) {
-        const int x0 = (b % ntx) * CT_X, y0 = ((b / ntx) % nty) * CT_Y, z0 = (b / (ntx * nty)) * CT_Z;
+        const Brick k = cur;
         __syncthreads();   // the previous brick's operands have been read (and the weights written)
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int e = tid + 256 * i;
-            if (e < CH_N * C4) *(v4s *)(xl + (size_t)e * 4) = hv[i];   // [h][CIN] = word e
+            const int e = tid + NT * i;
+            if (e < C::HN * CW) *(WT *)(xl + (e / CW) * VS + WPT * (e % CW)) = hv[i];
         }
         __syncthreads();
-        if (b + (int)gridDim.x < nbricks) load(b + gridDim.x);
-        v4f acc[CT_Y][NB];
+        if (b + (int)gridDim.x < nbricks) {
+            cur = brick_of(g, b + gridDim.x, TZ);
+            load(cur);
+        }
+        v4f acc[4][NBW];
 #pragma unroll
-        for (int mb = 0; mb < CT_Y; ++mb)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = v4f{0.f, 0.f, 0.f, 0.f};
+            for (int nb = 0; nb < NBW; ++nb) acc[r][nb] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            const int k = kb * KW + kq;
-            const bool kin = k < K;
-            const int tap = kin ? k / CIN : 0, ci = k - tap * CIN;
-            const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;   // halo offsets (0..2)
-            FT a[CT_Y];
+            FT x[4];
 #pragma unroll
-            for (int mb = 0; mb < CT_Y; ++mb) {
-                const int h = ((wave + dz) * CH_Y + (mb + dy)) * CH_X + (m + dx);
-                a[mb] = kin ? *(const FT *)(xl + (size_t)h * CIN + ci) : FT{};
+            for (int r = 0; r < 4; ++r) {
+                const int at = CIN <= 16 ? koff[CIN <= 16 ? kb : 0]
+                                         : lane_base + tap_off(CIN == 64 ? kb >> 1 : kb) + (CIN == 64 ? 32 * (kb & 1) : 0);
+                x[r] = *(const FT *)(xl + at + r * 18 * VS);
+                if (kb == KB - 1 && !last_in) x[r] = FT{};
             }
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const FT bf = wl[(kb * NB + nb) * 64 + lane];
+            for (int nb = 0; nb < NBW; ++nb) {
+                const FT w = C::WLDS ? wl[(kb * NBG + split * NBW + nb) * 64 + lane]
+                                     : Wf[((int64_t)kb * NB + nbw0 + nb) * 64 + lane];
 #pragma unroll
-                for (int mb = 0; mb < CT_Y; ++mb) acc[mb][nb] = mfma_k(a[mb], bf, acc[mb][nb]);
+                for (int r = 0; r < 4; ++r) acc[r][nb] = mfma_k(w, x[r], acc[r][nb]);
             }
         }
-        if constexpr (NB <= 2) {
-            // epilogue through LDS (16 or 32 output channels): each wave puts
-            // its 64 voxels x 16 NB channels into the halo area, which no wave
-            // reads any more, then lane v takes voxel v whole (x = v % 16,
-            // y = v / 16), adds bias and skip, applies the ReLU and stores the
-            // voxel with 16-byte accesses instead of one channel per lane and store
-            constexpr int C = 16 * NB, SC = C + 1;          // channels; staging row (one word of padding)
-            float *stg = (float *)xl + wave * (64 * SC);
-            __syncthreads();   // every wave is done with the halo
+        const int vx = k.x0 + n, vz = k.z0 + plane;
+        if (vx < g.nx && vz < k.zhi) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
+            for (int r = 0; r < 4; ++r) {
+                if (k.y0 + r >= g.ny) break;
+                const int64_t vo = (vx + (int64_t)g.nx * (k.y0 + r + (int64_t)g.ny * vz)) * g.cout + nbw0 * 16 + 4 * quad;
 #pragma unroll
-                for (int mb = 0; mb < CT_Y; ++mb)
+                for (int nb = 0; nb < NBW; ++nb) {
+                    v4f v = acc[r][nb] + bias[nb];
+                    const int64_t o = vo + 16 * nb;
+                    if (ep.skip) {
+                        const v4hu q = *(const v4hu *)(ep.skip + o);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) stg[(mb * 16 + mr + i) * SC + nb * 16 + n] = acc[mb][nb][i];
-            __syncthreads();
-            const int x = x0 + (lane & 15), y = y0 + (lane >> 4), z = z0 + wave;
-            if (x < g.nx && y < g.ny && z < g.nz) {
-                const int64_t vo = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
-                float v[C];
-#pragma unroll
-                for (int c = 0; c < C; ++c) v[c] = stg[lane * SC + c] + (bias ? bias[c] : 0.f);
-                if (skip) {
-                    const uint4 *sp = (const uint4 *)(skip + vo * C);
-#pragma unroll
-                    for (int q = 0; q < C / 8; ++q) {
-                        const uint4 sq = sp[q];
-                        const uint32_t sw[4] = {sq.x, sq.y, sq.z, sq.w};
-#pragma unroll
-                        for (int c = 0; c < 8; ++c) v[8 * q + c] += bf2f((uint16_t)(sw[c >> 1] >> (16 * (c & 1))));
+                        for (int i = 0; i < 4; ++i) v[i] += bf2f(q[i]);
                     }
-                }
-                if (relu)
+                    if (ep.relu)
 #pragma unroll
-                    for (int c = 0; c < C; ++c) v[c] = v[c] > 0.f ? v[c] : 0.f;
-                if (OUT_BF16) {
-                    uint4 *op = (uint4 *)((uint16_t *)out + vo * C);
+                        for (int i = 0; i < 4; ++i) v[i] = v[i] > 0.f ? v[i] : 0.f;
+                    if (ep.mask) {
+                        const v4hu q = *(const v4hu *)(ep.mask + o);
 #pragma unroll
-                    for (int q = 0; q < C / 8; ++q) {
-                        uint32_t pw[4];
-#pragma unroll
-                        for (int h = 0; h < 4; ++h)
-                            pw[h] = (uint32_t)f2bf(v[8 * q + 2 * h]) | ((uint32_t)f2bf(v[8 * q + 2 * h + 1]) << 16);
-                        op[q] = uint4{pw[0], pw[1], pw[2], pw[3]};
+                        for (int i = 0; i < 4; ++i) v[i] = bf2f(q[i]) > 0.f ? v[i] : 0.f;
                     }
-                } else {
-                    float4 *op = (float4 *)((float *)out + vo * C);
+                    if (ep.copy) *(v4fu *)(ep.copy + o) = v;
+                    if (OUT_BF16) {
+                        v4hu h;
 #pragma unroll
-                    for (int q = 0; q < C / 4; ++q) op[q] = float4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-                }
-            }
-        } else {
-            // epilogue: the skip inputs are loaded together, then bias, skip, ReLU, store
-            const int z = z0 + wave;
-            float sk[NB][CT_Y][4];
-    #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-    #pragma unroll
-                for (int mb = 0; mb < CT_Y; ++mb)
-    #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int x = x0 + mr + i, y = y0 + mb;
-                        sk[nb][mb][i] = 0.f;
-                        if (skip && x < g.nx && y < g.ny && z < g.nz)
-                            sk[nb][mb][i] = bf2f(skip[(x + (int64_t)g.nx * (y + (int64_t)g.ny * z)) * g.cout + nb * 16 + n]);
-                    }
-    #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int co = nb * 16 + n;
-                const float bb = bias ? bias[co] : 0.f;
-    #pragma unroll
-                for (int mb = 0; mb < CT_Y; ++mb) {
-                    const int y = y0 + mb;
-    #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int x = x0 + mr + i;
-                        if (x >= g.nx || y >= g.ny || z >= g.nz) continue;
-                        const int64_t vo = x + (int64_t)g.nx * (y + (int64_t)g.ny * z);
-                        float val = acc[mb][nb][i] + bb + sk[nb][mb][i];
-                        if (relu) val = val > 0.f ? val : 0.f;
-                        if (OUT_BF16) ((uint16_t *)out)[vo * g.cout + co] = f2bf(val);
-                        else ((float *)out)[vo * g.cout + co] = val;
+                        for (int i = 0; i < 4; ++i) h[i] = f2bf(v[i]);
+                        *(v4hu *)((uint16_t *)ep.out + o) = h;
+                    } else {
+                        *(v4fu *)((float *)ep.out + o) = v;
                     }
                 }
             }
@@ -381,67 +401,65 @@ __global__ __launch_bounds__(256) void k_conv_lds(ConvGeo g, const uint16_t *__r
     }
 }
 
-constexpr size_t CONV_LDS_MAX = 96 * 1024;
-
-// launch of k_conv: NB = cout / 16 column blocks; 4 voxel blocks per wave on
-// large levels (weight fragments reused four times), 1 on small ones (more waves)
-template <bool OUT_BF16>
-hipError_t launch_conv(hipStream_t st, const ConvGeo &g, const uint16_t *X, const void *Wf, int KB, const float *bias,
-                       const uint16_t *skip, int relu, void *out)
+template <int CIN, int NBW, int NSPLIT, int TZ, bool OUT_BF16>
+hipError_t launch_conv_lds(hipStream_t st, const ConvGeo &g, const uint16_t *X, const void *Wf, const Epilogue &ep)
 {
-    const int NB = (g.cout + 15) / 16;
-    if ((g.cin == 4 || g.cin == 16 || g.cin == 32) && conv_lds_bytes(g.cin, KB, NB) <= CONV_LDS_MAX && g.V >= 4096) {
-        static bool attr[2][5][3] = {};
-        const size_t sh = conv_lds_bytes(g.cin, KB, NB);
-        const int64_t nbricks = (int64_t)((g.nx + CT_X - 1) / CT_X) * ((g.ny + CT_Y - 1) / CT_Y) * ((g.nz + CT_Z - 1) / CT_Z);
-        // a few workgroups per CU, each walking many bricks with its weights staged once
-        const unsigned nwg = (unsigned)std::min<int64_t>(nbricks, 1024);
-        const int ci = g.cin == 4 ? 0 : (g.cin == 16 ? 1 : 2);
-#define RSV_CONVL(nb, cin)                                                                                                \
-    do {                                                                                                                  \
-        if (!attr[OUT_BF16][nb][ci]) {                                                                                    \
-            hipError_t e_ = hipFuncSetAttribute((const void *)k_conv_lds<nb, OUT_BF16, cin>,                              \
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)CONV_LDS_MAX);           \
-            if (e_ != hipSuccess) return e_;                                                                              \
-            attr[OUT_BF16][nb][ci] = true;                                                                                \
-        }                                                                                                                 \
-        hipLaunchKernelGGL((k_conv_lds<nb, OUT_BF16, cin>), dim3(nwg), dim3(256), sh, st, g, X, Wf, KB, bias, skip, relu, \
-                           out);                                                                                          \
-    } while (0)
-#define RSV_CONVL_NB(cin)                          \
-    do {                                           \
-        if (NB == 1) RSV_CONVL(1, cin);            \
-        else if (NB == 2) RSV_CONVL(2, cin);       \
-        else if (NB == 4) RSV_CONVL(4, cin);       \
-        else return hipErrorInvalidValue;          \
-    } while (0)
-        if (g.cin == 4) RSV_CONVL_NB(4);
-        else if (g.cin == 16) RSV_CONVL_NB(16);
-        else RSV_CONVL_NB(32);
-#undef RSV_CONVL_NB
-#undef RSV_CONVL
-        return hipGetLastError();
+    using C = ConvCfg<CIN, NBW, NSPLIT, TZ>;
+    auto *fn = &k_conv_lds<CIN, NBW, NSPLIT, TZ, OUT_BF16>;
+    if (C::LDS > 65536) {
+        const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
+        if (e != hipSuccess) return e;
     }
-    const int MB = g.V >= 131072 ? 4 : 1;
+    // a few workgroups per CU, each walking many bricks with its weights staged once
+    const unsigned groups = (unsigned)(g.cout / (16 * NSPLIT * NBW));
+    const unsigned nwg = std::min<unsigned>((unsigned)brick_count(g, TZ), 1024u / groups);
+    hipLaunchKernelGGL(fn, dim3(nwg, groups), dim3(C::NT), C::LDS, st, g, X, Wf, ep);
+    return hipGetLastError();
+}
+
+// Convolution launch: the staged kernels for the network's channel counts, else
+// the general one (rsv_conv3d alone: FP32 out, bias).
+template <bool OUT_BF16>
+hipError_t launch_conv(hipStream_t st, const ConvGeo &g, const uint16_t *X, const void *Wf, int KB, const Epilogue &ep)
+{
+    const int NB = g.cout / 16;
+    if (g.cout % 16 || (NB != 1 && NB != 2 && NB != 4)) return hipErrorInvalidValue;
+    const bool staged = (int64_t)g.nx * g.ny < (1 << 28);   // the staged kernel's halo offsets are 32-bit
+    if (!staged) {
+    } else if (g.cin == 4) {
+        if (NB == 1) return launch_conv_lds<4, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        if (NB == 2) return launch_conv_lds<4, 2, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        return launch_conv_lds<4, 4, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+    } else if (g.cin == 16) {
+        if (NB == 1) return launch_conv_lds<16, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        if (NB == 2) return launch_conv_lds<16, 2, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        return launch_conv_lds<16, 4, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+    } else if (g.cin == 32) {
+        if (NB == 1) return launch_conv_lds<32, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        return launch_conv_lds<32, 2, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+    } else if (g.cin == 64) {
+        if (NB == 1) return launch_conv_lds<64, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        return launch_conv_lds<64, 1, 2, 2, OUT_BF16>(st, g, X, Wf, ep);
+    }
+    if (OUT_BF16 || ep.skip || ep.relu || ep.mask || ep.copy || g.up || g.nz != g.nzs) return hipErrorInvalidValue;
+    const int MB = g.V >= 131072 ? 4 : 1;   // four voxel blocks per wave reuse the weights; small levels need the waves
     const int64_t waves = (g.V + 16 * MB - 1) / (16 * MB);
     const dim3 grid((unsigned)((waves + 3) / 4)), blk(256);
-#define RSV_CONV(mb, nb)                                                                                                \
-    do {                                                                                                                \
-        if (g.cin % 8 == 0)                                                                                             \
-            hipLaunchKernelGGL((k_conv<mb, nb, OUT_BF16, true>), grid, blk, 0, st, g, X, Wf, KB, bias, skip, relu, out);  \
-        else                                                                                                            \
-            hipLaunchKernelGGL((k_conv<mb, nb, OUT_BF16, false>), grid, blk, 0, st, g, X, Wf, KB, bias, skip, relu, out); \
+#define RSV_CONV(mb, nb)                                                                                             \
+    do {                                                                                                             \
+        if (g.cin % 8 == 0)                                                                                          \
+            hipLaunchKernelGGL((k_conv<mb, nb, true>), grid, blk, 0, st, g, X, Wf, KB, ep.bias, (float *)ep.out);    \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_conv<mb, nb, false>), grid, blk, 0, st, g, X, Wf, KB, ep.bias, (float *)ep.out);   \
     } while (0)
     if (MB == 4) {
         if (NB == 1) RSV_CONV(4, 1);
         else if (NB == 2) RSV_CONV(4, 2);
-        else if (NB == 4) RSV_CONV(4, 4);
-        else return hipErrorInvalidValue;
+        else RSV_CONV(4, 4);
     } else {
         if (NB == 1) RSV_CONV(1, 1);
         else if (NB == 2) RSV_CONV(1, 2);
-        else if (NB == 4) RSV_CONV(1, 4);
-        else return hipErrorInvalidValue;
+        else RSV_CONV(1, 4);
     }
 #undef RSV_CONV
     return hipGetLastError();
@@ -466,6 +484,7 @@ hipError_t launch_conv(hipStream_t st, const ConvGeo &g, const uint16_t *X, cons
 // (Summing them inside this kernel, by the last workgroup to finish, needs a
 // device-scope release per workgroup, which writes back the XCD's L2: 5x the
 // time of this kernel and the reduction together at 64x64x32.)
+constexpr int CT_Y = 4, CT_Z = 4, CH_Y = CT_Y + 2, CH_Z = CT_Z + 2;
 constexpr int DW_XS = CH_Z * CH_Y * 16 + 8;   // bf16 per input channel and shift (576 + padding)
 constexpr int DW_GS = CT_Z * CT_Y * 16 + 8;   // bf16 per output channel (256 + padding)
 constexpr int DW_PART = 27 * 256 + 16;        // floats per partial: 27 taps x 16 x 16, then 16 bias sums
@@ -489,8 +508,7 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int pair = blockIdx.x % npairs, chunk = blockIdx.x / npairs;
     const int cob_n = g.cout / 16, cib = pair / cob_n, cob = pair % cob_n;
-    const int ntx = (g.nx + CT_X - 1) / CT_X, nty = (g.ny + CT_Y - 1) / CT_Y, ntz = (g.nz + CT_Z - 1) / CT_Z;
-    const int nbricks = ntx * nty * ntz;
+    const int nbricks = brick_count(g, CT_Z);
     const int b_begin = chunk * bricks_per_chunk;
     const int b_end = b_begin + bricks_per_chunk < nbricks ? b_begin + bricks_per_chunk : nbricks;
     const int m = lane & 15, kx = 8 * ((lane >> 4) & 1), krow = lane >> 5;
@@ -502,7 +520,8 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
     float bq[4] = {0.f, 0.f, 0.f, 0.f};   // bias sums of channels 4 gq_q .. + 3
     DwRegs R;
     auto load = [&](int b) {
-        const int x0 = (b % ntx) * CT_X, y0 = ((b / ntx) % nty) * CT_Y, z0 = (b / (ntx * nty)) * CT_Z;
+        const Brick bk = brick_of(g, b, CT_Z);
+        const int x0 = bk.x0, y0 = bk.y0, z0 = bk.z0;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int u = tid + 256 * k;
@@ -514,7 +533,7 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
             for (int i = 0; i < 10; ++i) {
                 R.x[k][i] = v4s{0, 0, 0, 0};
                 if (ok) {
-                    const int64_t sv = src_voxel(g, x0, y0, z0, 8 * o + i - 1, hy - 1, hz - 1);
+                    const int64_t sv = src_voxel(g, x0, y0, z0, 8 * o + i - 1, hy - 1, hz - 1, bk.zlo, bk.zhi);
                     if (sv >= 0) R.x[k][i] = *(const v4s *)(X + sv * g.cin + c0);
                 }
             }
@@ -524,7 +543,7 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
         for (int i = 0; i < 8; ++i) {
             const int x = x0 + 8 * gq_o + i;
             R.gq[i] = v4s{0, 0, 0, 0};
-            if (tid < 128 && x < g.nx && y < g.ny && z < g.nz)
+            if (tid < 128 && x < g.nx && y < g.ny && z < bk.zhi)
                 R.gq[i] = *(const v4s *)(G + (x + (int64_t)g.nx * (y + (int64_t)g.ny * z)) * g.cout + cob * 16 + 4 * gq_q);
         }
     };
@@ -649,86 +668,113 @@ __global__ __launch_bounds__(256) void k_dw_reduce(const float *__restrict__ par
 }
 
 
-// sum over chunks (fixed order), added to the gradient
-__global__ void k_sum_chunks(const float *__restrict__ partials, int nchunk, int64_t n, float scale,
-                             float *__restrict__ grad)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        float s = 0.f;
-        for (int c = 0; c < nchunk; ++c) s += partials[(int64_t)c * n + e];
-        grad[e] += scale * s;
-    }
-}
-
 // ---------------------------------------------------------------- elementwise pieces
+
+// The level changes and the final layer work on 8 channels (16 bytes of BF16)
+// per access; channel counts are multiples of 16.  (One channel per thread was
+// bound by its 2-byte loads and index arithmetic: final layer 35 us, pools 21,
+// their adjoints 79 and the up-sampling's 39 per 2^20 voxels.)
+struct H8 { uint32_t w[4]; };   // 8 BF16 values
+__device__ inline H8 h8_load(const uint16_t *p) { const uint4 v = *(const uint4 *)p; return H8{{v.x, v.y, v.z, v.w}}; }
+__device__ inline float h8_get(const H8 &h, int i) { return bf2f((uint16_t)(h.w[i >> 1] >> (16 * (i & 1)))); }
+__device__ inline void h8_store(uint16_t *p, const float *v)
+{
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = (uint32_t)f2bf(v[2 * i]) | ((uint32_t)f2bf(v[2 * i + 1]) << 16);
+    *(uint4 *)p = uint4{w[0], w[1], w[2], w[3]};
+}
+// 8 FP32 values
+__device__ inline void f8_load(const float *p, float *v)
+{
+    const float4 a = ((const float4 *)p)[0], b = ((const float4 *)p)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
+// thread -> 8 channels from c of voxel (i, j, k) of an nx x ny x .. level
+struct Oct {
+    int64_t v;
+    int c, i, j, k;
+    __device__ inline Oct(int64_t e, int nx, int ny, int C)
+    {
+        v = e / (C / 8);
+        c = 8 * (int)(e - v * (C / 8));
+        const int64_t row = v / nx;
+        i = (int)(v - row * nx);
+        k = (int)(row / ny);
+        j = (int)(row - (int64_t)k * ny);
+    }
+};
 
 __global__ void k_pool(int nx, int ny, int nz, int C, const uint16_t *__restrict__ x, uint16_t *__restrict__ y)
 {
     const int mx = nx / 2, my = ny / 2;
-    const int64_t n = (int64_t)mx * my * (nz / 2) * C;
+    const int64_t n = (int64_t)mx * my * (nz / 2) * (C / 8);
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const int c = (int)(e % C);
-        const int64_t u = e / C;
-        const int i = (int)(u % mx), j = (int)((u / mx) % my), k = (int)(u / ((int64_t)mx * my));
-        float s = 0.f;
+        const Oct o(e, mx, my, C);
+        H8 h[8];
+#pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int ii = 2 * i + (q & 1), jj = 2 * j + ((q >> 1) & 1), kk = 2 * k + (q >> 2);
-            s += bf2f(x[(ii + (int64_t)nx * (jj + (int64_t)ny * kk)) * C + c]);
+            const int ii = 2 * o.i + (q & 1), jj = 2 * o.j + ((q >> 1) & 1), kk = 2 * o.k + (q >> 2);
+            h[q] = h8_load(x + (ii + (int64_t)nx * (jj + (int64_t)ny * kk)) * C + o.c);
         }
-        y[e] = f2bf(0.125f * s);
+        float s[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            float t = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t += h8_get(h[q], c);
+            s[c] = 0.125f * t;
+        }
+        h8_store(y + o.v * C + o.c, s);
     }
 }
 
-// adjoint of the average pool (fine grid nx,ny,nz): dx += dy(parent) / 8
-__global__ void k_pool_bwd(int nx, int ny, int nz, int C, const float *__restrict__ dy, float *__restrict__ dx)
+// The backward pass's gradients are masked by the ReLU of the layer they reach
+// and rounded to BF16 by the kernel that forms them: G = bf16(g * [act > 0]).
+
+// skip path + adjoint of the average pool (fine grid nx,ny,nz): g = gs + dy(parent) / 8
+__global__ void k_pool_bwd(int nx, int ny, int nz, int C, const float *__restrict__ dy, const float *__restrict__ gs,
+                           const uint16_t *__restrict__ act, uint16_t *__restrict__ G)
 {
     const int mx = nx / 2, my = ny / 2;
-    const int64_t n = (int64_t)nx * ny * nz * C;
+    const int64_t n = (int64_t)nx * ny * nz * (C / 8);
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const int c = (int)(e % C);
-        const int64_t v = e / C;
-        const int i = (int)(v % nx), j = (int)((v / nx) % ny), k = (int)(v / ((int64_t)nx * ny));
-        dx[e] += 0.125f * dy[((i / 2) + (int64_t)mx * ((j / 2) + (int64_t)my * (k / 2))) * C + c];
+        const Oct o(e, nx, ny, C);
+        float g[8], d[8];
+        f8_load(gs + o.v * C + o.c, g);
+        f8_load(dy + ((o.i / 2) + (int64_t)mx * ((o.j / 2) + (int64_t)my * (o.k / 2))) * C + o.c, d);
+        const H8 a = h8_load(act + o.v * C + o.c);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) g[c] = h8_get(a, c) > 0.f ? g[c] + 0.125f * d[c] : 0.f;
+        h8_store(G + o.v * C + o.c, g);
     }
 }
 
-// adjoint of nearest up-sampling (fine grid nx,ny,nz): parent = sum of 8 children
-__global__ void k_up_bwd(int nx, int ny, int nz, int C, const float *__restrict__ dyf, float *__restrict__ dx)
+// adjoint of nearest up-sampling (fine grid nx,ny,nz): g(parent) = sum of 8 children
+__global__ void k_up_bwd(int nx, int ny, int nz, int C, const float *__restrict__ dyf, const uint16_t *__restrict__ act,
+                         uint16_t *__restrict__ G)
 {
     const int mx = nx / 2, my = ny / 2;
-    const int64_t n = (int64_t)mx * my * (nz / 2) * C;
+    const int64_t n = (int64_t)mx * my * (nz / 2) * (C / 8);
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const int c = (int)(e % C);
-        const int64_t u = e / C;
-        const int i = (int)(u % mx), j = (int)((u / mx) % my), k = (int)(u / ((int64_t)mx * my));
-        float s = 0.f;
+        const Oct o(e, mx, my, C);
+        float d[8][8], s[8];
+#pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int ii = 2 * i + (q & 1), jj = 2 * j + ((q >> 1) & 1), kk = 2 * k + (q >> 2);
-            s += dyf[(ii + (int64_t)nx * (jj + (int64_t)ny * kk)) * C + c];
+            const int ii = 2 * o.i + (q & 1), jj = 2 * o.j + ((q >> 1) & 1), kk = 2 * o.k + (q >> 2);
+            f8_load(dyf + (ii + (int64_t)nx * (jj + (int64_t)ny * kk)) * C + o.c, d[q]);
         }
-        dx[e] = s;
+        const H8 a = h8_load(act + o.v * C + o.c);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            float t = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t += d[q][c];
+            s[c] = h8_get(a, c) > 0.f ? t : 0.f;
+        }
+        h8_store(G + o.v * C + o.c, s);
     }
-}
-
-// G = bf16(g * [y > 0]); optional FP32 copy of the masked gradient (skip paths)
-__global__ void k_mask(int64_t n, const float *__restrict__ g, const uint16_t *__restrict__ y,
-                       uint16_t *__restrict__ G, float *__restrict__ gm)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const float v = bf2f(y[e]) > 0.f ? g[e] : 0.f;
-        G[e] = f2bf(v);
-        if (gm) gm[e] = v;
-    }
-}
-
-__global__ void k_add(int64_t n, const float *__restrict__ a, float *__restrict__ b)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) b[e] += a[e];
-}
-
-__global__ void k_f2bf(int64_t n, const float *__restrict__ a, uint16_t *__restrict__ b)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) b[e] = f2bf(a[e]);
 }
 
 // final 1x1x1 layer: y[v][co] = b[co] + sum_ci W[ci][co] d1[v][ci]
@@ -737,70 +783,126 @@ __global__ void k_final(int64_t V, int C, const uint16_t *__restrict__ d1, const
 {
     for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
         float o[3] = {b[0], b[1], b[2]};
-        for (int ci = 0; ci < C; ++ci) {
-            const float a = bf2f(d1[v * C + ci]);
-            for (int co = 0; co < 3; ++co) o[co] += W[ci * 3 + co] * a;
+        for (int c8 = 0; c8 < C; c8 += 8) {
+            const H8 h = h8_load(d1 + v * C + c8);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int co = 0; co < 3; ++co) o[co] += W[(c8 + i) * 3 + co] * h8_get(h, i);
         }
         for (int co = 0; co < 3; ++co) y[v * 3 + co] = o[co];
     }
 }
 
-// backward of the final layer, data part: gd1[v][ci] = sum_co W[ci][co] gy[v][co]
-__global__ void k_final_bwd_data(int64_t V, int C, const float *__restrict__ W, const float *__restrict__ gy,
-                                 float *__restrict__ gd1)
+// Backward of the final layer: G[v][ci] = bf16((sum_co W[ci][co] gy[v][co]) *
+// [d1 > 0]) and the partial weight and bias sums of the block's voxels,
+// partials[block][ci * 3 + co] = sum_v d1[v][ci] gy[v][co], [3 C + co] =
+// sum_v gy[v][co].  A thread keeps one channel (C divides the block), so d1 is
+// read once, whole voxels at a time.
+__global__ __launch_bounds__(256) void k_final_bwd(int64_t V, int C, const float *__restrict__ W,
+                                                   const uint16_t *__restrict__ d1, const float *__restrict__ gy,
+                                                   uint16_t *__restrict__ G, float *__restrict__ partials)
 {
-    const int64_t n = V * C;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
-        const int ci = (int)(e % C);
-        const int64_t v = e / C;
-        gd1[e] = W[ci * 3] * gy[v * 3] + W[ci * 3 + 1] * gy[v * 3 + 1] + W[ci * 3 + 2] * gy[v * 3 + 2];
+    __shared__ float red[6][256];
+    const int ci = threadIdx.x % C, vg = threadIdx.x / C, nv = 256 / C;
+    const float w0 = W[ci * 3], w1 = W[ci * 3 + 1], w2 = W[ci * 3 + 2];
+    float s[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int64_t v = (int64_t)blockIdx.x * nv + vg; v < V; v += (int64_t)gridDim.x * nv) {
+        const float a = bf2f(d1[v * C + ci]);
+        const float g0 = gy[v * 3], g1 = gy[v * 3 + 1], g2 = gy[v * 3 + 2];
+        const float g = w0 * g0 + w1 * g1 + w2 * g2;
+        G[v * C + ci] = f2bf(a > 0.f ? g : 0.f);
+        s[0] += a * g0; s[1] += a * g1; s[2] += a * g2;
+        s[3] += g0; s[4] += g1; s[5] += g2;
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) red[q][threadIdx.x] = s[q];
+    __syncthreads();
+    float *out = partials + (int64_t)blockIdx.x * (3 * C + 3);
+    for (int q = threadIdx.x; q < 3 * C + 3; q += 256) {
+        const int c = q < 3 * C ? q / 3 : 0, k = q < 3 * C ? q % 3 : 3 + q - 3 * C;
+        float t = 0.f;
+        for (int h = 0; h < nv; ++h) t += red[k][h * C + c];
+        out[q] = t;
     }
 }
 
-// weight part: partials[chunk][q] for q = ci*3 + co (sum_v d1[v][ci] gy[v][co]) and
-// q = 3C + co (sum_v gy[v][co]); grid.x = q, grid.y = voxel chunk
-__global__ __launch_bounds__(256) void k_final_dw(int64_t V, int C, int64_t chunk, const uint16_t *__restrict__ d1,
-                                                  const float *__restrict__ gy, float *__restrict__ partials)
+// grad[q] += scale * (sum of partials[b][q] over the blocks), one workgroup per
+// q: thread t adds blocks t, t + 256, ..., then a fixed tree over the threads
+__global__ __launch_bounds__(256) void k_sum_blocks(const float *__restrict__ partials, int nb, int n, float scale,
+                                                    float *__restrict__ grad)
 {
     __shared__ float red[256];
-    const int q = blockIdx.x, nw = 3 * C + 3;
-    const int co = q % 3, ci = q / 3;
-    const int64_t v_begin = (int64_t)blockIdx.y * chunk;
-    const int64_t v_end = v_begin + chunk < V ? v_begin + chunk : V;
     float s = 0.f;
-    for (int64_t v = v_begin + threadIdx.x; v < v_end; v += 256)
-        s += (ci < C ? bf2f(d1[v * C + ci]) : 1.f) * gy[v * 3 + co];
+    for (int b = threadIdx.x; b < nb; b += 256) s += partials[(int64_t)b * n + blockIdx.x];
     red[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) partials[(int64_t)blockIdx.y * nw + q] = red[0];
+    if (threadIdx.x == 0) grad[blockIdx.x] += scale * red[0];
 }
 
-// network input from a residual.  rtl: tile-lane FP64 vector (or NULL), rnat:
-// natural block-row FP64 vector (or NULL); s2 = sum r^2 over all entries.
-// x0[v][0..2] = r/s (s = rms), x0[v][3] = standardised ln k (precomputed).
-__global__ void k_prep(Geo geo, const double *__restrict__ rtl, const double *__restrict__ rnat,
+// Batched kernels: nb samples, sample b's residual at r + b 3V, its scalars
+// s2[b] and so on.
+
+// partials[block][b] = the block's part of sum r^2 of sample b = blockIdx.y
+__global__ __launch_bounds__(256) void k_sumsq(int64_t n, const double *__restrict__ r, double *__restrict__ partials)
+{
+    __shared__ double lds[4];
+    const double *x = r + (int64_t)blockIdx.y * n;
+    double s = 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) s += x[e] * x[e];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] = lds[0] + lds[1] + lds[2] + lds[3];
+}
+
+// partials[block][b] = the block's part of sum ln k (sum == nullptr), or of
+// sum (ln k - mean)^2 with mean = sum[b] / V, for sample b = blockIdx.y
+__global__ __launch_bounds__(256) void k_lnk_sums(int64_t V, const float *__restrict__ lnk,
+                                                  const double *__restrict__ sum, double *__restrict__ partials)
+{
+    __shared__ double lds[4];
+    const float *x = lnk + (int64_t)blockIdx.y * V;
+    const double m = sum ? sum[blockIdx.y] / (double)V : 0.0;
+    double s = 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < V; e += (int64_t)gridDim.x * 256) {
+        const double d = (double)x[e] - m;
+        s += sum ? d * d : d;
+    }
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) partials[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] = lds[0] + lds[1] + lds[2] + lds[3];
+}
+
+// network input from a residual.  rtl: tile-lane FP64 vector (or NULL, one
+// sample), rnat: natural block-row FP64 vectors (or NULL); s2[b] = sum r^2 over
+// all entries.  x0[v][0..2] = r/s (s = rms), x0[v][3] = standardised ln k
+// (precomputed).
+__global__ void k_prep(Geo geo, int nb, const double *__restrict__ rtl, const double *__restrict__ rnat,
                        const double *__restrict__ s2, const uint16_t *__restrict__ lnk_std,
                        uint16_t *__restrict__ x0)
 {
     const int64_t V = (int64_t)geo.nx * geo.ny * geo.nz;
-    const double s = sqrt(s2[0] / (double)(3 * V));
-    const double inv = s > 0.0 ? 1.0 / s : 0.0;
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
+    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < V * nb; g += (int64_t)gridDim.x * 256) {
+        const int64_t b = g / V, v = g - b * V;
+        const double s = sqrt(s2[b] / (double)(3 * V));
+        const double inv = s > 0.0 ? 1.0 / s : 0.0;
         const int i = (int)(v % geo.nx), j = (int)((v / geo.nx) % geo.ny), k = (int)(v / ((int64_t)geo.nx * geo.ny));
         double r[3];
         if (rtl) {
             const int64_t sl = slot_of(geo, i, j, k);
             for (int p = 0; p < 3; ++p) r[p] = rtl[vidx(sl, p)];
         } else {
-            const int64_t row = row_of(geo, i, j, k);
+            const int64_t row = b * V + row_of(geo, i, j, k);
             for (int p = 0; p < 3; ++p) r[p] = rnat[3 * row + p];
         }
-        for (int p = 0; p < 3; ++p) x0[v * 4 + p] = f2bf((float)(r[p] * inv));
-        x0[v * 4 + 3] = lnk_std[v];
+        for (int p = 0; p < 3; ++p) x0[g * 4 + p] = f2bf((float)(r[p] * inv));
+        x0[g * 4 + 3] = lnk_std[g];
     }
 }
 
@@ -823,31 +925,37 @@ __global__ void k_post(Geo geo, const float *__restrict__ y, const double *__res
     }
 }
 
-// standardised ln k (mean/std given) in voxel order, BF16; lnk given per block row
-__global__ void k_lnk_std(Geo geo, const float *__restrict__ lnk, double mean, double inv_sd, uint16_t *__restrict__ out)
+// standardised ln k in voxel order, BF16; lnk given per block row, its sum and
+// sum of squared deviations per sample
+__global__ void k_lnk_std(Geo geo, int nb, const float *__restrict__ lnk, const double *__restrict__ sum,
+                          const double *__restrict__ dev2, uint16_t *__restrict__ out)
 {
     const int64_t V = (int64_t)geo.nx * geo.ny * geo.nz;
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
+    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < V * nb; g += (int64_t)gridDim.x * 256) {
+        const int64_t b = g / V, v = g - b * V;
+        const double mean = sum[b] / (double)V, sd = sqrt(dev2[b] / (double)V);
+        const double inv_sd = sd > 0.0 ? 1.0 / sd : 0.0;
         const int i = (int)(v % geo.nx), j = (int)((v / geo.nx) % geo.ny), k = (int)(v / ((int64_t)geo.nx * geo.ny));
-        out[v] = f2bf((float)(((double)lnk[row_of(geo, i, j, k)] - mean) * inv_sd));
+        out[g] = f2bf((float)(((double)lnk[b * V + row_of(geo, i, j, k)] - mean) * inv_sd));
     }
 }
 
-// loss partials: sum (y - e/s)^2 and sum (e/s)^2 for one sample; e natural FP64
+// loss partials of sample b = blockIdx.y, partials[block][2 b ..]: sum (y - e/s)^2
+// and sum (e/s)^2; e natural FP64
 __global__ __launch_bounds__(256) void k_loss(Geo geo, const float *__restrict__ y, const double *__restrict__ e,
                                               const double *__restrict__ s2, double *__restrict__ partials)
 {
     __shared__ double r0[256], r1[256];
-    const int64_t V = (int64_t)geo.nx * geo.ny * geo.nz;
-    const double s = sqrt(s2[0] / (double)(3 * V));
+    const int64_t V = (int64_t)geo.nx * geo.ny * geo.nz, vb = (int64_t)blockIdx.y * V;
+    const double s = sqrt(s2[blockIdx.y] / (double)(3 * V));
     const double inv = s > 0.0 ? 1.0 / s : 0.0;
     double a = 0.0, b = 0.0;
     for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
         const int i = (int)(v % geo.nx), j = (int)((v / geo.nx) % geo.ny), k = (int)(v / ((int64_t)geo.nx * geo.ny));
-        const int64_t row = row_of(geo, i, j, k);
+        const int64_t row = vb + row_of(geo, i, j, k);
         for (int p = 0; p < 3; ++p) {
             const double t = e[3 * row + p] * inv;
-            const double d = (double)y[v * 3 + p] - t;
+            const double d = (double)y[(vb + v) * 3 + p] - t;
             a += d * d;
             b += t * t;
         }
@@ -859,21 +967,27 @@ __global__ __launch_bounds__(256) void k_loss(Geo geo, const float *__restrict__
         if ((int)threadIdx.x < w) { r0[threadIdx.x] += r0[threadIdx.x + w]; r1[threadIdx.x] += r1[threadIdx.x + w]; }
         __syncthreads();
     }
-    if (threadIdx.x == 0) { partials[2 * blockIdx.x] = r0[0]; partials[2 * blockIdx.x + 1] = r1[0]; }
+    if (threadIdx.x == 0) {
+        double *out = partials + 2 * ((int64_t)blockIdx.x * gridDim.y + blockIdx.y);
+        out[0] = r0[0];
+        out[1] = r1[0];
+    }
 }
 
-// gy = scale * 2 (y - e/s) / ||e/s||^2   (tt = ||e/s||^2 in sc[0])
-__global__ void k_gy(Geo geo, const float *__restrict__ y, const double *__restrict__ e, const double *__restrict__ s2,
-                     const double *__restrict__ tt, float scale, float *__restrict__ gy)
+// gy = scale * 2 (y - e/s) / ||e/s||^2   (loss[2 b + 1] = ||e/s||^2 of sample b)
+__global__ void k_gy(Geo geo, int nb, const float *__restrict__ y, const double *__restrict__ e,
+                     const double *__restrict__ s2, const double *__restrict__ loss, float scale,
+                     float *__restrict__ gy)
 {
     const int64_t V = (int64_t)geo.nx * geo.ny * geo.nz;
-    const double s = sqrt(s2[0] / (double)(3 * V));
-    const double inv = s > 0.0 ? 1.0 / s : 0.0;
-    const double f = 2.0 * (double)scale / tt[0];
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) {
+    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < V * nb; g += (int64_t)gridDim.x * 256) {
+        const int64_t b = g / V, v = g - b * V;
+        const double s = sqrt(s2[b] / (double)(3 * V));
+        const double inv = s > 0.0 ? 1.0 / s : 0.0;
+        const double f = 2.0 * (double)scale / loss[2 * b + 1];
         const int i = (int)(v % geo.nx), j = (int)((v / geo.nx) % geo.ny), k = (int)(v / ((int64_t)geo.nx * geo.ny));
-        const int64_t row = row_of(geo, i, j, k);
-        for (int p = 0; p < 3; ++p) gy[v * 3 + p] = (float)(f * ((double)y[v * 3 + p] - e[3 * row + p] * inv));
+        const int64_t row = b * V + row_of(geo, i, j, k);
+        for (int p = 0; p < 3; ++p) gy[g * 3 + p] = (float)(f * ((double)y[g * 3 + p] - e[3 * row + p] * inv));
     }
 }
 
@@ -953,29 +1067,41 @@ struct rsv_net {
     float *P = nullptr, *G = nullptr, *M = nullptr, *Vv = nullptr;   // FP32 master, gradient, Adam moments
     v4s *wf[10] = {nullptr}, *wt[10] = {nullptr};                    // packed BF16 weights
     bool packed = false;
-    // workspace for one grid
-    int wx = 0, wy = 0, wz = 0;
+    // workspace for up to `wb` samples of one grid
+    int wx = 0, wy = 0, wz = 0, wb = 0;
     uint16_t *x0 = nullptr, *a1 = nullptr, *s1 = nullptr, *p1 = nullptr, *a2 = nullptr, *s2 = nullptr, *p2 = nullptr,
              *a3 = nullptr, *b3 = nullptr, *d2a = nullptr, *d2 = nullptr, *d1a = nullptr, *d1 = nullptr;
-    uint16_t *Gb = nullptr, *lnk_std = nullptr;
-    float *y = nullptr, *gy = nullptr, *g1 = nullptr, *g2 = nullptr, *gs1 = nullptr, *gs2 = nullptr, *part = nullptr;
-    double *d_sc = nullptr;   // [0] sum r^2, [1] sum (e/s)^2
+    uint16_t *lnk_std = nullptr;
+    float *y = nullptr;
+    // backward pass: BF16 gradients of the layer at hand and the next, FP32 ones that a pool
+    // or an up-sampling sums, and the skip paths'
+    bool wback = false;
+    uint16_t *Ga = nullptr, *Gb = nullptr;
+    float *gy = nullptr, *g1 = nullptr, *gs1 = nullptr, *gs2 = nullptr, *part = nullptr;
+    // per sample: sum r^2 [wb]; sum ln k [wb]; sum (ln k - mean)^2 [wb]; loss sums [wb][2]
+    double *d_sc = nullptr;
     int64_t part_cap = 0;
+    double *sum_r2() const { return d_sc; }
+    double *sum_lnk() const { return d_sc + wb; }
+    double *dev_lnk() const { return d_sc + 2 * wb; }
+    double *loss() const { return d_sc + 3 * wb; }
 
     ~rsv_net() { release(); }
     void free_ws()
     {
-        void *ps[] = {x0, a1, s1, p1, a2, s2, p2, a3, b3, d2a, d2, d1a, d1, Gb, lnk_std, y, gy, g1, g2, gs1, gs2, part};
+        void *ps[] = {x0, a1, s1, p1, a2, s2, p2, a3, b3, d2a, d2, d1a, d1, Ga, Gb, lnk_std, y, gy, g1, gs1, gs2, part, d_sc};
         for (void *p : ps) dev_free(p);
-        x0 = a1 = s1 = p1 = a2 = s2 = p2 = a3 = b3 = d2a = d2 = d1a = d1 = Gb = lnk_std = nullptr;
-        y = gy = g1 = g2 = gs1 = gs2 = part = nullptr;
+        x0 = a1 = s1 = p1 = a2 = s2 = p2 = a3 = b3 = d2a = d2 = d1a = d1 = Ga = Gb = lnk_std = nullptr;
+        y = gy = g1 = gs1 = gs2 = part = nullptr;
+        d_sc = nullptr;
         part_cap = 0;
-        wx = wy = wz = 0;
+        wx = wy = wz = wb = 0;
+        wback = false;
     }
     void release()
     {
         free_ws();
-        dev_free(P); dev_free(G); dev_free(M); dev_free(Vv); dev_free(d_sc);
+        dev_free(P); dev_free(G); dev_free(M); dev_free(Vv);
         for (int l = 0; l < 10; ++l) { dev_free(wf[l]); dev_free(wt[l]); }
     }
 };
@@ -997,32 +1123,46 @@ static rsv_status net_pack(rsv_net *n)
     return RSV_OK;
 }
 
-static rsv_status net_ws(rsv_net *n, int nx, int ny, int nz)
+// Workspace for nb samples of a grid, with the backward pass's when `back`;
+// kept while it is large enough.
+static rsv_status net_ws(rsv_net *n, int nx, int ny, int nz, int nb, bool back)
 {
-    if (n->wx == nx && n->wy == ny && n->wz == nz) return RSV_OK;
+    const bool same = n->wx == nx && n->wy == ny && n->wz == nz;
+    if (same && n->wb >= nb && (n->wback || !back)) return RSV_OK;
     rsv_ctx *c = n->c;
     RSV_HIP(c, hipStreamSynchronize(c->stream));
+    if (same) {
+        nb = std::max(nb, n->wb);
+        back = back || n->wback;
+    }
     n->free_ws();
-    const int64_t V1 = (int64_t)nx * ny * nz, V2 = V1 / 8, V3 = V2 / 8;
+    const int64_t V1 = (int64_t)nx * ny * nz * nb, V2 = V1 / 8, V3 = V2 / 8;
     const int c0 = n->a.c[0], c1 = n->a.c[1], c2 = n->a.c[2];
-    // largest data-path gradient: full resolution with c0 or c1 channels (the
-    // up-sampled input of the last decoder level), half resolution with c2
-    const int64_t gmax = std::max(V1 * std::max(c0, c1), V2 * std::max(c1, c2));
-    struct { void **p; size_t b; } L[] = {
-        {(void **)&n->x0, (size_t)V1 * 4 * 2}, {(void **)&n->a1, (size_t)V1 * c0 * 2}, {(void **)&n->s1, (size_t)V1 * c0 * 2},
-        {(void **)&n->p1, (size_t)V2 * c0 * 2}, {(void **)&n->a2, (size_t)V2 * c1 * 2}, {(void **)&n->s2, (size_t)V2 * c1 * 2},
-        {(void **)&n->p2, (size_t)V3 * c1 * 2}, {(void **)&n->a3, (size_t)V3 * c2 * 2}, {(void **)&n->b3, (size_t)V3 * c2 * 2},
-        {(void **)&n->d2a, (size_t)V2 * c1 * 2}, {(void **)&n->d2, (size_t)V2 * c1 * 2}, {(void **)&n->d1a, (size_t)V1 * c0 * 2},
-        {(void **)&n->d1, (size_t)V1 * c0 * 2}, {(void **)&n->Gb, (size_t)gmax * 2}, {(void **)&n->lnk_std, (size_t)V1 * 2},
-        {(void **)&n->y, (size_t)V1 * 3 * 4}, {(void **)&n->gy, (size_t)V1 * 3 * 4},
-        {(void **)&n->g1, (size_t)gmax * 4}, {(void **)&n->g2, (size_t)gmax * 4},
-        {(void **)&n->gs1, (size_t)V1 * c0 * 4}, {(void **)&n->gs2, (size_t)V2 * c1 * 4},
+    // masked gradients: each level's own channels
+    const int64_t gmask = std::max(V1 * c0, std::max(V2 * c1, V3 * c2));
+    // unmasked ones: the up-sampled inputs of the decoder levels (full resolution with c1
+    // channels, half with c2) and the pooled ones (half with c0, quarter with c1)
+    const int64_t gfull = std::max(std::max(V1 * c1, V2 * c2), std::max(V2 * c0, V3 * c1));
+    struct { void **p; size_t b; bool back; } L[] = {
+        {(void **)&n->x0, (size_t)V1 * 4 * 2, false}, {(void **)&n->a1, (size_t)V1 * c0 * 2, false},
+        {(void **)&n->s1, (size_t)V1 * c0 * 2, false}, {(void **)&n->p1, (size_t)V2 * c0 * 2, false},
+        {(void **)&n->a2, (size_t)V2 * c1 * 2, false}, {(void **)&n->s2, (size_t)V2 * c1 * 2, false},
+        {(void **)&n->p2, (size_t)V3 * c1 * 2, false}, {(void **)&n->a3, (size_t)V3 * c2 * 2, false},
+        {(void **)&n->b3, (size_t)V3 * c2 * 2, false}, {(void **)&n->d2a, (size_t)V2 * c1 * 2, false},
+        {(void **)&n->d2, (size_t)V2 * c1 * 2, false}, {(void **)&n->d1a, (size_t)V1 * c0 * 2, false},
+        {(void **)&n->d1, (size_t)V1 * c0 * 2, false}, {(void **)&n->lnk_std, (size_t)V1 * 2, false},
+        {(void **)&n->y, (size_t)V1 * 3 * 4, false}, {(void **)&n->d_sc, (size_t)nb * 5 * sizeof(double), false},
+        {(void **)&n->Ga, (size_t)gmask * 2, true}, {(void **)&n->Gb, (size_t)gmask * 2, true},
+        {(void **)&n->gy, (size_t)V1 * 3 * 4, true}, {(void **)&n->g1, (size_t)gfull * 4, true},
+        {(void **)&n->gs1, (size_t)V1 * c0 * 4, true}, {(void **)&n->gs2, (size_t)V2 * c1 * 4, true},
     };
     for (auto &e : L) {
+        if (e.back && !back) continue;
         rsv_status s = dev_alloc(c, e.p, e.b);
         if (s != RSV_OK) { n->free_ws(); return s; }
     }
-    n->wx = nx; n->wy = ny; n->wz = nz;
+    n->wx = nx; n->wy = ny; n->wz = nz; n->wb = nb;
+    n->wback = back;
     return RSV_OK;
 }
 
@@ -1037,38 +1177,42 @@ static rsv_status part_reserve(rsv_net *n, int64_t nfloat)
     return s;
 }
 
-// y = conv(X) + b [+ skip], relu, BF16 out
-static rsv_status conv_fwd(rsv_net *n, int l, int nx, int ny, int nz, int up, const uint16_t *X, const uint16_t *skip,
-                           int relu, uint16_t *out)
+// relu(conv(X) + b [+ skip]), BF16; nz layers in all, nzs per sample
+static rsv_status conv_fwd(rsv_net *n, int l, int nx, int ny, int nz, int nzs, int up, const uint16_t *X,
+                           const uint16_t *skip, uint16_t *out)
 {
     rsv_ctx *c = n->c;
-    ConvGeo g{nx, ny, nz, up, n->a.cin[l], n->a.cout[l], (int64_t)nx * ny * nz};
-    if (g.cout % 16) return set_err(c, RSV_ERR_ARG, "channel count must be 16, 32 or 64");
-    const hipError_t e = launch_conv<true>(c->stream, g, X, n->wf[l], n->a.kb(l), n->P + n->a.boff[l], skip, relu, out);
+    ConvGeo g{nx, ny, nz, nzs, up, n->a.cin[l], n->a.cout[l], (int64_t)nx * ny * nz};
+    const Epilogue ep{n->P + n->a.boff[l], skip, 1, nullptr, nullptr, out};
+    const hipError_t e = launch_conv<true>(c->stream, g, X, n->wf[l], n->a.kb(l), ep);
     if (e != hipSuccess) return set_err(c, RSV_ERR_HIP, std::string("conv launch: ") + hipGetErrorString(e));
     return RSV_OK;
 }
 
-// dX (FP32, resolution of G) = transposed conv of the BF16 gradient G
-static rsv_status conv_bwd_data(rsv_net *n, int l, int nx, int ny, int nz, const uint16_t *G, float *dX)
+// dX (resolution of G) = transposed conv of the BF16 gradient G: FP32 into dX32,
+// or masked by the activations `mask` and BF16 into dX16 (FP32 copy of that in `copy`)
+static rsv_status conv_bwd_data(rsv_net *n, int l, int nx, int ny, int nz, int nzs, const uint16_t *G, float *dX32,
+                                const uint16_t *mask, uint16_t *dX16, float *copy)
 {
     rsv_ctx *c = n->c;
-    ConvGeo g{nx, ny, nz, 0, n->a.cout[l], n->a.cin[l], (int64_t)nx * ny * nz};
+    ConvGeo g{nx, ny, nz, nzs, 0, n->a.cout[l], n->a.cin[l], (int64_t)nx * ny * nz};
     if (g.cout % 16) return set_err(c, RSV_ERR_ARG, "channel count must be 16, 32 or 64");
-    const hipError_t e = launch_conv<false>(c->stream, g, G, n->wt[l], n->a.kbt(l), nullptr, nullptr, 0, dX);
+    const Epilogue ep{nullptr, nullptr, 0, mask, copy, mask ? (void *)dX16 : (void *)dX32};
+    const hipError_t e = mask ? launch_conv<true>(c->stream, g, G, n->wt[l], n->a.kbt(l), ep)
+                              : launch_conv<false>(c->stream, g, G, n->wt[l], n->a.kbt(l), ep);
     if (e != hipSuccess) return set_err(c, RSV_ERR_HIP, std::string("conv launch: ") + hipGetErrorString(e));
     return RSV_OK;
 }
 
 // grad(W_l) += scale * X^T G, grad(b_l) += scale * colsum(G)
-static rsv_status conv_bwd_weight(rsv_net *n, int l, int nx, int ny, int nz, int up, const uint16_t *X,
+static rsv_status conv_bwd_weight(rsv_net *n, int l, int nx, int ny, int nz, int nzs, int up, const uint16_t *X,
                                   const uint16_t *G, float scale, float *grad_w, float *grad_b)
 {
     rsv_ctx *c = n->c;
-    ConvGeo g{nx, ny, nz, up, n->a.cin[l], n->a.cout[l], (int64_t)nx * ny * nz};
+    ConvGeo g{nx, ny, nz, nzs, up, n->a.cin[l], n->a.cout[l], (int64_t)nx * ny * nz};
     if (g.cout % 16 || g.cin > 64) return set_err(c, RSV_ERR_ARG, "channel count must be 16, 32 or 64");
     const int npairs = ((g.cin + 15) / 16) * (g.cout / 16);
-    const int64_t nbricks = (int64_t)((nx + CT_X - 1) / CT_X) * ((ny + CT_Y - 1) / CT_Y) * ((nz + CT_Z - 1) / CT_Z);
+    const int64_t nbricks = brick_count(g, CT_Z);
     // about 256 workgroups (two per CU fit the 63 KB of LDS) of at least two bricks
     const int64_t want = std::max<int64_t>(1, std::min<int64_t>((nbricks + 1) / 2, std::max(1, 256 / npairs)));
     const int per = (int)((nbricks + want - 1) / want);
@@ -1084,30 +1228,31 @@ static rsv_status conv_bwd_weight(rsv_net *n, int l, int nx, int ny, int nz, int
     return RSV_OK;
 }
 
-// forward pass; x0 must be filled; result y (FP32 [V][3])
-static rsv_status net_forward(rsv_net *n, int nx, int ny, int nz)
+// forward pass of nb samples; x0 must be filled; result y (FP32 [nb][V][3])
+static rsv_status net_forward(rsv_net *n, int nx, int ny, int nzs, int nb)
 {
     if (!n->packed) {
         rsv_status s = net_pack(n);
         if (s != RSV_OK) return s;
     }
-    const int mx = nx / 2, my = ny / 2, mz = nz / 2, lx = nx / 4, ly = ny / 4, lz = nz / 4;
+    const int nz = nzs * nb;
+    const int mx = nx / 2, my = ny / 2, mz = nz / 2, ms = nzs / 2, lx = nx / 4, ly = ny / 4, lz = nz / 4, ls = nzs / 4;
     const int c0 = n->a.c[0], c1 = n->a.c[1];
     rsv_ctx *c = n->c;
     ProfScope ps(c, RSV_K_NET);
     rsv_status s;
-    if ((s = conv_fwd(n, 0, nx, ny, nz, 0, n->x0, nullptr, 1, n->a1)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 1, nx, ny, nz, 0, n->a1, nullptr, 1, n->s1)) != RSV_OK) return s;
-    hipLaunchKernelGGL(k_pool, dim3(nblk((int64_t)mx * my * mz * c0)), dim3(256), 0, c->stream, nx, ny, nz, c0, n->s1, n->p1);
-    if ((s = conv_fwd(n, 2, mx, my, mz, 0, n->p1, nullptr, 1, n->a2)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 3, mx, my, mz, 0, n->a2, nullptr, 1, n->s2)) != RSV_OK) return s;
-    hipLaunchKernelGGL(k_pool, dim3(nblk((int64_t)lx * ly * lz * c1)), dim3(256), 0, c->stream, mx, my, mz, c1, n->s2, n->p2);
-    if ((s = conv_fwd(n, 4, lx, ly, lz, 0, n->p2, nullptr, 1, n->a3)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 5, lx, ly, lz, 0, n->a3, nullptr, 1, n->b3)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 6, mx, my, mz, 1, n->b3, n->s2, 1, n->d2a)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 7, mx, my, mz, 0, n->d2a, nullptr, 1, n->d2)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 8, nx, ny, nz, 1, n->d2, n->s1, 1, n->d1a)) != RSV_OK) return s;
-    if ((s = conv_fwd(n, 9, nx, ny, nz, 0, n->d1a, nullptr, 1, n->d1)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 0, nx, ny, nz, nzs, 0, n->x0, nullptr, n->a1)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 1, nx, ny, nz, nzs, 0, n->a1, nullptr, n->s1)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_pool, dim3(nblk((int64_t)mx * my * mz * c0 / 8)), dim3(256), 0, c->stream, nx, ny, nz, c0, n->s1, n->p1);
+    if ((s = conv_fwd(n, 2, mx, my, mz, ms, 0, n->p1, nullptr, n->a2)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 3, mx, my, mz, ms, 0, n->a2, nullptr, n->s2)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_pool, dim3(nblk((int64_t)lx * ly * lz * c1 / 8)), dim3(256), 0, c->stream, mx, my, mz, c1, n->s2, n->p2);
+    if ((s = conv_fwd(n, 4, lx, ly, lz, ls, 0, n->p2, nullptr, n->a3)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 5, lx, ly, lz, ls, 0, n->a3, nullptr, n->b3)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 6, mx, my, mz, ms, 1, n->b3, n->s2, n->d2a)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 7, mx, my, mz, ms, 0, n->d2a, nullptr, n->d2)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 8, nx, ny, nz, nzs, 1, n->d2, n->s1, n->d1a)) != RSV_OK) return s;
+    if ((s = conv_fwd(n, 9, nx, ny, nz, nzs, 0, n->d1a, nullptr, n->d1)) != RSV_OK) return s;
     const int64_t V1 = (int64_t)nx * ny * nz;
     hipLaunchKernelGGL(k_final, dim3(nblk(V1)), dim3(256), 0, c->stream, V1, c0, n->d1, n->P + n->a.woff[10],
                        n->P + n->a.boff[10], n->y);
@@ -1115,68 +1260,58 @@ static rsv_status net_forward(rsv_net *n, int nx, int ny, int nz)
     return RSV_OK;
 }
 
-// backward pass for gy (in n->g2 as [V1][3] FP32 on entry is not assumed: gy pointer given)
-static rsv_status net_backward(rsv_net *n, int nx, int ny, int nz, const float *gy, float scale)
+// backward pass of nb samples for n->gy, adding to the gradient n->G
+static rsv_status net_backward(rsv_net *n, int nx, int ny, int nzs, int nb)
 {
     rsv_ctx *c = n->c;
     ProfScope ps(c, RSV_K_NET);
-    const int mx = nx / 2, my = ny / 2, mz = nz / 2, lx = nx / 4, ly = ny / 4, lz = nz / 4;
+    const int nz = nzs * nb;
+    const int mx = nx / 2, my = ny / 2, mz = nz / 2, ms = nzs / 2, lx = nx / 4, ly = ny / 4, lz = nz / 4, ls = nzs / 4;
     const int c0 = n->a.c[0], c1 = n->a.c[1], c2 = n->a.c[2];
     const int64_t V1 = (int64_t)nx * ny * nz, V2 = V1 / 8, V3 = V2 / 8;
     float *gw = n->G;
-#define GW(l) (gw + n->a.woff[l])
-#define GB(l) (gw + n->a.boff[l])
     rsv_status s;
-    // final layer: gd1 -> g1, weight and bias gradients by voxel chunks
     {
         const int nwf = c0 * 3 + 3;
-        const int64_t chunk = 4096;
-        const int nch = (int)((V1 + chunk - 1) / chunk);
-        if ((s = part_reserve(n, (int64_t)nch * nwf)) != RSV_OK) return s;
-        hipLaunchKernelGGL(k_final_bwd_data, dim3(nblk(V1 * c0)), dim3(256), 0, c->stream, V1, c0,
-                           (const float *)(n->P + n->a.woff[10]), gy, n->g1);
-        hipLaunchKernelGGL(k_final_dw, dim3(nwf, nch), dim3(256), 0, c->stream, V1, c0, chunk, (const uint16_t *)n->d1,
-                           gy, n->part);
-        hipLaunchKernelGGL(k_sum_chunks, dim3(1), dim3(256), 0, c->stream, (const float *)n->part, nch, (int64_t)nwf, scale,
-                           GW(10));
+        const int nbl = (int)std::max<int64_t>(1, std::min<int64_t>(V1 * c0 / 4096, 1024));
+        if ((s = part_reserve(n, (int64_t)nbl * nwf)) != RSV_OK) return s;
+        hipLaunchKernelGGL(k_final_bwd, dim3(nbl), dim3(256), 0, c->stream, V1, c0, (const float *)(n->P + n->a.woff[10]),
+                           (const uint16_t *)n->d1, (const float *)n->gy, n->Ga, n->part);
+        hipLaunchKernelGGL(k_sum_blocks, dim3(nwf), dim3(256), 0, c->stream, (const float *)n->part, nbl, nwf, 1.0f,
+                           gw + n->a.woff[10]);
         RSV_LAUNCH(c);
     }
-    // data-path gradients are unscaled; weight gradients are multiplied by `scale`
-    auto layer = [&](int l, int lnx, int lny, int lnz, int up, const uint16_t *X, const uint16_t *Y, float *gY,
-                     float *gX, float *gskip) -> rsv_status {
-        const int64_t V = (int64_t)lnx * lny * lnz;
-        const int64_t ne = V * n->a.cout[l];
-        hipLaunchKernelGGL(k_mask, dim3(nblk(ne)), dim3(256), 0, c->stream, ne, (const float *)gY, Y, n->Gb, gskip);
-        RSV_LAUNCH(c);
-        rsv_status st = conv_bwd_weight(n, l, lnx, lny, lnz, up, X, n->Gb, scale, GW(l), GB(l));
-        if (st != RSV_OK) return st;
-        if (gX) st = conv_bwd_data(n, l, lnx, lny, lnz, n->Gb, gX);
+    // layer l at lx x ly x lz (ls layers per sample) with input X and masked output gradient G:
+    // weight gradients, then the data gradient, masked by `act` into `next` or FP32 into n->g1
+    auto layer = [&](int l, int x, int y, int z, int zs, int up, const uint16_t *X, const uint16_t *G,
+                     const uint16_t *act, uint16_t *next, float *gskip) -> rsv_status {
+        rsv_status st = conv_bwd_weight(n, l, x, y, z, zs, up, X, G, 1.0f, gw + n->a.woff[l], gw + n->a.boff[l]);
+        if (st == RSV_OK && l > 0) st = conv_bwd_data(n, l, x, y, z, zs, G, n->g1, act, next, gskip);
         return st;
     };
-    // dec1b: in d1a, out d1
-    if ((s = layer(9, nx, ny, nz, 0, n->d1a, n->d1, n->g1, n->g2, nullptr)) != RSV_OK) return s;
-    // dec1a: out d1a = relu(conv8(up(d2)) + s1); skip gradient -> gs1
-    if ((s = layer(8, nx, ny, nz, 1, n->d2, n->d1a, n->g2, n->g1, n->gs1)) != RSV_OK) return s;
-    hipLaunchKernelGGL(k_up_bwd, dim3(nblk(V2 * c1)), dim3(256), 0, c->stream, nx, ny, nz, c1, (const float *)n->g1, n->g2);
-    // dec2b
-    if ((s = layer(7, mx, my, mz, 0, n->d2a, n->d2, n->g2, n->g1, nullptr)) != RSV_OK) return s;
-    // dec2a: skip gradient -> gs2
-    if ((s = layer(6, mx, my, mz, 1, n->b3, n->d2a, n->g1, n->g2, n->gs2)) != RSV_OK) return s;
-    hipLaunchKernelGGL(k_up_bwd, dim3(nblk(V3 * c2)), dim3(256), 0, c->stream, mx, my, mz, c2, (const float *)n->g2, n->g1);
+    // dec1b, then dec1a: out d1a = relu(conv8(up(d2)) + s1), skip gradient -> gs1
+    if ((s = layer(9, nx, ny, nz, nzs, 0, n->d1a, n->Ga, n->d1a, n->Gb, n->gs1)) != RSV_OK) return s;
+    if ((s = layer(8, nx, ny, nz, nzs, 1, n->d2, n->Gb, nullptr, nullptr, nullptr)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_up_bwd, dim3(nblk(V2 * c1 / 8)), dim3(256), 0, c->stream, nx, ny, nz, c1, (const float *)n->g1,
+                       (const uint16_t *)n->d2, n->Ga);
+    // dec2b, dec2a: skip gradient -> gs2
+    if ((s = layer(7, mx, my, mz, ms, 0, n->d2a, n->Ga, n->d2a, n->Gb, n->gs2)) != RSV_OK) return s;
+    if ((s = layer(6, mx, my, mz, ms, 1, n->b3, n->Gb, nullptr, nullptr, nullptr)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_up_bwd, dim3(nblk(V3 * c2 / 8)), dim3(256), 0, c->stream, mx, my, mz, c2, (const float *)n->g1,
+                       (const uint16_t *)n->b3, n->Ga);
     // enc3b, enc3a
-    if ((s = layer(5, lx, ly, lz, 0, n->a3, n->b3, n->g1, n->g2, nullptr)) != RSV_OK) return s;
-    if ((s = layer(4, lx, ly, lz, 0, n->p2, n->a3, n->g2, n->g1, nullptr)) != RSV_OK) return s;
-    // pool 2: gs2 += pool_bwd(gp2)
-    hipLaunchKernelGGL(k_pool_bwd, dim3(nblk(V2 * c1)), dim3(256), 0, c->stream, mx, my, mz, c1, (const float *)n->g1, n->gs2);
+    if ((s = layer(5, lx, ly, lz, ls, 0, n->a3, n->Ga, n->a3, n->Gb, nullptr)) != RSV_OK) return s;
+    if ((s = layer(4, lx, ly, lz, ls, 0, n->p2, n->Gb, nullptr, nullptr, nullptr)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_pool_bwd, dim3(nblk(V2 * c1 / 8)), dim3(256), 0, c->stream, mx, my, mz, c1, (const float *)n->g1,
+                       (const float *)n->gs2, (const uint16_t *)n->s2, n->Ga);
     // enc2b, enc2a
-    if ((s = layer(3, mx, my, mz, 0, n->a2, n->s2, n->gs2, n->g1, nullptr)) != RSV_OK) return s;
-    if ((s = layer(2, mx, my, mz, 0, n->p1, n->a2, n->g1, n->g2, nullptr)) != RSV_OK) return s;
-    hipLaunchKernelGGL(k_pool_bwd, dim3(nblk(V1 * c0)), dim3(256), 0, c->stream, nx, ny, nz, c0, (const float *)n->g2, n->gs1);
+    if ((s = layer(3, mx, my, mz, ms, 0, n->a2, n->Ga, n->a2, n->Gb, nullptr)) != RSV_OK) return s;
+    if ((s = layer(2, mx, my, mz, ms, 0, n->p1, n->Gb, nullptr, nullptr, nullptr)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_pool_bwd, dim3(nblk(V1 * c0 / 8)), dim3(256), 0, c->stream, nx, ny, nz, c0, (const float *)n->g1,
+                       (const float *)n->gs1, (const uint16_t *)n->s1, n->Ga);
     // enc1b, enc1a
-    if ((s = layer(1, nx, ny, nz, 0, n->a1, n->s1, n->gs1, n->g1, nullptr)) != RSV_OK) return s;
-    if ((s = layer(0, nx, ny, nz, 0, n->x0, n->a1, n->g1, nullptr, nullptr)) != RSV_OK) return s;
-#undef GW
-#undef GB
+    if ((s = layer(1, nx, ny, nz, nzs, 0, n->a1, n->Ga, n->a1, n->Gb, nullptr)) != RSV_OK) return s;
+    if ((s = layer(0, nx, ny, nz, nzs, 0, n->x0, n->Gb, nullptr, nullptr, nullptr)) != RSV_OK) return s;
     RSV_LAUNCH(c);
     return RSV_OK;
 }
@@ -1188,35 +1323,43 @@ static rsv_status dims_check(rsv_ctx *c, const rsv_grid *g)
     return RSV_OK;
 }
 
-// standardised ln k channel (mean/std over the grid, FP64 on the host) into out[V]
-static rsv_status set_lnk(rsv_net *n, const rsv_grid *g, const float *lnk_dev, uint16_t *out)
+// blocks of a batched reduction: as many as launch_dot takes for one sample
+static int red_blocks(int64_t len) { return vec_blocks(len); }
+
+// standardised ln k channel (mean and standard deviation over each sample's
+// grid, FP64) of nb samples into out[nb][V]; sums: 2 nb doubles of scratch
+static rsv_status set_lnk(rsv_net *n, const rsv_grid *g, int nb, const float *lnk_dev, double *sum, double *dev2,
+                          uint16_t *out)
 {
     rsv_ctx *c = n->c;
     const int64_t V = g->ncell;
-    std::vector<float> h(V);
-    RSV_HIP(c, hipMemcpyAsync(h.data(), lnk_dev, V * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-    RSV_HIP(c, hipStreamSynchronize(c->stream));
-    double m = 0.0, m2 = 0.0;
-    for (float v : h) m += v;
-    m /= (double)V;
-    for (float v : h) m2 += ((double)v - m) * ((double)v - m);
-    const double sd = std::sqrt(m2 / (double)V);
-    hipLaunchKernelGGL(k_lnk_std, dim3(nblk(V)), dim3(256), 0, c->stream, g->geo, lnk_dev, m, sd > 0 ? 1.0 / sd : 0.0,
-                       out);
+    const int nbl = red_blocks(V);
+    rsv_status s = partials_reserve(c, (int64_t)nbl * nb);
+    if (s != RSV_OK) return s;
+    hipLaunchKernelGGL(k_lnk_sums, dim3(nbl, nb), dim3(256), 0, c->stream, V, lnk_dev, (const double *)nullptr, c->d_partials);
+    if ((s = launch_reduce_to(c, nbl, nb, sum)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_lnk_sums, dim3(nbl, nb), dim3(256), 0, c->stream, V, lnk_dev, (const double *)sum, c->d_partials);
+    if ((s = launch_reduce_to(c, nbl, nb, dev2)) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_lnk_std, dim3(nblk(V * nb)), dim3(256), 0, c->stream, g->geo, nb, lnk_dev, (const double *)sum,
+                       (const double *)dev2, out);
     RSV_LAUNCH(c);
     return RSV_OK;
 }
 
-// Fills x0 from r (tile-lane rtl or natural rnat) and leaves sum r^2 in n->d_sc[0]
-static rsv_status prep(rsv_net *n, const rsv_grid *g, const double *rtl, const double *rnat, const uint16_t *lnk_std)
+// Fills x0 of nb samples from r (tile-lane rtl, one sample, or natural rnat)
+// and leaves their sums of r^2 in n->sum_r2()
+static rsv_status prep(rsv_net *n, const rsv_grid *g, int nb, const double *rtl, const double *rnat,
+                       const uint16_t *lnk_std)
 {
     rsv_ctx *c = n->c;
     const int64_t len = rtl ? g->nv : 3 * g->ncell;
-    rsv_status s = launch_dot(c, len, rtl ? rtl : rnat, rtl ? rtl : rnat, SC_MISC);
+    const int nbl = red_blocks(len);
+    rsv_status s = partials_reserve(c, (int64_t)nbl * nb);
     if (s != RSV_OK) return s;
-    RSV_HIP(c, hipMemcpyAsync(n->d_sc, c->d_scal + SC_MISC, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-    hipLaunchKernelGGL(k_prep, dim3(nblk(g->ncell)), dim3(256), 0, c->stream, g->geo, rtl, rnat, (const double *)n->d_sc,
-                       lnk_std, n->x0);
+    hipLaunchKernelGGL(k_sumsq, dim3(nbl, nb), dim3(256), 0, c->stream, len, rtl ? rtl : rnat, c->d_partials);
+    if ((s = launch_reduce_to(c, nbl, nb, n->sum_r2())) != RSV_OK) return s;
+    hipLaunchKernelGGL(k_prep, dim3(nblk(g->ncell * nb)), dim3(256), 0, c->stream, g->geo, nb, rtl, rnat,
+                       (const double *)n->sum_r2(), lnk_std, n->x0);
     RSV_LAUNCH(c);
     return RSV_OK;
 }
@@ -1238,18 +1381,18 @@ struct Learned : PcImpl {
     {
         rsv_grid *g = M->g;
         rsv_ctx *c = net->c;
-        rsv_status s = net_ws(net, g->geo.nx, g->geo.ny, g->geo.nz);
+        rsv_status s = net_ws(net, g->geo.nx, g->geo.ny, g->geo.nz, 1, false);
         const double *in = r;
         if (s == RSV_OK && base) {
             s = base->apply(r, t1);
             if (s == RSV_OK) s = launch_spmv(c, g->geo, M->d_A, SPMV_RESID, t1, r1, r, 0.0, 0.0, SC_MISC);
             in = r1;
         }
-        if (s == RSV_OK) s = prep(net, g, in, nullptr, lnk_std);
-        if (s == RSV_OK) s = net_forward(net, g->geo.nx, g->geo.ny, g->geo.nz);
+        if (s == RSV_OK) s = prep(net, g, 1, in, nullptr, lnk_std);
+        if (s == RSV_OK) s = net_forward(net, g->geo.nx, g->geo.ny, g->geo.nz, 1);
         if (s != RSV_OK) return s;
         hipLaunchKernelGGL(k_post, dim3(nblk(g->ncell)), dim3(256), 0, c->stream, g->geo, (const float *)net->y,
-                           (const double *)net->d_sc, z, (double *)nullptr, (const double *)(base ? t1 : nullptr));
+                           (const double *)net->sum_r2(), z, (double *)nullptr, (const double *)(base ? t1 : nullptr));
         RSV_LAUNCH(c);
         return RSV_OK;
     }
@@ -1268,8 +1411,8 @@ rsv_status learned_create(rsv_matrix *A, const rsv_pc_params *p, PcImpl **out, P
     L->M = A;
     L->net = n;
     s = dev_alloc(c, (void **)&L->lnk_std, (size_t)A->g->ncell * 2);
-    if (s == RSV_OK) s = set_lnk(n, A->g, p->lnk, L->lnk_std);
-    if (s == RSV_OK) s = net_ws(n, A->g->geo.nx, A->g->geo.ny, A->g->geo.nz);
+    if (s == RSV_OK) s = net_ws(n, A->g->geo.nx, A->g->geo.ny, A->g->geo.nz, 1, false);
+    if (s == RSV_OK) s = set_lnk(n, A->g, 1, p->lnk, n->sum_lnk(), n->dev_lnk(), L->lnk_std);
     if (s == RSV_OK && p->learned_mode == 1) {
         if (!base) s = set_err(c, RSV_ERR_ARG, "learned mode 1 needs the BILU0 base");
         L->base = base;
@@ -1305,7 +1448,6 @@ rsv_status rsv_net_create(rsv_ctx *c, const rsv_net_arch *arch, uint64_t seed, r
     if (s == RSV_OK) s = dev_alloc(c, (void **)&n->G, pb);
     if (s == RSV_OK) s = dev_alloc(c, (void **)&n->M, pb);
     if (s == RSV_OK) s = dev_alloc(c, (void **)&n->Vv, pb);
-    if (s == RSV_OK) s = dev_alloc(c, (void **)&n->d_sc, 8 * sizeof(double));
     for (int l = 0; l < 10 && s == RSV_OK; ++l) {
         s = dev_alloc(c, (void **)&n->wf[l], (size_t)n->a.kb(l) * (n->a.cout[l] / 16) * 64 * conv_frag_bytes(n->a.cin[l]));
         if (s == RSV_OK)
@@ -1411,48 +1553,60 @@ rsv_status rsv_net_forward(rsv_net *n, rsv_grid *g, const double *r, const float
     if (!n || !g || !r || !lnk || !z) return set_err(n ? n->c : nullptr, RSV_ERR_ARG, "NULL argument");
     rsv_ctx *c = n->c;
     rsv_status s = dims_check(c, g);
-    if (s == RSV_OK) s = net_ws(n, g->geo.nx, g->geo.ny, g->geo.nz);
-    if (s == RSV_OK) s = set_lnk(n, g, lnk, n->lnk_std);
-    if (s == RSV_OK) s = prep(n, g, nullptr, r, n->lnk_std);
-    if (s == RSV_OK) s = net_forward(n, g->geo.nx, g->geo.ny, g->geo.nz);
+    if (s == RSV_OK) s = net_ws(n, g->geo.nx, g->geo.ny, g->geo.nz, 1, false);
+    if (s == RSV_OK) s = set_lnk(n, g, 1, lnk, n->sum_lnk(), n->dev_lnk(), n->lnk_std);
+    if (s == RSV_OK) s = prep(n, g, 1, nullptr, r, n->lnk_std);
+    if (s == RSV_OK) s = net_forward(n, g->geo.nx, g->geo.ny, g->geo.nz, 1);
     if (s != RSV_OK) return s;
     hipLaunchKernelGGL(k_post, dim3(nblk(g->ncell)), dim3(256), 0, c->stream, g->geo, (const float *)n->y,
-                       (const double *)n->d_sc, (double *)nullptr, z);
+                       (const double *)n->sum_r2(), (double *)nullptr, z);
     RSV_LAUNCH(c);
     RSV_HIP(c, hipStreamSynchronize(c->stream));
     return RSV_OK;
 }
 
+// Loss and gradient of a batch.  Samples go through the network together, as
+// many as keep a pass within 2^21 voxels (at 64x64x32 all of a batch of 8 or
+// 16): one sample's quarter-resolution layers are 16 workgroups, and each of
+// the backward pass's launches costs about what such a layer computes.  Larger
+// passes gain nothing and cost about 600 bytes of workspace per voxel.
 static rsv_status loss_grad_batch(rsv_net *n, rsv_grid *g, int32_t nb, const double *r, const double *e,
                                   const float *lnk, float *loss_out)
 {
     rsv_ctx *c = n->c;
     if (nb < 1) return set_err(c, RSV_ERR_ARG, "batch must be >= 1");
     rsv_status s = dims_check(c, g);
-    if (s == RSV_OK) s = net_ws(n, g->geo.nx, g->geo.ny, g->geo.nz);
+    if (s != RSV_OK) return s;
+    const int64_t V = g->ncell, N = 3 * V;
+    const int nx = g->geo.nx, ny = g->geo.ny, nz = g->geo.nz;
+    int per = (int)std::max<int64_t>(1, std::min<int64_t>(nb, ((int64_t)1 << 21) / V));
+    s = net_ws(n, nx, ny, nz, per, true);
+    if (s == RSV_ERR_OOM && per > 1) s = net_ws(n, nx, ny, nz, per = 1, true);   // one sample's may still fit
     if (s != RSV_OK) return s;
     if (!n->packed && (s = net_pack(n)) != RSV_OK) return s;
-    const int64_t V = g->ncell, N = 3 * V;
     RSV_HIP(c, hipMemsetAsync(n->G, 0, (size_t)n->a.np * sizeof(float), c->stream));
     double total = 0.0;
+    std::vector<double> sums(2 * (size_t)per);
     const int nbk = nblk(V) < 1024 ? nblk(V) : 1024;
-    if ((s = partials_reserve(c, 2 * nbk)) != RSV_OK) return s;
-    for (int b = 0; b < nb; ++b) {
-        if ((s = set_lnk(n, g, lnk + (int64_t)b * V, n->lnk_std)) != RSV_OK) return s;
-        if ((s = prep(n, g, nullptr, r + (int64_t)b * N, n->lnk_std)) != RSV_OK) return s;
-        if ((s = net_forward(n, g->geo.nx, g->geo.ny, g->geo.nz)) != RSV_OK) return s;
-        hipLaunchKernelGGL(k_loss, dim3(nbk), dim3(256), 0, c->stream, g->geo, (const float *)n->y, e + (int64_t)b * N,
-                           (const double *)n->d_sc, c->d_partials);
+    for (int b0 = 0; b0 < nb; b0 += per) {
+        const int q = std::min<int>(per, nb - b0);
+        const double *rb = r + (int64_t)b0 * N, *eb = e + (int64_t)b0 * N;
+        if ((s = set_lnk(n, g, q, lnk + (int64_t)b0 * V, n->sum_lnk(), n->dev_lnk(), n->lnk_std)) != RSV_OK) return s;
+        if ((s = prep(n, g, q, nullptr, rb, n->lnk_std)) != RSV_OK) return s;
+        if ((s = net_forward(n, nx, ny, nz, q)) != RSV_OK) return s;
+        if ((s = partials_reserve(c, 2 * (int64_t)nbk * q)) != RSV_OK) return s;
+        hipLaunchKernelGGL(k_loss, dim3(nbk, q), dim3(256), 0, c->stream, g->geo, (const float *)n->y, eb,
+                           (const double *)n->sum_r2(), c->d_partials);
         RSV_LAUNCH(c);
-        if ((s = launch_reduce(c, nbk, 2, SC_MISC)) != RSV_OK) return s;
-        if ((s = scal_to_host(c, SC_MISC, 2)) != RSV_OK) return s;
-        total += c->h_scal[SC_MISC] / c->h_scal[SC_MISC + 1];
-        RSV_HIP(c, hipMemcpyAsync(n->d_sc + 1, c->d_scal + SC_MISC + 1, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+        if ((s = launch_reduce_to(c, nbk, 2 * q, n->loss())) != RSV_OK) return s;
         // gy = (2 / nb) (y - e/s) / ||e/s||^2
-        hipLaunchKernelGGL(k_gy, dim3(nblk(V)), dim3(256), 0, c->stream, g->geo, (const float *)n->y, e + (int64_t)b * N,
-                           (const double *)n->d_sc, (const double *)(n->d_sc + 1), 1.0f / (float)nb, n->gy);
+        hipLaunchKernelGGL(k_gy, dim3(nblk(V * q)), dim3(256), 0, c->stream, g->geo, q, (const float *)n->y, eb,
+                           (const double *)n->sum_r2(), (const double *)n->loss(), 1.0f / (float)nb, n->gy);
         RSV_LAUNCH(c);
-        if ((s = net_backward(n, g->geo.nx, g->geo.ny, g->geo.nz, n->gy, 1.0f)) != RSV_OK) return s;
+        if ((s = net_backward(n, nx, ny, nz, q)) != RSV_OK) return s;
+        RSV_HIP(c, hipMemcpyAsync(sums.data(), n->loss(), 2 * (size_t)q * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        RSV_HIP(c, hipStreamSynchronize(c->stream));
+        for (int b = 0; b < q; ++b) total += sums[2 * b] / sums[2 * b + 1];
     }
     if (loss_out) *loss_out = (float)(total / nb);
     return RSV_OK;
@@ -1502,8 +1656,8 @@ rsv_status rsv_conv3d(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32_t ci
     if (s != RSV_OK) return s;
     hipLaunchKernelGGL(k_pack, dim3(nblk((int64_t)KB * NB * 64)), dim3(256), 0, c->stream, w, cin, cout, 0, KB, NB,
                        conv_kw(cin), wf);
-    ConvGeo g{nx, ny, nz, 0, cin, cout, (int64_t)nx * ny * nz};
-    hipError_t e = launch_conv<false>(c->stream, g, x, wf, KB, b, nullptr, 0, y);
+    ConvGeo g{nx, ny, nz, nz, 0, cin, cout, (int64_t)nx * ny * nz};
+    hipError_t e = launch_conv<false>(c->stream, g, x, wf, KB, Epilogue{b, nullptr, 0, nullptr, nullptr, y});
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     dev_free(wf);
     if (e != hipSuccess) return set_err(c, RSV_ERR_HIP, std::string("conv3d: ") + hipGetErrorString(e));
@@ -1525,13 +1679,12 @@ rsv_status rsv_conv3d_bwd(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32_
     tmp.a.cout[1] = cout;
     const int KBt = conv_kblocks(cout), NBt = (cin + 15) / 16;
     rsv_status s = RSV_OK;
-    ConvGeo g{nx, ny, nz, 0, cin, cout, (int64_t)nx * ny * nz};
     if (dx) {
         s = dev_alloc(c, (void **)&tmp.wt[1], (size_t)KBt * NBt * 64 * conv_frag_bytes(cout));
         if (s == RSV_OK) {
             hipLaunchKernelGGL(k_pack, dim3(nblk((int64_t)KBt * NBt * 64)), dim3(256), 0, c->stream, w, cin, cout, 1, KBt,
                                NBt, conv_kw(cout), (short *)tmp.wt[1]);
-            s = conv_bwd_data(&tmp, 1, nx, ny, nz, dy, dx);
+            s = conv_bwd_data(&tmp, 1, nx, ny, nz, nz, dy, dx, nullptr, nullptr, nullptr);
         }
     }
     if (s == RSV_OK && (dw || db)) {
@@ -1540,7 +1693,7 @@ rsv_status rsv_conv3d_bwd(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32_
         s = dev_alloc(c, (void **)&gw, (size_t)nwb * sizeof(float));
         if (s == RSV_OK && hipMemsetAsync(gw, 0, (size_t)nwb * sizeof(float), c->stream) != hipSuccess)
             s = set_err(c, RSV_ERR_HIP, "hipMemsetAsync");
-        if (s == RSV_OK) s = conv_bwd_weight(&tmp, 1, nx, ny, nz, 0, x, dy, 1.0f, gw, gw + 27LL * cin * cout);
+        if (s == RSV_OK) s = conv_bwd_weight(&tmp, 1, nx, ny, nz, nz, 0, x, dy, 1.0f, gw, gw + 27LL * cin * cout);
         if (s == RSV_OK && dw)
             if (hipMemcpyAsync(dw, gw, 27LL * cin * cout * sizeof(float), hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
                 s = set_err(c, RSV_ERR_HIP, "hipMemcpyAsync");
@@ -1551,7 +1704,6 @@ rsv_status rsv_conv3d_bwd(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32_
         dev_free(gw);
     }
     if (hipStreamSynchronize(c->stream) != hipSuccess && s == RSV_OK) s = set_err(c, RSV_ERR_HIP, "sync");
-    (void)g;
     return s;
 }
 

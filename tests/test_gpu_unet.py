@@ -429,3 +429,79 @@ def test_fgmres_mixed_decisions_match_oracle(rsv, ctx, mode, thetas):
         checked += 1
     assert checked >= 1
     A.close(); g.close(); net.close()
+
+
+# ---------------------------------------------------------------- staged convolutions and batches
+
+@pytest.mark.parametrize("cin", [4, 16, 32, 64])
+@pytest.mark.parametrize("cout", [16, 32, 64])
+@pytest.mark.parametrize("dims", [(1, 1, 1), (15, 3, 3), (17, 5, 5), (33, 9, 2), (18, 21, 31)])
+def test_staged_conv_edges(rsv, ctx, dims, cin, cout):
+    """Every channel pair of the staged kernels at the edges of their 16 x 4 x 4
+    (x 2) bricks, forward and data gradient: the bound of the layer tests."""
+    log("staged conv", dims, cin, cout)
+    V = dims[0] * dims[1] * dims[2]
+    x = bf16_values(11, 5, V * cin)
+    w = bf16_values(12, 5, 27 * cin * cout, -0.2, 0.2)
+    b = I.uniform(13, 5, cout, -0.5, 0.5).astype(np.float32).astype(np.float64)
+    y = torch.full((V * cout + 64,), 7.0, dtype=torch.float32, device="cuda")
+    rsv.conv3d(ctx, dims, cin, cout, bf16_bits(x), dev(w.astype(np.float32)), dev(b.astype(np.float32)), y)
+    got = y.cpu().numpy().astype(np.float64)
+    ref = U.conv3d(dims, cin, cout, x, w, b)
+    bound = U.conv3d(dims, cin, cout, np.abs(x), np.abs(w), np.abs(b))
+    assert np.all(np.abs(got[:V * cout] - ref) <= 2e-5 * bound + 1e-30)
+    assert np.all(got[V * cout:] == 7.0)
+    if cin == 4:
+        return
+    g = bf16_values(14, 5, V * cout)
+    dx = torch.zeros(V * cin, dtype=torch.float32, device="cuda")
+    rsv.conv3d_bwd(ctx, dims, cin, cout, bf16_bits(x), dev(w.astype(np.float32)), bf16_bits(g), dx=dx)
+    # the data gradient is the convolution with taps reversed and channels exchanged
+    wt = w.reshape(27, cin, cout)[::-1].transpose(0, 2, 1).reshape(-1)
+    ref = U.conv3d(dims, cout, cin, g, wt, np.zeros(cin))
+    bound = U.conv3d(dims, cout, cin, np.abs(g), np.abs(wt), np.zeros(cin))
+    assert np.all(np.abs(dx.cpu().numpy().astype(np.float64) - ref) <= 2e-5 * bound + 1e-30)
+
+
+@pytest.mark.parametrize("dims,nb", [((4, 4, 4), 5), ((12, 8, 20), 3), ((64, 64, 64), 10)])
+def test_batch_is_its_samples(rsv, ctx, dims, nb):
+    """Samples that share a pass do not see each other: a batch's loss is the
+    mean of its samples' losses and its gradient the mean over the samples of
+    the gradient of a batch that repeats that sample (FP32 sums in another
+    order: 2e-6 of the gradient's norm; a single sample's own gradient is
+    rounded to BF16 at another scale, 1 instead of 1 / nb).  The last case needs
+    two passes (2^21 voxels each)."""
+    log("batch", dims, nb)
+    g = rsv.Grid(ctx, *dims)
+    net = rsv.Net(ctx, seed=3)
+    net.set_params(net_params(21).astype(np.float32))
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    n = g.ncell
+    r = torch.randn(nb, 3 * n, generator=gen, device="cuda", dtype=torch.float64) * torch.logspace(-3, 3, nb, device="cuda",
+                                                                                                  dtype=torch.float64)[:, None]
+    e = torch.randn(nb, 3 * n, generator=gen, device="cuda", dtype=torch.float64)
+    k = torch.randn(nb, n, generator=gen, device="cuda") * 2 + torch.arange(nb, device="cuda")[:, None]
+    loss, grad = net.loss_grad(g, nb, r, e, k)
+    one = [net.loss_grad(g, 1, r[b].contiguous(), e[b].contiguous(), k[b].contiguous()) for b in range(nb)]
+    assert abs(loss - np.mean([o[0] for o in one])) <= 1e-6 * abs(loss)
+    rep = lambda t, b: t[b:b + 1].expand(nb, -1).contiguous()  # noqa: E731
+    ref = np.mean([net.loss_grad(g, nb, rep(r, b), rep(e, b), rep(k, b))[1].astype(np.float64) for b in range(nb)], axis=0)
+    assert rel(grad, ref) <= 2e-6
+    net.close(); g.close()
+
+
+def test_input_channel_statistics(rsv, ctx):
+    """ln k is standardised over each sample's own grid: a constant field is the
+    zero channel, whatever the constant, and a shifted and scaled field is the
+    same channel (powers of two: exactly)."""
+    dims = (8, 12, 16)
+    g = rsv.Grid(ctx, *dims)
+    net = rsv.Net(ctx, seed=4)
+    n = g.ncell
+    r = dev(I.test_vector(31, 3 * n))
+    k = torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(6), device="cuda")
+    out = [net.forward(g, r, f, torch.zeros_like(r)).clone() for f in
+           (torch.zeros_like(k), torch.full_like(k, 0.1), torch.full_like(k, -3.7), k, 4 * k)]
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+    assert torch.equal(out[3], out[4]) and not torch.equal(out[0], out[3])
+    net.close(); g.close()
