@@ -271,7 +271,9 @@ rsv_status grid_create_planes(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, in
     *out = nullptr;
     if (nx < 1 || ny < 1 || nz < 1) return set_err(c, RSV_ERR_ARG, "grid dimensions must be >= 1");
     if (ordering != RSV_BOTTOM_UP && ordering != RSV_TOP_DOWN) return set_err(c, RSV_ERR_ARG, "bad ordering");
-    if (mx < 1 || my < 1 || mz < 1) return set_err(c, RSV_ERR_ARG, "bad plane moduli");
+    // a tile's columns must keep their order inside one box
+    if (mx < 1 || my < 1 || mz < 1 || (mx < nx && mx % 8) || (my < ny && my % 8))
+        return set_err(c, RSV_ERR_ARG, "bad plane moduli");
     const int ntx = (nx + 7) / 8, nty = (ny + 7) / 8;
     const int64_t nslot = (int64_t)ntx * nty * nz * 64;
     if (nslot * 3 >= ((int64_t)1 << 31)) return set_err(c, RSV_ERR_ARG, "grid too large (3*padded cells must fit int32)");
@@ -282,37 +284,9 @@ rsv_status grid_create_planes(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, in
     g->ncell = (int64_t)nx * ny * nz;
     g->nv = 3 * nslot;
     g->nplanes = std::min(mx, nx) + std::min(my, ny) + std::min(mz, nz) - 2;
-    // real slots bucketed by plane (i mod mx) + (j mod my) + (k mod mz),
-    // ascending slot within a plane
-    std::vector<int64_t> cnt(g->nplanes + 1, 0);
-    for (int k = 0; k < nz; ++k)
-        for (int j = 0; j < ny; ++j)
-            for (int i = 0; i < nx; ++i) cnt[i % mx + j % my + k % mz + 1]++;
-    for (int p = 0; p < g->nplanes; ++p) cnt[p + 1] += cnt[p];
-    g->plane_ptr = cnt;
-    std::vector<int32_t> slots(g->ncell);
-    std::vector<int64_t> fill(cnt.begin(), cnt.end() - 1);
-    int li[64], lj[64];
-    for (int L = 0; L < 64; ++L) lane_ij(L, li[L], lj[L]);
-    int64_t s = 0;
-    for (int T = 0; T < ntx * nty; ++T) {
-        const int x0 = (T % ntx) * 8, y0 = (T / ntx) * 8;
-        for (int r = 0; r < nz; ++r)
-            for (int L = 0; L < 64; ++L, ++s) {
-                const int gx = x0 + li[L], gy = y0 + lj[L];
-                if (gx >= nx || gy >= ny) continue;
-                const int k = wrap_nz(r - li[L] - lj[L], nz);
-                slots[fill[gx % mx + gy % my + k % mz]++] = (int32_t)s;
-            }
-    }
-    rsv_status st = dev_alloc(c, (void **)&g->d_plane_slots, slots.size() * sizeof(int32_t));
-    if (st != RSV_OK) { delete g; return st; }
-    hipError_t e = hipMemcpy(g->d_plane_slots, slots.data(), slots.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-        dev_free(g->d_plane_slots);
-        delete g;
-        return set_err(c, RSV_ERR_HIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
-    }
+    g->mx = mx;
+    g->my = my;
+    g->mz = mz;
     *out = g;
     return RSV_OK;
 }
@@ -327,7 +301,6 @@ rsv_status rsv_grid_create(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32
 void rsv_grid_destroy(rsv_grid *g)
 {
     if (!g) return;
-    dev_free(g->d_plane_slots);
     delete g;
 }
 

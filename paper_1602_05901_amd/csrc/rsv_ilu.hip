@@ -75,16 +75,48 @@ __device__ __forceinline__ void bwd_cell(const T *u, const T *dd, const T *vx, c
     for (int p = 0; p < 3; ++p) out[p] = fma_t(dd[3 * p + 2], tv[2], fma_t(dd[3 * p + 1], tv[1], dd[3 * p] * tv[0]));
 }
 
+// ---------------------------------------------------------------- hyperplanes
+// Hyperplane p of a grid of boxes: the cells with (i mod mx) + (j mod my) +
+// (k mod mz) = p.  Thread t of a launch takes column t mod (64 tiles) of the
+// boxes' layer t / (64 tiles), which holds at most one cell of p; a wave's
+// columns are one tile's lanes, whose cells of p share a row.  (Lists of each
+// plane's slots, built on the host with every grid and auxiliary grid, were 12
+// of the 14.7 ms of a RAS setup at 128x128x64, which takes 2.4 ms without.)
+struct Planes {
+    Geo g;
+    int mx, my, mz, p;
+};
+inline unsigned plane_blocks(const rsv_grid *G)
+{
+    const int64_t n = (int64_t)G->geo.ntx * G->geo.nty * 64 * ((G->geo.nz + G->mz - 1) / G->mz);
+    return (unsigned)((n + BS - 1) / BS);
+}
+__device__ inline bool plane_cell(const Planes &P, int &gx, int &gy, int &k, int64_t &slot)
+{
+    const int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x, layer = (int64_t)P.g.ntx * P.g.nty * 64;
+    const int zb = (int)(t / layer), T = (int)((t - zb * layer) >> 6);
+    const int x0 = (T % P.g.ntx) * 8, y0 = (T / P.g.ntx) * 8;
+    const int q = P.p - x0 % P.mx - y0 % P.my;   // k mod mz of the tile's lane (0, 0)
+    if (q < 0 || q >= P.mz + 14) return false;
+    int i, j;
+    lane_ij((int)(t & 63), i, j);
+    gx = x0 + i;
+    gy = y0 + j;
+    const int kk = q - i - j;
+    k = zb * P.mz + kk;
+    if (kk < 0 || kk >= P.mz || gx >= P.g.nx || gy >= P.g.ny || k >= P.g.nz) return false;
+    slot = slot_of(P.g, gx, gy, k);
+    return true;
+}
+
 // ---------------------------------------------------------------- factorisation (one launch per hyperplane)
-__global__ __launch_bounds__(BS) void k_factor_plane(Geo g, const int32_t *__restrict__ slots, int64_t n,
-                                                     const double *__restrict__ A, double *__restrict__ Lf,
+__global__ __launch_bounds__(BS) void k_factor_plane(Planes P, const double *__restrict__ A, double *__restrict__ Lf,
                                                      double *__restrict__ Dinv, int32_t *flags)
 {
-    const int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (t >= n) return;
-    const int64_t slot = slots[t];
+    const Geo &g = P.g;
     int gx, gy, k;
-    cell_of(g, slot, gx, gy, k);
+    int64_t slot;
+    if (!plane_cell(P, gx, gy, k, slot)) return;
     double D[9];
     for (int e = 0; e < 9; ++e) D[e] = A[aidx(slot, 27 + e)];
     for (int s = 0; s < 3; ++s) {   // -z, -y, -x: ascending column order
@@ -137,15 +169,13 @@ __global__ __launch_bounds__(BS) void k_upper_f32(int64_t nslot, const double *_
 // T: arithmetic / factor type.  Upper blocks: U (T, [row][27][64]) when
 // non-null, else the FP64 matrix A directly.
 template <typename T>
-__global__ __launch_bounds__(BS) void k_fwd_plane(Geo g, const int32_t *__restrict__ slots, int64_t n,
-                                                  const T *__restrict__ Lf, const double *__restrict__ r,
+__global__ __launch_bounds__(BS) void k_fwd_plane(Planes P, const T *__restrict__ Lf, const double *__restrict__ r,
                                                   T *__restrict__ y)
 {
-    const int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (t >= n) return;
-    const int64_t slot = slots[t];
+    const Geo &g = P.g;
     int gx, gy, k;
-    cell_of(g, slot, gx, gy, k);
+    int64_t slot;
+    if (!plane_cell(P, gx, gy, k, slot)) return;
     T v[3][3];   // -z, -y, -x neighbour values
     for (int s = 0; s < 3; ++s) {
         int di, dj, dk;
@@ -164,16 +194,14 @@ __global__ __launch_bounds__(BS) void k_fwd_plane(Geo g, const int32_t *__restri
 }
 
 template <typename T>
-__global__ __launch_bounds__(BS) void k_bwd_plane(Geo g, const int32_t *__restrict__ slots, int64_t n,
-                                                  const T *__restrict__ Dinv, const T *__restrict__ U,
+__global__ __launch_bounds__(BS) void k_bwd_plane(Planes P, const T *__restrict__ Dinv, const T *__restrict__ U,
                                                   const double *__restrict__ A, const T *__restrict__ y,
                                                   T *__restrict__ zt, double *__restrict__ z)
 {
-    const int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x;
-    if (t >= n) return;
-    const int64_t slot = slots[t];
+    const Geo &g = P.g;
     int gx, gy, k;
-    cell_of(g, slot, gx, gy, k);
+    int64_t slot;
+    if (!plane_cell(P, gx, gy, k, slot)) return;
     T v[3][3];   // +x, +y, +z neighbour values
     for (int s = 4; s < 7; ++s) {
         int di, dj, dk;
@@ -816,11 +844,9 @@ struct Bilu0 : PcImpl {
         s = flags_reset(c);
         if (s != RSV_OK) return s;
         ProfScope ps(c, RSV_K_FACTOR);
+        const unsigned pb = plane_blocks(M->g);
         for (int p = 0; p < M->g->nplanes; ++p) {
-            const int64_t off = M->g->plane_ptr[p], n = M->g->plane_ptr[p + 1] - off;
-            if (n == 0) continue;
-            hipLaunchKernelGGL(k_factor_plane, dim3((unsigned)((n + BS - 1) / BS)), dim3(BS), 0, c->stream, g,
-                               M->g->d_plane_slots + off, n, M->d_A, Lf, Dinv, c->d_flags);
+            hipLaunchKernelGGL(k_factor_plane, dim3(pb), dim3(BS), 0, c->stream, planes(p), M->d_A, Lf, Dinv, c->d_flags);
             RSV_LAUNCH(c);
         }
         s = flags_check(c, bad_cell);
@@ -879,24 +905,19 @@ struct Bilu0 : PcImpl {
         return RSV_OK;
     }
 
+    Planes planes(int p) const { return Planes{M->g->geo, M->g->mx, M->g->my, M->g->mz, p}; }
+
     template <typename T>
     rsv_status apply_plane(const double *r, double *z, const T *L_, const T *D_, const T *U_, T *zt)
     {
-        const Geo &g = M->g->geo;
         T *y = (T *)ybuf;
-        for (int p = 0; p < M->g->nplanes; ++p) {
-            const int64_t off = M->g->plane_ptr[p], n = M->g->plane_ptr[p + 1] - off;
-            if (n == 0) continue;
-            hipLaunchKernelGGL(k_fwd_plane<T>, dim3((unsigned)((n + BS - 1) / BS)), dim3(BS), 0, c->stream, g,
-                               M->g->d_plane_slots + off, n, L_, r, y);
-        }
+        const unsigned pb = plane_blocks(M->g);
+        for (int p = 0; p < M->g->nplanes; ++p)
+            hipLaunchKernelGGL(k_fwd_plane<T>, dim3(pb), dim3(BS), 0, c->stream, planes(p), L_, r, y);
         RSV_LAUNCH(c);
-        for (int p = M->g->nplanes - 1; p >= 0; --p) {
-            const int64_t off = M->g->plane_ptr[p], n = M->g->plane_ptr[p + 1] - off;
-            if (n == 0) continue;
-            hipLaunchKernelGGL(k_bwd_plane<T>, dim3((unsigned)((n + BS - 1) / BS)), dim3(BS), 0, c->stream, g,
-                               M->g->d_plane_slots + off, n, D_, U_, M->d_A, (const T *)y, zt, z);
-        }
+        for (int p = M->g->nplanes - 1; p >= 0; --p)
+            hipLaunchKernelGGL(k_bwd_plane<T>, dim3(pb), dim3(BS), 0, c->stream, planes(p), D_, U_, M->d_A, (const T *)y, zt,
+                               z);
         RSV_LAUNCH(c);
         return RSV_OK;
     }

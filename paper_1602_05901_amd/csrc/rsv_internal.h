@@ -166,8 +166,7 @@ struct rsv_grid {
     int64_t ncell = 0;
     int64_t nv = 0;               // internal vector length (3*nslot)
     int nplanes = 0;              // nx+ny+nz-2 hyperplanes
-    std::vector<int64_t> plane_ptr;   // host, nplanes+1
-    int32_t *d_plane_slots = nullptr; // device, real slots sorted by (plane, slot)
+    int mx = 0, my = 0, mz = 0;   // cell (i, j, k) lies on hyperplane i mod mx + j mod my + k mod mz
 };
 
 struct SolverWork;
@@ -296,8 +295,8 @@ rsv_status scal_wait(rsv_ctx *c, int buf);
 rsv_status scal_set(rsv_ctx *c, int k0, const double *vals, int n);
 
 // A grid whose factorisation "hyperplanes" are (i mod mx) + (j mod my) + (k mod mz):
-// for a grid of independent boxes of mx x my x mz cells (rsv_grid_create: the
-// plain hyperplanes, mx = nx, my = ny, mz = nz).
+// for a grid of independent boxes of mx x my x mz cells, mx and my multiples of
+// 8 (rsv_grid_create: the plain hyperplanes, mx = nx, my = ny, mz = nz).
 rsv_status grid_create_planes(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32_t ordering, int mx, int my,
                               int mz, rsv_grid **out);
 
