@@ -350,3 +350,34 @@ __host__ __device__ inline bool inv3(const double *a, double *o)
     }
     return na * ni <= 1e14;
 }
+
+// ------------------------------------------------------------------ faces between sweeping tiles
+// A 64-bit face word holds a 32-bit call epoch and one 32-bit half of a value;
+// relaxed agent-scope accesses, valid exactly when the epoch matches.
+__device__ inline uint64_t face_ld(const uint64_t *p)
+{
+    return __hip_atomic_load(const_cast<uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void face_st(uint64_t *p, uint64_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// 32-bit half h of a value's bits (h = 0 for FP32)
+__device__ inline uint32_t half_bits(double v, int h) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> (32 * h)); }
+__device__ inline uint32_t half_bits(float v, int) { return __float_as_uint(v); }
+
+// Spin-loop guard: checks the clock and the shared error flag only every 256th
+// call (the flag read is a device-scope load, which waits for every memory
+// operation the wave still has in flight).
+__device__ inline bool spin_guard(int32_t *flags, uint64_t t0, uint32_t &n, uint64_t limit)
+{
+    if ((++n & 255u) != 0u) return false;
+    const int32_t fl = __hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (fl & FLAG_TIMEOUT) return true;
+    if (wall_clock64() - t0 > limit) {
+        atomicOr(&flags[0], FLAG_TIMEOUT);
+        return true;
+    }
+    return false;
+}

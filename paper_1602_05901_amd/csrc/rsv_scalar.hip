@@ -410,6 +410,279 @@ __global__ __launch_bounds__(APPLY_T) void k_sras_apply(SRasDev d, const double 
     }
 }
 
+// ---------------------------------------------------------------- RAS by pipelined tile columns
+// Every subdomain's extended box, padded to whole 8 x 8 tiles, has a place of
+// its own in an auxiliary tile-lane grid (SX x SY boxes of GX x GY cells, EZ
+// layers), as the block systems' boxes do, and one wave sweeps one tile column
+// at a time: lane (i, j) walks up its column skewed by i + j steps, so a step's
+// 64 cells lie on one hyperplane.  A step reads its neighbours' previous results
+// from LDS and costs one LDS round trip and three dependent multiply-adds, so
+// the wave needs no helper waves: its factors, its right-hand side and its face
+// words are loaded ST_AHEAD steps early into registers.  Tiles exchange faces
+// through epoch-tagged words and are handed out by a ticket in topological order
+// inside their boxes, so a tile waits only on tiles that run already, and every
+// wait is bounded.
+//
+// Against one workgroup per subdomain (above) this fills the chip from a few
+// subdomains: 27 boxes of 88^3 are 3267 tile columns.  One apply at 256^3 in 27
+// boxes 3.48 -> 0.57 ms (2.8 TB/s of its 80 + 8 bytes a cell); what bounds it
+// is the pipeline's fill, 21 anti-diagonals of tiles per box.
+//
+// The local matrices are zero outside Omega_s, where values are zero too.  r is
+// read from and z written to the caller's order a layer of the tile at a time,
+// eight runs of 64 bytes, and an LDS ring of 16 layers delays a lane's value by
+// its i + j steps (the 64 cells of a step are 64 separate lines there: 130 us
+// more to read r and 180 to write z at 256^3).
+// Steps loaded ahead, and waves (tile columns at a time) per CU.  A tile falls
+// behind its upstream neighbours until their face words are there when it loads
+// them, so a longer lead is a longer pipeline (loads return in order: faces
+// loaded later than the factors would only wait for them), and more columns in
+// flight queue behind one another: at 256^3 in 27 boxes, forward / backward us,
+// 4 waves with a lead of 4, 6, 8 steps 264/301, 280/317, 307/343; 2 waves
+// 360/362; 6 waves 273/321; 8 waves with a lead of 8 335/377.
+constexpr int ST_AHEAD = 4;
+constexpr int ST_WAVES = 4;
+
+struct STBox {
+    int32_t x0, x1, y0, y1, z0, z1, ex, ey, ez;   // core and the extended box's origin
+};
+
+struct STDev {
+    Geo a, g;                    // auxiliary grid, the matrix's grid
+    int32_t btx, bty, SX, nsub, ov;
+    const STBox *box;
+    double *l;                   // [row][3][64]: a_ck / D_k toward -z, -y, -x
+    double *u;                   // [row][4][64]: a_cm toward +x, +y, +z; 1 / D_c
+    double *y;                   // [row][64]
+};
+
+// the column of auxiliary cell (X, Y): its box, its grid column, the range
+// [klo, khi) of its layers in Omega_s and [olo, ohi) of those the box owns
+struct STColumn {
+    int gx, gy, ez, klo, khi, olo, ohi;
+};
+__device__ inline STColumn st_column(const STDev &d, int X, int Y)
+{
+    STColumn c{0, 0, 0, 0, 0, 0, 0};
+    const int bx = X / (8 * d.btx), by = Y / (8 * d.bty), s = by * d.SX + bx;
+    if (s >= d.nsub) return c;
+    const STBox q = d.box[s];
+    c.gx = q.ex + X - bx * 8 * d.btx;
+    c.gy = q.ey + Y - by * 8 * d.bty;
+    c.ez = q.ez;
+    const int dx = c.gx < q.x0 ? q.x0 - c.gx : (c.gx >= q.x1 ? c.gx - q.x1 + 1 : 0);
+    const int dy = c.gy < q.y0 ? q.y0 - c.gy : (c.gy >= q.y1 ? c.gy - q.y1 + 1 : 0);
+    const int64_t rest = (int64_t)d.ov - dx - dy;
+    if (c.gx >= d.g.nx || c.gy >= d.g.ny || rest < 0) {
+        c.gx = c.gy = 0;
+        return c;
+    }
+    c.klo = (int)max((int64_t)0, q.z0 - rest) - q.ez;
+    c.khi = (int)min((int64_t)d.g.nz, q.z1 + rest) - q.ez;
+    if (dx == 0 && dy == 0) {
+        c.olo = q.z0 - q.ez;
+        c.ohi = q.z1 - q.ez;
+    }
+    return c;
+}
+
+// one hyperplane of every box's factorisation (the planes before p are final)
+__global__ __launch_bounds__(SB) void k_st_factor(STDev d, int p, const double *__restrict__ coef, int32_t *flags)
+{
+    const int64_t n = (int64_t)d.g.nx * d.g.ny * d.g.nz;
+    const int64_t t = (int64_t)blockIdx.x * SB + threadIdx.x;
+    const int T = (int)(t >> 6), L = (int)(t & 63);
+    if (T >= d.a.ntx * d.a.nty) return;
+    const int tx = T % d.a.ntx, ty = T / d.a.ntx;
+    const int q = p - 8 * (tx % d.btx) - 8 * (ty % d.bty);
+    if (q < 0 || q >= d.a.nz + 14) return;
+    int i, j;
+    lane_ij(L, i, j);
+    const int X = 8 * tx + i, Y = 8 * ty + j, k = q - i - j;
+    const STColumn c = st_column(d, X, Y);
+    if (k < c.klo || k >= c.khi) return;
+    const int64_t r = row_of(d.g, c.gx, c.gy, c.ez + k);
+    const int64_t slot = slot_of(d.a, X, Y, k), e = (slot >> 6), la = slot & 63;
+    double dd = coef[3 * n + r];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {        // -z, -y, -x
+        const int dX = a == 2 ? -1 : 0, dY = a == 1 ? -1 : 0, dk = a == 0 ? -1 : 0;
+        // a lower neighbour of the box lies in the same box, so its column is one of it
+        bool in = a == 0 ? k > c.klo : (a == 1 ? Y % (8 * d.bty) > 0 : X % (8 * d.btx) > 0);
+        if (in && a > 0) {
+            const STColumn m = st_column(d, X + dX, Y + dY);
+            in = k >= m.klo && k < m.khi;
+        }
+        double lv = 0.0;
+        if (in) {
+            const int64_t ns = slot_of(d.a, X + dX, Y + dY, k + dk);
+            const double a_ck = coef[LO_SLOT[a] * n + r];
+            const double a_kc = coef[(6 - LO_SLOT[a]) * n + row_of(d.g, c.gx + dX, c.gy + dY, c.ez + k + dk)];
+            lv = a_ck * d.u[(ns >> 6) * 256 + 192 + (ns & 63)];
+            dd -= lv * a_kc;
+        }
+        d.l[e * 192 + a * 64 + la] = lv;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {        // +x, +y, +z
+        const int dX = a == 0, dY = a == 1;
+        bool in = a == 2 ? k + 1 < c.khi : (a == 1 ? (Y + 1) % (8 * d.bty) > 0 : (X + 1) % (8 * d.btx) > 0);
+        if (in && a < 2) {
+            const STColumn m = st_column(d, X + dX, Y + dY);
+            in = k >= m.klo && k < m.khi;
+        }
+        d.u[e * 256 + a * 64 + la] = in ? coef[HI_SLOT[a] * n + r] : 0.0;
+    }
+    double di = 0.0;
+    if (!(fabs(dd) > 1e-300) || !isfinite(dd)) {
+        atomicOr(&flags[0], (int32_t)FLAG_PIVOT);
+        atomicMin(&flags[1], (int32_t)r);
+    } else {
+        di = 1.0 / dd;
+    }
+    d.u[e * 256 + 192 + la] = di;
+}
+
+struct STSweep {
+    const int32_t *tile_order;
+    uint64_t *ticket;
+    uint64_t ticket_base;
+    uint64_t *face;              // [tile][nz + 7][x: 16 words, y: 16 words]
+    uint32_t epoch;
+    int32_t *flags;
+    uint64_t wait_limit;
+};
+
+// DIR 0: y = L^-1 r, v the caller's r.  DIR 1: z = U^-1 y, v the caller's z.
+// Step t of a tile: lane (i, j) is at k = t - (i + j) (DIR 0) or nz - 1 - (t -
+// (14 - i - j)) (DIR 1), on row t mod nz or (nz + 13 - t) mod nz.  Lanes whose k
+// is out of range load the nearest in-range lane's entry, so a step touches only
+// the lines it needs and every load is unconditional.
+template <int DIR>
+__global__ __launch_bounds__(64) void k_st_sweep(STDev d, STSweep a, double *__restrict__ v)
+{
+    __shared__ double lds[80];   // 64 results, then the x and the y face's 8 values
+    __shared__ double ring[16 * 64];   // layer k of r (DIR 0) or z (DIR 1) in entry k mod 16
+    uint32_t *ldw = (uint32_t *)lds;
+    constexpr int NF = DIR == 0 ? 3 : 4;
+    const int nz = d.a.nz, NT = d.a.ntx * d.a.nty, nsteps = nz + 14, L = threadIdx.x;
+    const int64_t frow = (int64_t)(nz + 7) * 32, plane = (int64_t)d.g.nx * d.g.ny;
+    int li, lj;
+    lane_ij(L, li, lj);
+    const int dd = DIR == 0 ? li + lj : 14 - li - lj;       // step at which the lane's column starts
+    // where the lane's x and y neighbour values are (indices into lds)
+    const int ax = DIR == 0 ? (li > 0 ? ij_lane(li - 1, lj) : 64 + lj) : (li < 7 ? ij_lane(li + 1, lj) : 64 + lj);
+    const int ay = DIR == 0 ? (lj > 0 ? ij_lane(li, lj - 1) : 72 + li) : (lj < 7 ? ij_lane(li, lj + 1) : 72 + li);
+    // face words: lane q < 32 holds half (q >> 3) & 1 of entry q & 7 of the x (q < 16) or y face
+    const int fe = L & 7, fh = (L >> 3) & 1, fy = (L >> 4) & 1;
+    const bool flane = L < 32;
+    const int fdst = 128 + 16 * fy + 2 * fe + fh;                                          // incoming, 32-bit index
+    const int fsrc = 2 * (fy ? ij_lane(fe, DIR == 0 ? 7 : 0) : ij_lane(DIR == 0 ? 7 : 0, fe)) + fh;   // outgoing
+    const int fk_in = DIR == 0 ? fe : 7 - fe, fk_out = DIR == 0 ? 7 + fe : 14 - fe;
+    const int lq = L & 31;
+    struct Pre {
+        double f[NF], v;
+        uint64_t w;
+    };
+    for (;;) {
+        uint64_t tk = 0;
+        if (L == 0) tk = atomicAdd((unsigned long long *)a.ticket, 1ull) - a.ticket_base;
+        tk = __shfl(tk, 0, 64);
+        if (tk >= (uint64_t)NT) break;
+        const int T = a.tile_order[DIR == 0 ? (int)tk : NT - 1 - (int)tk];
+        const int tx = T % d.a.ntx, ty = T / d.a.ntx, bx = tx % d.btx, by = ty % d.bty;
+        const bool has_x = DIR == 0 ? bx > 0 : bx < d.btx - 1, has_y = DIR == 0 ? by > 0 : by < d.bty - 1;
+        const bool out_x = DIR == 0 ? bx < d.btx - 1 : bx > 0, out_y = DIR == 0 ? by < d.bty - 1 : by > 0;
+        const bool fin = flane && (fy ? has_y : has_x), fout = flane && (fy ? out_y : out_x);
+        // a tile without that neighbour reads its own row, an in-range dummy
+        const int Tn = !fin ? T : (DIR == 0 ? (fy ? T - d.a.ntx : T - 1) : (fy ? T + d.a.ntx : T + 1));
+        const uint64_t *fsp = a.face + Tn * frow + lq;
+        uint64_t *fdp = a.face + T * frow + lq;
+        const STColumn c = st_column(d, 8 * tx + li, 8 * ty + lj);
+        // the caller's entry of layer k is cv[k * ck]
+        const bool td = d.g.ordering == RSV_TOP_DOWN;
+        const int64_t ck = td ? -plane : plane;
+        double *cv = v + row_of(d.g, c.gx, c.gy, c.ez);
+        const int64_t rowbase = (int64_t)T * nz;
+        auto issue = [&](Pre &R, int t) {
+            const int tc = t < nsteps ? t : nsteps - 1;
+            const int dmin = DIR == 0 ? max(tc - nz + 1, 0) : max(14 - tc, 0);
+            const int dmax = DIR == 0 ? min(tc, 14) : min(13 - tc + nz, 14);
+            const int Ls = min(max(L, lane_first(dmin)), lane_first(dmax + 1) - 1);
+            const int64_t row = rowbase + (DIR == 0 ? wrap_nz(tc, nz) : wrap_nz(nz + 13 - tc, nz));
+            const double *f = (DIR == 0 ? d.l : d.u) + row * (NF * 64) + Ls;
+#pragma unroll
+            for (int q = 0; q < NF; ++q) R.f[q] = __builtin_nontemporal_load(f + q * 64);
+            if constexpr (DIR == 0) {
+                R.v = cv[min(max(tc, c.klo), max(c.khi - 1, c.klo)) * ck];   // layer t; taken up dd steps later
+            } else {
+                R.v = d.y[row * 64 + Ls];
+            }
+            const int tr = t < nz + 7 ? t : nz + 6;
+            R.w = face_ld(fsp + (int64_t)tr * 32);
+        };
+        double last = 0.0;
+        auto step = [&](Pre &R, int t) {
+            // the faces this step's boundary lanes need
+            const bool need = fin && (unsigned)(t - fk_in) < (unsigned)nz;
+            uint64_t w = R.w;
+            if (__ballot(need && (uint32_t)(w >> 32) != a.epoch) != 0ull) {
+                const uint64_t t0 = wall_clock64();
+                uint32_t n = 0;
+                for (;;) {
+                    if (need) w = face_ld(fsp + (int64_t)t * 32);
+                    if (__ballot(need && (uint32_t)(w >> 32) != a.epoch) == 0ull) break;
+                    if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            }
+            if (flane) ldw[fdst] = need ? (uint32_t)w : 0u;
+            if constexpr (DIR == 0) ring[(t & 15) * 64 + L] = R.v;
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);   // one wave: its LDS accesses complete in program order
+            const double vx = lds[ax], vy = lds[ay];
+            const int k = DIR == 0 ? t - dd : nz - 1 - (t - dd);
+            const bool in = k >= c.klo && k < c.khi;
+            double o = DIR == 0 ? ring[((t - dd) & 15) * 64 + L] : R.v;
+            if constexpr (DIR == 0) {
+                o -= R.f[0] * last;
+                o -= R.f[1] * vy;
+                o -= R.f[2] * vx;
+            } else {
+                o -= R.f[0] * vx;
+                o -= R.f[1] * vy;
+                o -= R.f[2] * last;
+                o *= R.f[3];
+            }
+            o = in ? o : 0.0;
+            last = o;
+            lds[L] = o;
+            if constexpr (DIR == 1) ring[(k & 15) * 64 + L] = o;
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            const uint32_t fo = ldw[fsrc];
+            if (fout && (unsigned)(t - fk_out) < (unsigned)nz)
+                face_st(fdp + (int64_t)(t - 7) * 32, ((uint64_t)a.epoch << 32) | fo);
+            if constexpr (DIR == 0) {
+                if (k >= 0 && k < nz) d.y[(rowbase + wrap_nz(t, nz)) * 64 + L] = o;
+            } else {
+                // every lane has passed layer kz
+                const int kz = nz - 1 - (t - 14);
+                const double z = ring[(kz & 15) * 64 + L];
+                if (kz >= c.olo && kz < c.ohi) cv[kz * ck] = z;
+            }
+        };
+        Pre R[ST_AHEAD];
+#pragma unroll
+        for (int q = 0; q < ST_AHEAD; ++q) issue(R[q], q);
+        // steps past the last have no lane in range
+        for (int t = 0; t < nsteps; t += ST_AHEAD)
+#pragma unroll
+            for (int q = 0; q < ST_AHEAD; ++q) {
+                step(R[q], t + q);
+                issue(R[q], t + q + ST_AHEAD);
+            }
+    }
+}
+
 int64_t box_start(int64_t b, int64_t len, int64_t p)
 {
     const int64_t base = len / p, rem = len % p;
@@ -610,6 +883,137 @@ struct SRas final : PcImpl {
     }
 };
 
+// The tile-column form of the scalar RAS (and of BILU0: one subdomain).
+struct STile final : PcImpl {
+    rsv_matrix *M = nullptr;
+    rsv_ctx *c = nullptr;
+    STDev d{};
+    int64_t ncell = 0, nbytes = 0;          // cells over all Omega_s
+    int nplane = 0;
+    std::vector<void *> mem;
+    int32_t *tile_order = nullptr;
+    uint64_t *face = nullptr;
+    bool unfit = false;                     // the boxes pad too much or exceed the index range
+
+    ~STile() override
+    {
+        if (c) (void)hipStreamSynchronize(c->stream);
+        for (void *p : mem) dev_free(p);
+    }
+    int64_t bytes() const override { return nbytes; }
+    // per Omega_s cell: 3 + 3 coefficients and the pivot inverse (56 B), r in,
+    // y out, y in (24 B); z out once per grid cell
+    int64_t apply_bytes() const override
+    {
+        const Geo &G = M->g->geo;
+        return ncell * 80 + (int64_t)G.nx * G.ny * G.nz * 8;
+    }
+    template <class T> rsv_status alloc(T **p, int64_t n, bool zero)
+    {
+        rsv_status s = dev_alloc(c, (void **)p, (size_t)n * sizeof(T));
+        if (s != RSV_OK) return s;
+        mem.push_back(*p);
+        nbytes += n * (int64_t)sizeof(T);
+        if (zero) RSV_HIP(c, hipMemsetAsync(*p, 0, (size_t)n * sizeof(T), c->stream));
+        return RSV_OK;
+    }
+
+    rsv_status setup(int px, int py, int pz, int ov, int64_t *bad_cell)
+    {
+        const Geo &G = M->g->geo;
+        const int64_t nsub = (int64_t)px * py * pz;
+        auto lo = [](int64_t v, int64_t o) { return (int32_t)std::max<int64_t>(0, v - o); };
+        int EX = 1, EY = 1, EZ = 1;
+        // extended box sizes, and the cells of Omega_s (at most the extended boxes')
+        std::vector<STBox> B((size_t)nsub);
+        for (int64_t s = 0; s < nsub; ++s) {
+            const int64_t sx = s % px, sy = (s / px) % py, sz = s / ((int64_t)px * py);
+            STBox &b = B[s];
+            b.x0 = (int32_t)box_start(sx, G.nx, px); b.x1 = (int32_t)box_start(sx + 1, G.nx, px);
+            b.y0 = (int32_t)box_start(sy, G.ny, py); b.y1 = (int32_t)box_start(sy + 1, G.ny, py);
+            b.z0 = (int32_t)box_start(sz, G.nz, pz); b.z1 = (int32_t)box_start(sz + 1, G.nz, pz);
+            b.ex = lo(b.x0, ov); b.ey = lo(b.y0, ov); b.ez = lo(b.z0, ov);
+            const int ex = (int)std::min<int64_t>(G.nx, (int64_t)b.x1 + ov) - b.ex;
+            const int ey = (int)std::min<int64_t>(G.ny, (int64_t)b.y1 + ov) - b.ey;
+            const int ez = (int)std::min<int64_t>(G.nz, (int64_t)b.z1 + ov) - b.ez;
+            EX = std::max(EX, ex); EY = std::max(EY, ey); EZ = std::max(EZ, ez);
+            for (int y = 0; y < ey; ++y)
+                for (int x = 0; x < ex; ++x) {
+                    const int gx = b.ex + x, gy = b.ey + y;
+                    const int64_t rest = (int64_t)ov - (gx < b.x0 ? b.x0 - gx : (gx >= b.x1 ? gx - b.x1 + 1 : 0)) -
+                                         (gy < b.y0 ? b.y0 - gy : (gy >= b.y1 ? gy - b.y1 + 1 : 0));
+                    if (rest >= 0)
+                        ncell += std::min<int64_t>(G.nz, b.z1 + rest) - std::max<int64_t>(0, b.z0 - rest);
+                }
+        }
+        d.btx = (EX + 7) / 8;
+        d.bty = (EY + 7) / 8;
+        int64_t SX = 1;
+        while (SX * SX < nsub) ++SX;
+        const int64_t SY = (nsub + SX - 1) / SX, slots = SX * d.btx * SY * d.bty * (int64_t)EZ * 64;
+        // Boxes much smaller than their padded tiles (under about 8 cells a side)
+        // are left to the chunk form, which pads rows of 8 cells only; so are
+        // more than 2^31 / 3 slots.
+        if (slots > 4 * ncell + 4096 || 3 * slots >= ((int64_t)1 << 31)) {
+            unfit = true;
+            return RSV_OK;
+        }
+        d.SX = (int32_t)SX;
+        d.nsub = (int32_t)nsub;
+        d.ov = ov;
+        d.g = G;
+        const int ntx = (int)(SX * d.btx), nty = (int)(SY * d.bty), NT = ntx * nty;
+        d.a = Geo{8 * ntx, 8 * nty, EZ, ntx, nty, RSV_BOTTOM_UP, slots};
+        nplane = 8 * d.btx + 8 * d.bty + EZ - 2;
+        const int64_t rows = slots / 64;
+        STBox *dbox = nullptr;
+        rsv_status st = alloc(&dbox, nsub, false);
+        if (st == RSV_OK) st = alloc(&d.l, rows * 192, true);
+        if (st == RSV_OK) st = alloc(&d.u, rows * 256, true);
+        if (st == RSV_OK) st = alloc(&d.y, rows * 64, true);
+        if (st == RSV_OK) st = alloc(&tile_order, (int64_t)NT, false);
+        if (st == RSV_OK) st = alloc(&face, (int64_t)NT * (EZ + 7) * 32, true);   // no word may carry a tag (epochs are never 0)
+        if (st != RSV_OK) return st;
+        d.box = dbox;
+        std::vector<int32_t> ord(NT);
+        for (int t = 0; t < NT; ++t) ord[t] = t;
+        const int w = ntx, btx = d.btx, bty = d.bty;
+        std::stable_sort(ord.begin(), ord.end(), [=](int32_t p, int32_t q) {
+            return (p % w) % btx + (p / w) % bty < (q % w) % btx + (q / w) % bty;
+        });
+        RSV_HIP(c, hipMemcpyAsync(dbox, B.data(), (size_t)nsub * sizeof(STBox), hipMemcpyHostToDevice, c->stream));
+        RSV_HIP(c, hipMemcpyAsync(tile_order, ord.data(), (size_t)NT * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+        st = flags_reset(c);   // synchronises: the host arrays may be released after it
+        if (st != RSV_OK) return st;
+        {
+            ProfScope ps(c, RSV_K_FACTOR);
+            for (int p = 0; p < nplane; ++p)
+                hipLaunchKernelGGL(k_st_factor, dim3((unsigned)(((int64_t)NT * 64 + SB - 1) / SB)), dim3(SB), 0, c->stream, d,
+                                   p, M->d_coef, c->d_flags);
+        }
+        RSV_LAUNCH(c);
+        return flags_check(c, bad_cell);
+    }
+
+    rsv_status apply(const double *r, double *z) override
+    {
+        ProfScope ps(c, RSV_K_RAS);
+        const int NT = d.a.ntx * d.a.nty;
+        const int nw = std::min(NT, c->num_cu * ST_WAVES);
+        auto args = [&]() {
+            STSweep a{tile_order, c->d_tickets, c->ticket_base[0], face, c->epoch++, c->d_flags, c->wait_ticks};
+            if (c->epoch == 0) c->epoch = 1;
+            c->ticket_base[0] += (uint64_t)NT + nw;
+            return a;
+        };
+        hipLaunchKernelGGL(k_st_sweep<0>, dim3(nw), dim3(64), 0, c->stream, d, args(), const_cast<double *>(r));
+        RSV_LAUNCH(c);
+        hipLaunchKernelGGL(k_st_sweep<1>, dim3(nw), dim3(64), 0, c->stream, d, args(), z);
+        RSV_LAUNCH(c);
+        return RSV_OK;
+    }
+};
+
 }  // namespace
 
 rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, const double *x, double *y,
@@ -669,6 +1073,18 @@ rsv_status sras_create(rsv_matrix *A, const rsv_pc_params *p, PcImpl **out, int6
             return set_err(c, RSV_ERR_ARG, "bad RAS subdomain counts or overlap");
     }
     if (p->precision != RSV_FP64) return set_err(c, RSV_ERR_ARG, "scalar systems have FP64 preconditioners only");
+    STile *T = new (std::nothrow) STile();
+    if (!T) return set_err(c, RSV_ERR_OOM, "scalar RAS");
+    T->M = A;
+    T->c = c;
+    rsv_status st = T->setup(px, py, pz, ov, bad_cell);
+    if (st == RSV_OK && !T->unfit) {
+        *out = T;
+        return RSV_OK;
+    }
+    const bool unfit = T->unfit;
+    delete T;
+    if (!unfit) return st;
     SRas *R = new (std::nothrow) SRas();
     if (!R) return set_err(c, RSV_ERR_OOM, "scalar RAS");
     R->M = A;

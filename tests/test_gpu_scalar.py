@@ -220,3 +220,54 @@ def test_scalar_errors(rsv, ctx):
         with pytest.raises(rsv.RsvError):
             rsv.Precond(A, **kw)
     A.close(); g.close()
+
+
+@pytest.mark.parametrize("dims,parts,ov,ordering", [
+    ((16, 16, 1), (2, 2, 1), 1, 0),      # one layer: shorter than the diagonal ramp and the load lead
+    ((24, 17, 3), (1, 1, 1), 0, 1), ((40, 33, 15), (2, 2, 1), 3, 0), ((33, 47, 16), (2, 3, 1), 1, 1),
+    ((64, 9, 70), (3, 1, 2), 2, 0), ((50, 50, 50), (3, 3, 3), 1, 1),
+    ((70, 20, 20), (2, 2, 2), 25, 0),    # an overlap wider than a box's neighbour
+    ((12, 12, 12), (6, 6, 6), 1, 0)])    # boxes far below a tile: the chunk form
+def test_scalar_ras_tile_columns(rsv, ctx, dims, parts, ov, ordering):
+    """The tile-column sweeps at the edges of their work division, in both
+    numberings, twice on the same buffers (the face words' epochs move on)."""
+    log("tile columns", dims, parts, ov, ordering)
+    nx, ny, nz = dims
+    cfg, C, Ao = system(dims, 2.0, 12)
+    c = np.arange(cfg.ncell)
+    perm = ((nz - 1 - c // (nx * ny)) * ny + (c // nx) % ny) * nx + c % nx if ordering else c
+    Ct = np.empty_like(C)
+    Ct[perm] = C
+    g = rsv.Grid(ctx, *dims, ordering)
+    A = rsv.Matrix(g, dev(Ct), scalar=True)
+    M = rsv.Precond(A, type=rsv.PC_RAS, ras_px=parts[0], ras_py=parts[1], ras_pz=parts[2], ras_overlap=ov)
+    R = S.RAS(Ao, dims, parts, ov)
+    for q in range(2):
+        r = I.test_vector(20 + q, cfg.ncell)
+        rt = np.empty_like(r)
+        rt[perm] = r
+        z = torch.full((cfg.ncell,), 9.0, dtype=torch.float64, device="cuda")
+        M.apply(dev(rt), z)
+        ref = R.apply(r)
+        assert np.max(np.abs(z.cpu().numpy()[perm] - ref)) <= 1e-12 * np.max(np.abs(ref))
+    M.close(); A.close(); g.close()
+
+
+def test_scalar_wait_limit_reports_timeout_and_recovers(rsv, ctx):
+    """A wait bound of 0.1 us, set from the host, makes the tile columns' waits
+    give up: the apply says so and the next one is right."""
+    T = Sys(rsv, ctx, (64, 64, 64), 1.0, 13)
+    M = rsv.Precond(T.A, type=rsv.PC_RAS, ras_px=1, ras_py=1, ras_pz=1, ras_overlap=0)
+    r = I.test_vector(22, T.n)
+    z = torch.zeros(T.n, dtype=torch.float64, device="cuda")
+    ctx.set_wait_limit(1e-7)
+    try:
+        with pytest.raises(rsv.RsvError) as e:
+            M.apply(dev(r), z)
+        assert e.value.status == rsv.ERR_TIMEOUT
+    finally:
+        ctx.set_wait_limit(2.0)
+    M.apply(dev(r), z)
+    ref = S.ILU(T.Ao).apply(r)
+    assert np.max(np.abs(z.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
+    M.close(); T.close()
