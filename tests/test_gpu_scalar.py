@@ -227,7 +227,7 @@ def test_scalar_errors(rsv, ctx):
     ((24, 17, 3), (1, 1, 1), 0, 1), ((40, 33, 15), (2, 2, 1), 3, 0), ((33, 47, 16), (2, 3, 1), 1, 1),
     ((64, 9, 70), (3, 1, 2), 2, 0), ((50, 50, 50), (3, 3, 3), 1, 1),
     ((70, 20, 20), (2, 2, 2), 25, 0),    # an overlap wider than a box's neighbour
-    ((12, 12, 12), (6, 6, 6), 1, 0)])    # boxes far below a tile: the chunk form
+    ((12, 12, 12), (6, 6, 6), 1, 0), ((9, 8, 7), (9, 8, 7), 1, 0)])    # boxes far below a tile
 def test_scalar_ras_tile_columns(rsv, ctx, dims, parts, ov, ordering):
     """The tile-column sweeps at the edges of their work division, in both
     numberings, twice on the same buffers (the face words' epochs move on)."""
