@@ -1075,18 +1075,20 @@ rsv_status sras_create(rsv_matrix *A, const rsv_pc_params *p, PcImpl **out, int6
             return set_err(c, RSV_ERR_ARG, "bad RAS subdomain counts or overlap");
     }
     if (p->precision != RSV_FP64) return set_err(c, RSV_ERR_ARG, "scalar systems have FP64 preconditioners only");
-    STile *T = new (std::nothrow) STile();
-    if (!T) return set_err(c, RSV_ERR_OOM, "scalar RAS");
-    T->M = A;
-    T->c = c;
-    rsv_status st = T->setup(px, py, pz, ov, bad_cell);
-    if (st == RSV_OK && !T->unfit) {
-        *out = T;
-        return RSV_OK;
+    if (p->pipelined) {
+        STile *T = new (std::nothrow) STile();
+        if (!T) return set_err(c, RSV_ERR_OOM, "scalar RAS");
+        T->M = A;
+        T->c = c;
+        rsv_status st = T->setup(px, py, pz, ov, bad_cell);
+        if (st == RSV_OK && !T->unfit) {
+            *out = T;
+            return RSV_OK;
+        }
+        const bool unfit = T->unfit || st == RSV_ERR_OOM;
+        delete T;
+        if (!unfit) return st;
     }
-    const bool unfit = T->unfit || st == RSV_ERR_OOM;
-    delete T;
-    if (!unfit) return st;
     SRas *R = new (std::nothrow) SRas();
     if (!R) return set_err(c, RSV_ERR_OOM, "scalar RAS");
     R->M = A;

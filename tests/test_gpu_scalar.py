@@ -222,16 +222,17 @@ def test_scalar_errors(rsv, ctx):
     A.close(); g.close()
 
 
+@pytest.mark.parametrize("pipelined", [1, 0])   # tile columns; one workgroup per subdomain
 @pytest.mark.parametrize("dims,parts,ov,ordering", [
     ((16, 16, 1), (2, 2, 1), 1, 0),      # one layer: shorter than the diagonal ramp and the load lead
     ((24, 17, 3), (1, 1, 1), 0, 1), ((40, 33, 15), (2, 2, 1), 3, 0), ((33, 47, 16), (2, 3, 1), 1, 1),
     ((64, 9, 70), (3, 1, 2), 2, 0), ((50, 50, 50), (3, 3, 3), 1, 1),
     ((70, 20, 20), (2, 2, 2), 25, 0),    # an overlap wider than a box's neighbour
     ((12, 12, 12), (6, 6, 6), 1, 0), ((9, 8, 7), (9, 8, 7), 1, 0)])    # boxes far below a tile
-def test_scalar_ras_tile_columns(rsv, ctx, dims, parts, ov, ordering):
+def test_scalar_ras_tile_columns(rsv, ctx, dims, parts, ov, ordering, pipelined):
     """The tile-column sweeps at the edges of their work division, in both
     numberings, twice on the same buffers (the face words' epochs move on)."""
-    log("tile columns", dims, parts, ov, ordering)
+    log("tile columns", dims, parts, ov, ordering, pipelined)
     nx, ny, nz = dims
     cfg, C, Ao = system(dims, 2.0, 12)
     c = np.arange(cfg.ncell)
@@ -240,7 +241,8 @@ def test_scalar_ras_tile_columns(rsv, ctx, dims, parts, ov, ordering):
     Ct[perm] = C
     g = rsv.Grid(ctx, *dims, ordering)
     A = rsv.Matrix(g, dev(Ct), scalar=True)
-    M = rsv.Precond(A, type=rsv.PC_RAS, ras_px=parts[0], ras_py=parts[1], ras_pz=parts[2], ras_overlap=ov)
+    M = rsv.Precond(A, type=rsv.PC_RAS, ras_px=parts[0], ras_py=parts[1], ras_pz=parts[2], ras_overlap=ov,
+                    pipelined=pipelined)
     R = S.RAS(Ao, dims, parts, ov)
     for q in range(2):
         r = I.test_vector(20 + q, cfg.ncell)
