@@ -239,22 +239,42 @@ __global__ __launch_bounds__(BS) void k_factors_to_rows(Geo g, const double *__r
 
 // ---------------------------------------------------------------- pipelined tile-lane sweeps
 //
-// One workgroup per tile at a time: wave 0 computes, waves 1..NL stream the
-// tile's per-step data into a ring of D slots in LDS (warp specialisation).
-// A wavefront can keep at most 63 memory operations outstanding and retires
-// them in order, so one wave alone cannot hide HBM latency for the ~30 loads
-// each step needs; each loader wave owns every NL-th step and brings its own
-// outstanding-load budget.  The compute wave leaves each step's results in
-// the step's slot; the loader that refills the slot D steps later first
-// stores them to HBM.  A wave's memory instructions queue behind the loads
-// of the CU's other waves, so every store the compute wave issued itself
-// would hold up its chain of steps (measured: 25 % of the sweep time on
-// tiles without neighbours); it stores only the face rows.
+// One workgroup of nine waves per tile at a time.  Step t of a tile: lane (i, j)
+// handles cell k = t - (i+j) (forward) or k = nz-1-(t-(14-i-j)) (backward), so
+// the 64 cells of a step lie on one hyperplane; the cell's data sit in row (t
+// mod nz) (forward) or ((nz+13-t) mod nz) (backward) of the tile.
 //
-// Step t of a tile: lane (i,j) of the compute wave handles cell k = t - (i+j)
-// (forward) or k = nz-1-(t-(14-i-j)) (backward); the cell's data sit in row
-// (t mod nz) (forward) or ((nz+13-t) mod nz) (backward) of the tile, so every
-// load is one coalesced 64-lane row.
+// What bounds a sweep of a small or medium grid is the length of a step, since
+// the steps of a tile, and of the tiles behind it, follow one another.  A step
+// done by one wave is that wave's instruction issue (27 multiply-adds, 30 or 39
+// operand reads, addresses, tags, faces: 1070 cycles forward, 1450 backward), so
+// it is cut up: waves 0 to 3 update 16 cells each, one component of a cell per
+// lane in groups of four lanes (9 multiply-adds; the backward sweep exchanges the
+// three inside the group before the product with D^-1), waves 4 to 6 bring in
+// operands, wave 7 the next step's faces, and wave 8 hands on the previous step's
+// and stores its results.  One workgroup barrier per step orders them; there are
+// no tags inside the workgroup.
+//
+// Operands and faces go from memory to LDS without passing through registers:
+// the loading waves copy a step's rows with 16-byte LDS loads (1 KiB per
+// instruction) into a ring of D slots, D steps ahead, and wait for a step's
+// copies by the count of loads issued since.  The updating waves read a step's
+// operands during the step before and keep their own last values in registers:
+// between two barriers lie two reads, of one component of the x and y neighbours
+// (the lanes of a group exchange them), and six multiply-adds.  The components of
+// a cell are three rows apart, in the same banks; so the copies turn row r by
+// (r mod 4) times eight cells.  Tiles follow one another in the ring without a
+// gap.  A tile has one empty step at its end, in which the last results leave
+// before wave 7 waits for the next tile's first faces.
+//
+// Against one updating wave fed by 7 (3) register-loading waves, forward/backward
+// in us: 8 x 8 x 2048 cells FP64 912/1241 -> 607/694 (0.29/0.33 per step, bound by
+// the reads and copies of LDS and the barrier), 64 x 64 x 256 231/301 -> 173/204,
+// 128 x 128 x 64 236/283 -> 183/209, 20 x 20 x 10 40/48 -> 34/38; FP32 785/861 ->
+// 530/580, 177/192 -> 150/159, 177/192 -> 167/175, 33/35 -> 32/34.  Between tiles a
+// hop costs eight steps and about 2 us, from the store of a face to its arrival;
+// loading faces 4 or 8 steps ahead instead of 2 makes that longer (128 x 128 x 64
+// forward 199 and 237).
 //
 // Face exchange between neighbouring tiles: face row s of a tile holds the
 // eight boundary values (three components each) that the neighbouring tile
@@ -265,16 +285,12 @@ __global__ __launch_bounds__(BS) void k_factors_to_rows(Geo g, const double *__r
 // no fences between tiles, no clearing between calls (the buffers are cleared
 // once, when allocated: memory another object wrote, possibly under another
 // context's epochs, could otherwise hold a word with a matching tag).  Word (p*W + h)*8 + e
-// of a row holds half h of component p of entry e.  The compute wave writes
-// a whole face row with one store instruction (for the same reason, the
-// number of store instructions, not their width, sets their cost): lane q
-// takes word q of the row from the results in LDS, where the boundary lane
-// has just put them.  The loader of step t
-// reads the row (one word per lane), waits until every needed word carries
-// the epoch, and writes the values into the slot.  Tiles are handed out by an
-// atomic ticket in topological order, so a tile only waits on tiles held by
-// running workgroups; every wait is bounded by a wall-clock limit that raises
-// an error flag and makes all other waits give up at once.
+// of a row holds half h of component p of entry e.  A row is loaded SW_FACE
+// steps before it is needed and, if it was not there yet, loaded again with those
+// behind it until it is.  Tiles are
+// handed out by an atomic ticket in topological order, so a tile only waits on
+// tiles held by running workgroups; every wait is bounded by a wall-clock limit
+// that raises an error flag and makes all other waits give up.
 
 template <typename T> struct FaceW;
 template <> struct FaceW<double> { static constexpr int W = 2; };
@@ -290,7 +306,6 @@ struct SweepArgs {
     uint32_t epoch;
     int32_t *flags;
     uint64_t wait_limit;         // wall-clock ticks a wait may last
-    int D;                       // LDS ring slots
     int btx, bty;                // tiles per box in x and y: faces are exchanged only between
                                  // tiles of one box (the whole grid is one box for BILU0)
     uint64_t *trace;             // optional: per tile [start, step 8 reached, end, steps that waited for data]
@@ -307,435 +322,459 @@ struct SweepSrc {
                                                   // the output has this grid's layout
 };
 
-// NLOAD loader waves per workgroup (each keeps two steps in flight)
-template <int DIR, typename T, int NLOAD>
-__global__ __launch_bounds__(64 * (1 + NLOAD)) void k_sweep(SweepArgs a, SweepSrc<T> src, T *__restrict__ yout,
-                                                           double *__restrict__ zout)
+constexpr int SW_FACE = 2;       // steps a face row is loaded ahead
+constexpr int SW_MAXD = 10;      // ring slots at most: the next tile is claimed D + 5 steps before a tile's end
+constexpr int SW_LDS = 160 * 1024;
+constexpr int SW_THREADS = 64 * 9;
+
+// One step's operands in LDS: factor blocks (27 rows of 64), D^-1 (backward, 9),
+// the right-hand side (3; FP64 forward), each as it lies in memory.
+template <int DIR, typename T> struct SweepCfg {
+    static constexpr int W = FaceW<T>::W, RW = 24 * W;
+    static constexpr int ROWB = 64 * (int)sizeof(T);
+    static constexpr int FB = 27 * ROWB, DB = DIR == 0 ? 0 : 9 * ROWB;
+    static constexpr int VB = DIR == 0 ? 192 * 8 : 3 * ROWB;
+    static constexpr int NF = (FB + 1023) / 1024, ND = (DB + 1023) / 1024, NV = (VB + 1023) / 1024;
+    static constexpr int SLOT = FB + DB + VB;
+    static constexpr int NCH = NF + ND + NV;                 // 1 KiB copies per step
+    static constexpr int per(int w) { return (NCH - w + 2) / 3; }   // of loading wave w: w, w + 3, ...
+    static constexpr int BUF = 3 * 80 * (int)sizeof(T);      // results [3][64] and faces [3][8 + 8] of one step
+    static constexpr int ZB = DIR == 0 ? 0 : 2 * SW_FACE * 256;   // backward: output map entries of 2 SW_FACE steps
+    static constexpr int FIXED = 2 * BUF + ZB + SW_FACE * 1024 + 16;
+    // slots: what fits one workgroup, and no more loads in flight per wave than its counter holds
+    static constexpr int dmin(int x, int y) { return x < y ? x : y; }
+    static constexpr int D = dmin(SW_MAXD, dmin((SW_LDS - FIXED) / SLOT, 63 / per(0)));
+    static constexpr int BYTES = D * SLOT + FIXED;
+    static_assert(D >= 3 && D <= SW_MAXD && SW_FACE >= 2, "a tile has at least 16 steps: it is claimed D + 5 before the end");
+};
+
+// 16 (or 4) bytes per lane from src + voff to LDS address dst + 16 (4) lane (both
+// + AT, below 4096); src uniform.  The compiler does not count these loads: the
+// waits are explicit.
+template <int AT> __device__ __forceinline__ void lds_copy(uint32_t voff, const void *src, uint32_t dst)
 {
-    constexpr int W = FaceW<T>::W;
-    constexpr int RW = 24 * W;                   // face words per row
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+                 :
+                 : "v"(voff), "s"(src), "s"(dst), "n"(AT)
+                 : "memory");
+}
+// the same past the caches that other dies do not see, as the face words need it
+__device__ __forceinline__ void lds_copy_face(const void *p, uint32_t dst)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc1" ::"v"(p), "s"(dst) : "memory");
+}
+__device__ __forceinline__ void lds_copy4(const void *p, uint32_t dst)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(p), "s"(dst) : "memory");
+}
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// A loading wave's share of one step's copies: chunks c, c + 3, ... of the slot at
+// LDS address dst.  f, d, v: the step's rows; vt, v8: the lanes' offsets within
+// even and odd KiB of T and of FP64 rows.
+template <int DIR, typename T, int c>
+__device__ __forceinline__ void sweep_copy(const char *f, const char *d, const char *v, const uint32_t (&vt)[2],
+                                           const uint32_t (&v8)[2], uint32_t dst, int L)
+{
+    using C = SweepCfg<DIR, T>;
+    if constexpr (c < C::NCH) {
+        constexpr bool isf = c < C::NF, isd = !isf && c < C::NF + C::ND;
+        constexpr int q = isf ? c : isd ? c - C::NF : c - C::NF - C::ND;          // KiB within its rows
+        constexpr int len = (isf ? C::FB : isd ? C::DB : C::VB) - 1024 * q;
+        constexpr int at = isf ? 0 : isd ? C::FB : C::FB + C::DB;
+        constexpr int big = q / 4 * 4096, imm = q % 4 * 1024;
+        const char *src = (isf ? f : isd ? d : v) + big;
+        const uint32_t vo = (DIR == 0 && !isf) ? v8[q & 1] : vt[q & 1];
+        if (len >= 1024 || L < len / 16) lds_copy<imm>(vo, src, dst + at + big);
+        sweep_copy<DIR, T, c + 3>(f, d, v, vt, v8, dst, L);
+    }
+}
+
+// lane Q's value in every group of four lanes
+template <int Q> __device__ __forceinline__ float quad_get(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xf, 0xf, true));
+}
+template <int Q> __device__ __forceinline__ double quad_get(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), Q * 0x55, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), Q * 0x55, 0xf, 0xf, true));
+}
+
+template <int DIR, typename T>
+__global__ __launch_bounds__(SW_THREADS) void k_sweep(SweepArgs a, SweepSrc<T> src, T *__restrict__ yout,
+                                               double *__restrict__ zout)
+{
+    using C = SweepCfg<DIR, T>;
+    constexpr int W = C::W, RW = C::RW;
     extern __shared__ __align__(16) unsigned char smem[];
     const Geo &g = a.g;
-    const int nz = g.nz, NT = g.ntx * g.nty, nsteps = nz + 14;
-    const int D = a.D;
-    constexpr int NE = DIR == 0 ? 30 : 39;       // T entries per lane per step (27 blocks [+9 D^-1] + 3 vector)
-    constexpr int NS = DIR == 0 ? NE : NE + 1;   // + the output map entry (bwd)
-    constexpr int RES = NS * 64 + 48;            // + x and y faces (8 entries x 3 components each)
-    constexpr int slot_elems = RES + 192;        // + the step's results ([64 lanes][3])
-    T *ring = (T *)smem;
-    int32_t *tags = (int32_t *)(smem + (size_t)D * slot_elems * sizeof(T));
-    int32_t *consumed = tags + D;
-    int32_t *tile_ring = consumed + 1;   // tile of the workgroup's k-th tile in entry k mod 4
-    int32_t *tile_tag = tile_ring + 4;   // k + 1 once entry k mod 4 holds the k-th tile
-    int32_t *ftags = tile_tag + 4;       // per slot: step whose face values are in the slot (+1)
-    const int wave = threadIdx.x >> 6, L = threadIdx.x & 63;
-    int li, lj;
-    lane_ij(L, li, lj);
+    const int nz = g.nz, NT = g.ntx * g.nty, nsteps = nz + 14, nst = nsteps + 1;
+    constexpr int D = C::D;
+    unsigned char *buf = smem + (size_t)D * C::SLOT;        // [parity][3][80]: 64 results, x face, y face
+    int32_t *zb = (int32_t *)(buf + 2 * C::BUF);            // backward: [step % (2 SW_FACE)][64]
+    unsigned char *fcb = (unsigned char *)zb + C::ZB;       // [step % SW_FACE]: x row, y row (512 bytes apart)
+    int32_t *next = (int32_t *)(fcb + SW_FACE * 1024);
+    auto lds_of = [](const void *p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p; };
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), L = threadIdx.x & 63;
     const int64_t frow = (int64_t)(nz + 7) * RW;
-    // Tiles come from an atomic ticket (-1 past the last tile).  The k-th tile
-    // of this workgroup is published by the first loader wave when it has
-    // issued its last step of tile k - 1 (so tiles are still claimed close to
-    // when a workgroup can take them up), and the loaders stream the next
-    // tile's first steps while the compute wave finishes the current one;
-    // there is no barrier between tiles.  Four entries: an entry is rewritten only after
-    // every wave has read it (no wave is more than one tile behind another,
-    // since the loaders run at most D < nsteps steps ahead of the compute wave).
-    auto take = [&]() -> int32_t {
-        const uint64_t tk = atomicAdd((unsigned long long *)a.ticket, 1ull) - a.ticket_base;
-        return (tk >= (uint64_t)NT) ? -1 : a.tile_order[DIR == 0 ? (int)tk : NT - 1 - (int)tk];
+    auto take = [&]() -> uint64_t { return atomicAdd((unsigned long long *)a.ticket, 1ull) - a.ticket_base; };
+    auto tile_of = [&](uint64_t tk) -> int32_t {
+        return tk >= (uint64_t)NT ? -1 : a.tile_order[DIR == 0 ? (int)tk : NT - 1 - (int)tk];
     };
-    auto publish = [&](int k) {
-        const int32_t id = take();
-        __hip_atomic_store(&tile_ring[k & 3], id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __hip_atomic_store(&tile_tag[k & 3], k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    if (threadIdx.x == 0) *consumed = 0;
-    for (int s = threadIdx.x; s < D; s += blockDim.x) tags[s] = ftags[s] = 0;
-    if (threadIdx.x < 4) tile_tag[threadIdx.x] = 0;
+    for (int e = threadIdx.x; e < 2 * C::BUF / 4; e += SW_THREADS) ((uint32_t *)buf)[e] = 0;
+    if (threadIdx.x == 448) *next = tile_of(take());
     __syncthreads();
-    if (threadIdx.x == 0) publish(0);
-    __syncthreads();
-    int gstep = 0;   // running step count across tiles (tags are gstep + 1)
-    int prevT = -1;  // the workgroup's previous tile
-    bool aborted = false;
-    // Loader part: the results of global step Gs (tile Ts, local step ts),
-    // which the compute wave left in slot sl, go to HBM (lanes whose cell is
-    // in range).  The loader that refills a slot does this first, so the
-    // compute wave issues no stores of its own besides the face rows.
-    auto store_results = [&](const T *sl, int Ts, int ts) {
-        const int kk = DIR == 0 ? ts - (li + lj) : ts - (14 - li - lj);
-        if (Ts < 0 || kk < 0 || kk >= nz) return;
-        const T *res = sl + RES + L * 3;
-        const int row = DIR == 0 ? wrap_nz(ts, nz) : wrap_nz(nz + 13 - ts, nz);
-        const int64_t rb = (int64_t)Ts * nz + row;
-        if constexpr (DIR == 0) {
-            T *yp = yout + rb * 192 + L;
+    int T_ = __builtin_amdgcn_readfirstlane(*next);
+    if (T_ < 0) return;
+    int gs = 0;      // steps so far, of all tiles
+    if (wave < 4) {
+        // ------------------------------------------------ updating waves
+        const int cell = 16 * wave + (L >> 2), cp = min(L & 3, 2);   // the fourth lane repeats the third
+        int li, lj;
+        lane_ij(cell, li, lj);
+        const int dd = DIR == 0 ? li + lj : 14 - li - lj;   // step at which the lane's column starts
+        const int ax = DIR == 0 ? (li > 0 ? ij_lane(li - 1, lj) : 64 + lj) : (li < 7 ? ij_lane(li + 1, lj) : 64 + lj);
+        const int ay = DIR == 0 ? (lj > 0 ? ij_lane(li, lj - 1) : 72 + li) : (lj < 7 ? ij_lane(li, lj + 1) : 72 + li);
+        // row 3 cp + k of a slot's factors lies at r4[k & 3] + k ROWB, turned by eight cells times its number mod 4
+        constexpr int E = sizeof(T), EV = DIR == 0 ? 8 : E;
+        int r4[4];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) __builtin_nontemporal_store(res[p], yp + p * 64);
-        } else {
-            int64_t o = rb * 192 + L;
-            if (src.zmap) {
-                const int32_t zm = ((const int32_t *)(sl + NE * 64))[L];
-                if (zm < 0) return;
-                o = ((int64_t)zm >> 6) * 192 + (zm & 63);
+        for (int k = 0; k < 4; ++k) r4[k] = 3 * cp * C::ROWB + ((cell + 8 * ((3 * cp + k) & 3)) & 63) * E;
+        const int rv = C::FB + C::DB + (cp * 64 + ((cell + 8 * cp) & 63)) * EV;
+        struct Ops {
+            T f[9], d[3], r;
+        } A, B;
+        int slot = 0, t = 0;
+        T own = 0;      // this lane's value of the step before
+        auto operands = [&](Ops &o) {
+            const unsigned char *sl = smem + (size_t)slot * C::SLOT;
+            auto row = [&](int at, int k) { return *(const T *)(sl + r4[k & 3] + at + k * C::ROWB); };
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) o.f[3 * s + q] = row(0, 9 * s + q);
+            if constexpr (DIR == 0) {
+                o.r = (T)*(const double *)(sl + rv);
+            } else {
+                o.r = *(const T *)(sl + rv);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) o.d[q] = row(C::FB, q);
             }
-#pragma unroll
-            for (int p = 0; p < 3; ++p) __builtin_nontemporal_store((double)res[p], zout + o + p * 64);
-        }
-    };
-    for (int k = 0;; ++k) {
-        if (__hip_atomic_load(&tile_tag[k & 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != k + 1) {
-            const uint64_t t0 = wall_clock64();
-            uint32_t n = 0;
-            bool gave_up = false;
-            while (__hip_atomic_load(&tile_tag[k & 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != k + 1) {
-                if (spin_guard(a.flags, t0, n, a.wait_limit)) {
-                    gave_up = true;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
+            slot = slot + 1 == D ? 0 : slot + 1;
+        };
+        // one step with operands o, reading the next one's; false after the last tile
+        auto step = [&](const Ops &o, Ops &n, int par) {
+            const T *rp = (const T *)(buf + (par ^ 1) * C::BUF);   // last step's results, this step's faces
+            const T vx = rp[cp * 80 + ax], vy = rp[cp * 80 + ay];
+            asm volatile("" ::: "memory");   // these first: reads return in order
+            operands(n);
+            asm volatile("" ::: "memory");
+            const bool act = (unsigned)(t - dd) < (unsigned)nz;
+            bool more = true;
+            if (++t == nst) {
+                t = 0;
+                more = __builtin_amdgcn_readfirstlane(*next) >= 0;
             }
-            if (gave_up) {   // the error flag is set; every wave leaves
-                aborted = true;
-                break;
+            auto block = [&](T acc, int s, T v) {
+                acc = fma_t(-o.f[3 * s], quad_get<0>(v), acc);
+                acc = fma_t(-o.f[3 * s + 1], quad_get<1>(v), acc);
+                return fma_t(-o.f[3 * s + 2], quad_get<2>(v), acc);
+            };
+            if constexpr (DIR == 0) {
+                own = block(block(block(o.r, 0, own), 1, vy), 2, vx);
+            } else {
+                own = block(block(block(o.r, 0, vx), 1, vy), 2, own);
+                own = fma_t(o.d[2], quad_get<2>(own), fma_t(o.d[1], quad_get<1>(own), o.d[0] * quad_get<0>(own)));
             }
-        }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const int T_ = __hip_atomic_load(&tile_ring[k & 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (T_ < 0) break;
-        const int tx = T_ % g.ntx, ty = T_ / g.ntx;
-        const int64_t rowbase = (int64_t)T_ * nz;
-        const int bx = tx % a.btx, by = ty % a.bty;   // tile position inside its box
-        const bool hasx = DIR == 0 ? bx > 0 : bx < a.btx - 1;
-        const bool hasy = DIR == 0 ? by > 0 : by < a.bty - 1;
-        if (wave > 0) {
-            // ------------------------------------------------ loader waves
-            const uint64_t *xin = a.faceX + (int64_t)(DIR == 0 ? T_ - 1 : T_ + 1) * frow;
-            const uint64_t *yin = a.faceY + (int64_t)(DIR == 0 ? T_ - g.ntx : T_ + g.ntx) * frow;
-            const int eq = L & 7;                    // face entry of this lane's word
-            const int fdst = (eq * 3 + (L >> 3) / W) * W + (L >> 3) % W;   // its 32-bit half in the slot's [8][3] values
-            constexpr int nv = DIR == 0 ? 27 : 36;
-            struct Regs {
-                T v[nv + 3];
-                int32_t zm;        // output map entry (bwd with a map)
-                uint64_t wx, wy;   // face words of the same step
-            };
-            // face words: always two loads per lane (a tile without that neighbour
-            // reads its own face buffer, an in-range dummy); validity is decided later
-            const uint64_t *xsrc = hasx ? xin : a.faceX + (int64_t)T_ * frow;
-            const uint64_t *ysrc = hasy ? yin : a.faceY + (int64_t)T_ * frow;
-            const int lq = L < RW ? L : RW - 1;
-            // loads are issued unconditionally (out-of-range steps re-read a valid
-            // row) so that the outstanding-load count is static and the compiler
-            // can wait for exactly the buffer it needs
-            // Lanes are ordered by anti-diagonal, so the lanes whose cell is in range
-            // at step t are one contiguous range [lo, hi]; an out-of-range lane reads
-            // the slot of the nearest in-range lane instead of its own, so a step
-            // touches only the cache lines its in-range lanes need (the wrapped
-            // layout would otherwise re-read rows at the start and end of a column).
-            auto issue_lane = [&](int tc) {
-                const int dmin = DIR == 0 ? (tc - nz + 1 > 0 ? tc - nz + 1 : 0) : (14 - tc > 0 ? 14 - tc : 0);
-                const int dmax = DIR == 0 ? (tc < 14 ? tc : 14) : (13 - tc + nz < 14 ? 13 - tc + nz : 14);
-                const int lo = lane_first(dmin), hi = lane_first(dmax + 1) - 1;
-                return L < lo ? lo : (L > hi ? hi : L);
-            };
-            // The factor blocks are read once per apply and the results written
-            // once: both bypass the caches' retention (nontemporal; measured
-            // 3-4 % faster sweeps on the 512x512x128 grid).
-            auto issue_data = [&](Regs &R, int t) {
-                const int tc = t < nsteps ? t : nsteps - 1;
-                const int row = DIR == 0 ? wrap_nz(tc, nz) : wrap_nz(nz + 13 - tc, nz);
-                const int64_t rb = rowbase + row;
-                const int Ls = issue_lane(tc);
-                const T *q0 = src.p0 + rb * src.s0 + src.o0 + Ls;
-#pragma unroll
-                for (int e = 0; e < 27; ++e) R.v[e] = __builtin_nontemporal_load(q0 + e * 64);
-                if constexpr (DIR == 1) {
-                    const T *q1 = src.p1 + rb * src.s1 + src.o1 + Ls;
-#pragma unroll
-                    for (int e = 0; e < 9; ++e) R.v[27 + e] = __builtin_nontemporal_load(q1 + e * 64);
-                }
-                if constexpr (DIR == 0) {
-                    const double *q2 = src.v64 + rb * 192 + Ls;
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) R.v[nv + p] = (T)q2[p * 64];
-                } else {
-                    const T *q2 = src.vT + rb * 192 + Ls;
-#pragma unroll
-                    for (int p = 0; p < 3; ++p) R.v[nv + p] = q2[p * 64];
-                    R.zm = src.zmap ? src.zmap[rb * 64 + Ls] : -1;
-                }
-                // face words of the same step, issued with its data (they may still
-                // be stale when the step is delivered; then they are polled again)
-                const int tr = t < nz + 7 ? t : nz + 6;
-                R.wx = face_ld(xsrc + (int64_t)tr * RW + lq);
-                R.wy = face_ld(ysrc + (int64_t)tr * RW + lq);
-            };
-            // face words of step t (entries whose cell exists)
-            auto face_need = [&](int t) {
-                const int kk = DIR == 0 ? t - eq : t - 7 + eq;
-                return L < RW && kk >= 0 && kk < nz;
-            };
-            auto finish = [&](const Regs &R, int t) {
-                uint64_t wx = R.wx, wy = R.wy;
-                const int G = gstep + t;
-                const int slot = G % D;
-                T *sl = ring + (size_t)slot * slot_elems;
-                // wait for the compute wave to release this slot (step G - D)
-                if (__hip_atomic_load(consumed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < G - D + 1) {
-                    const uint64_t t0 = wall_clock64();
-                    uint32_t n = 0;
-                    while (__hip_atomic_load(consumed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < G - D + 1) {
-                        if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
-                        __builtin_amdgcn_s_sleep(1);
-                    }
-                }
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                // the slot still holds the results of step G - D (this tile's or the previous one's)
-                if (G >= D) {
-                    const int Gs = G - D;
-                    const bool cur = Gs >= gstep;
-                    store_results(sl, cur ? T_ : prevT, cur ? Gs - gstep : Gs - gstep + nsteps);
-                }
-#pragma unroll
-                for (int e = 0; e < nv + 3; ++e) sl[e * 64 + L] = R.v[e];
-                if constexpr (DIR == 1) ((int32_t *)(sl + NE * 64))[L] = R.zm;
-                // operands first (the compute wave prefetches them while faces are pending)
-                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                __hip_atomic_store(&tags[slot], G + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                const bool need = face_need(t);
-                const bool okx = !hasx || !need || (uint32_t)(wx >> 32) == a.epoch;
-                const bool oky = !hasy || !need || (uint32_t)(wy >> 32) == a.epoch;
-                if (!(okx && oky)) {
-                    // Slow path.  Seven loaders: every loader polls its own
-                    // step's rows at a short fixed interval, so consecutive
-                    // steps are not serialised on each other's poll round trips.
-                    // Backward FP64 sweep (three loaders): rows become valid in
-                    // step order, so first wait (in LDS) until the previous step
-                    // has been delivered; then only the loader of the oldest
-                    // pending step polls device memory, with exponential backoff
-                    // up to four 512-cycle sleeps.  (Measured: the first is
-                    // faster forward, the second backward; a cap of 16 sleeps
-                    // made the backward sweep at 128x128x64 4 % slower.)
-                    const uint64_t t0 = wall_clock64();
-                    uint32_t n = 0;
-                    constexpr bool serial = NLOAD < 7;
-                    if (serial && t > 0)
-                        while (__hip_atomic_load(&ftags[(G - 1) % D], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < G) {
-                            if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
-                            __builtin_amdgcn_s_sleep(2);
-                        }
-                    int backoff = 1;
-                    for (;;) {
-                        if (hasx) wx = face_ld(xin + (int64_t)t * RW + lq);
-                        if (hasy) wy = face_ld(yin + (int64_t)t * RW + lq);
-                        const bool ok = (!hasx || !need || (uint32_t)(wx >> 32) == a.epoch) &&
-                                        (!hasy || !need || (uint32_t)(wy >> 32) == a.epoch);
-                        if (__ballot(!ok) == 0ull) break;
-                        if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
-                        if (!serial) {
-                            __builtin_amdgcn_s_sleep(2);
-                        } else {
-                            for (int q = 0; q < backoff; ++q) __builtin_amdgcn_s_sleep(8);
-                            backoff = backoff < 4 ? 2 * backoff : 4;
-                        }
-                    }
-                }
-                // the low 32 bits of word q are 32-bit half q of the row's values
-                // (zero when the tile has no such neighbour: the value of an absent cell)
-                uint32_t *fs = (uint32_t *)(sl + NS * 64);
-                if (L < RW) {
-                    fs[fdst] = hasx ? (uint32_t)wx : 0u;
-                    fs[RW + fdst] = hasy ? (uint32_t)wy : 0u;
-                }
-                // the face writes complete before the face tag is published
-                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                __hip_atomic_store(&ftags[slot], G + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            };
-            // two steps in flight per loader: the next step's loads are issued
-            // before the current one is delivered
-            Regs A, B;
-            int t = wave - 1;
-            issue_data(A, t);
-            for (; t < nsteps; t += 2 * NLOAD) {
-                issue_data(B, t + NLOAD);
-                finish(A, t);
-                if (t + NLOAD >= nsteps) break;
-                issue_data(A, t + 2 * NLOAD);
-                finish(B, t + NLOAD);
-            }
-            if (wave == 1 && L == 0) publish(k + 1);
-        } else {
-            // ------------------------------------------------ compute wave
-            const int d = li + lj;
-            const int e_ = 14 - d;
-            const int lx = DIR == 0 ? (li > 0 ? ij_lane(li - 1, lj) : L) : (li < 7 ? ij_lane(li + 1, lj) : L);
-            const int ly = DIR == 0 ? (lj > 0 ? ij_lane(li, lj - 1) : L) : (lj < 7 ? ij_lane(li, lj + 1) : L);
-            const bool cx = DIR == 0 ? li == 0 : li == 7, cy = DIR == 0 ? lj == 0 : lj == 7;
-            // packed face stores: lane q < RW owns word q of each outgoing face
-            // row, half h = (q >> 3) % W of component (q >> 3) / W of entry
-            // e = q & 7, read from the result row of the boundary lane of
-            // entry e (x face: i = 7 forward, 0 backward, j = e; y face: i = e)
-            const int fe = L & 7, fp = (L >> 3) / W, fh = (L >> 3) % W;
-            const int fbx = DIR == 0 ? 7 : 0;
-            const int fx_src = ij_lane(fbx, fe) * 3 + fp;   // in the step's result rows
-            const int fy_src = ij_lane(fe, fbx) * 3 + fp;
-            const bool fxw = L < RW && (DIR == 0 ? bx < a.btx - 1 : bx > 0);
-            const bool fyw = L < RW && (DIR == 0 ? by < a.bty - 1 : by > 0);
-            // the boundary cell of entry e at step t is in range when (t - fk0) is in [0, nz)
-            const int fk0 = DIR == 0 ? 7 + fe : 14 - fe;
-            uint64_t *fxo = a.faceX + (int64_t)T_ * frow + L;
-            uint64_t *fyo = a.faceY + (int64_t)T_ * frow + L;
-            uint32_t waited = 0;
-            if (a.trace && L == 0) a.trace[4 * T_ + 0] = wall_clock64();
-            // Neighbour values come through LDS: every step the wave writes its
-            // three results into the result rows of the step's slot; at the next
-            // step an interior lane reads the row of its -x (+x) and -y (+y)
-            // neighbour lane there (the slot is released for new operands, but
-            // its result rows are rewritten only by this wave, D steps later),
-            // and a boundary lane reads the face entry the loader put in the
-            // step's slot.  One wave only, so its LDS accesses stay in program
-            // order.  At a tile's first step the previous slot holds another
-            // tile's results, but only the lane of the tile corner is in range
-            // then, and it takes both values from faces.
-            const uint32_t slot_bytes = (uint32_t)slot_elems * sizeof(T);
-            const uint32_t xo_int = (uint32_t)(RES + lx * 3) * sizeof(T);
-            const uint32_t yo_int = (uint32_t)(RES + ly * 3) * sizeof(T);
-            const uint32_t xo_face = (uint32_t)(NS * 64 + lj * 3) * sizeof(T);
-            const uint32_t yo_face = (uint32_t)(NS * 64 + 24 + li * 3) * sizeof(T);
-            T last[3] = {0, 0, 0};   // this lane's previous result: the -z (+z) neighbour value
-            // spin until the loaders have delivered step G into `slot` (tag G + 1);
-            // `seen` is a tag value already read
-            auto wait_slot = [&](int32_t *tg, int slot, int G, int seen) {
-                if (seen != G + 1) {
-                    ++waited;
-                    const uint64_t t0 = wall_clock64();
-                    uint32_t n = 0;
-                    while (__hip_atomic_load(&tg[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != G + 1) {
-                        if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
-                        __builtin_amdgcn_s_sleep(0);
-                    }
-                }
-                // LDS only: the slot's data were written before the tag (see the loader)
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            };
-            auto load_ops = [&](T *nf, int slot) {
-                const T *sl = ring + (size_t)slot * slot_elems;
-#pragma unroll
-                for (int e = 0; e < NE; ++e) nf[e] = sl[e * 64 + L];
-            };
-            int slot = gstep % D;                                   // slot of the current step
-            // Step t with operands f (already in registers).  Order: neighbour
-            // reads and the next slot's tag; the cell update; result writes;
-            // release of this step's slot (its reads are consumed and its
-            // results written); the next step's operands into fn (they land
-            // while the face stores below are issued).
-            int fseen = 0;   // face tag of the current step's slot, read one step ahead
-            auto step = [&](const T *f, T *fn, int t) {
-                const int G = gstep + t;
-                const int nslot = slot + 1 == D ? 0 : slot + 1;
-                const int pslot = slot == 0 ? D - 1 : slot - 1;   // the previous step's slot
-                wait_slot(ftags, slot, G, fseen);   // the boundary lanes read this step's faces
-                const T *bx = (const T *)(smem + (cx ? (uint32_t)slot * slot_bytes + xo_face : (uint32_t)pslot * slot_bytes + xo_int));
-                const T *by = (const T *)(smem + (cy ? (uint32_t)slot * slot_bytes + yo_face : (uint32_t)pslot * slot_bytes + yo_int));
-                T vx[3], vy[3];
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    vx[p] = bx[p];
-                    vy[p] = by[p];
-                }
-                const bool more = t + 1 < nsteps;
-                const int seen = more ? __hip_atomic_load(&tags[nslot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
-                const int kk = DIR == 0 ? t - d : t - e_;
-                const bool act = kk >= 0 && kk < nz;
-                T out[3];
-                if (DIR == 0) fwd_cell(f, last, vy, vx, f + 27, out);
-                else bwd_cell(f, f + 27, vx, vy, last, f + 36, out);
-                T *res = ring + (size_t)slot * slot_elems + RES;
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    out[p] = act ? out[p] : (T)0;
-                    res[L * 3 + p] = out[p];
-                    last[p] = out[p];
-                }
-                // this step's outgoing face words, from the result rows just written
-                // (one wave: its LDS accesses complete in program order)
-                const uint32_t fxv = half_bits(res[fx_src], fh);
-                const uint32_t fyv = half_bits(res[fy_src], fh);
-                // every read of this step's slot has been consumed and its results
-                // written (the loader that refills the slot stores them): hand it back
-                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                if (L == 0) __hip_atomic_store(consumed, G + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                if (more) {
-                    wait_slot(tags, nslot, G + 1, seen);
-                    load_ops(fn, nslot);
-                    fseen = __hip_atomic_load(&ftags[nslot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
-                // this step's face rows (row t - 7): the neighbouring tiles wait for them
-                if ((unsigned)(t - fk0) < (unsigned)nz) {
-                    const uint64_t ep = (uint64_t)a.epoch << 32;
-                    if (fxw) face_st(fxo + (int64_t)(t - 7) * RW, ep | fxv);
-                    if (fyw) face_st(fyo + (int64_t)(t - 7) * RW, ep | fyv);
-                }
-                slot = nslot;
-            };
-            T fa[NE], fb[NE];
-            wait_slot(tags, slot, gstep, __hip_atomic_load(&tags[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            load_ops(fa, slot);
-            fseen = __hip_atomic_load(&ftags[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            for (int t = 0; t < nsteps; t += 2) {
-                if (a.trace && L == 0 && t == 8) a.trace[4 * T_ + 1] = wall_clock64();
-                step(fa, fb, t);
-                if (t + 1 >= nsteps) break;
-                step(fb, fa, t + 1);
-            }
-            if (a.trace && L == 0) {
-                a.trace[4 * T_ + 2] = wall_clock64();
-                a.trace[4 * T_ + 3] = waited;
-            }
-        }
-        gstep += nsteps;
-        prevT = T_;
+            own = act ? own : (T)0;
+            if ((L & 3) < 3) ((T *)(buf + par * C::BUF))[cp * 80 + cell] = own;
+            lds_barrier();
+            return more;
+        };
+        lds_barrier();
+        operands(A);
+        lds_barrier();
+        while (step(A, B, 0) && step(B, A, 1)) {}
+        return;
     }
-    // loaders: the results of the last D steps are still in the ring
-    if (wave > 0 && !aborted && prevT >= 0) {
-        const int G0 = gstep - nsteps;   // first step of the last tile
-        for (int G = gstep - D > G0 ? gstep - D : G0; G < gstep; ++G) {
-            if (G % NLOAD != wave - 1) continue;
-            if (__hip_atomic_load(consumed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < G + 1) {
+    if (wave < 7) {
+        // ------------------------------------------------ loading waves
+        // the next copies: step of the tile, its row's pointers, ring slot
+        int tl = 0, row = DIR == 0 ? 0 : 13 % nz, slot = 0;
+        const char *f, *d, *v;
+        constexpr int sv = DIR == 0 ? 192 * 8 : 3 * C::ROWB;
+        const int64_t sf = src.s0 * (int64_t)sizeof(T), sd = DIR == 0 ? 0 : src.s1 * (int64_t)sizeof(T);
+        // rows go up (down) and around
+        const int up = DIR == 0 ? 1 : -1, back = up * (1 - nz);
+        const int64_t uf = up * sf, ud = up * sd, bf = back * sf, bd = back * sd;
+        auto start = [&](int id) {
+            tl = 0;
+            row = DIR == 0 ? 0 : 13 % nz;
+            const int64_t rb = (int64_t)id * nz + row;
+            f = (const char *)(src.p0 + src.o0) + rb * sf;
+            d = DIR == 0 ? nullptr : (const char *)(src.p1 + src.o1) + rb * sd;
+            v = (DIR == 0 ? (const char *)src.v64 : (const char *)src.vT) + rb * sv;
+        };
+        auto next_row = [&]() {
+            const bool wrap = row == (DIR == 0 ? nz - 1 : 0);
+            row += wrap ? back : up;
+            f += wrap ? bf : uf;
+            if constexpr (DIR == 1) d += wrap ? bd : ud;
+            v += wrap ? back * sv : up * sv;
+        };
+        start(T_);
+        // a lane's offset in even (o = 0) or odd KiB of rows of E-byte entries, the cells held to [lo, hi]
+        auto lane_at = [&](auto e, int o, int lo, int hi) -> uint32_t {
+            constexpr int E = decltype(e)::value, CPR = 4 * E, LPC = 16 / E;   // 16-byte pieces per row, cells per piece
+            const int r = L / CPR, turn = (r + (E == 8 ? 2 * o : 0)) * (8 / LPC);
+            return (r * CPR + min(max((L - turn) & (CPR - 1), lo / LPC), hi / LPC)) * 16;
+        };
+        uint32_t vt0[2], v80[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            vt0[o] = lane_at(std::integral_constant<int, sizeof(T)>{}, o, 0, 63);
+            v80[o] = lane_at(std::integral_constant<int, 8>{}, o, 0, 63);
+        }
+        const uint32_t base = lds_of(smem);
+        // Out-of-range lanes of the first and last steps copy the nearest in-range
+        // lane's 16 bytes, so a step touches only the lines it needs (the wrapped
+        // layout would re-read the rows at both ends of a column).
+        auto copy = [&](auto w) {
+            const int tc = tl < nsteps ? tl : nsteps - 1;
+            uint32_t vt[2] = {vt0[0], vt0[1]}, v8[2] = {v80[0], v80[1]};
+            if (tc < 14 || tc >= nz) {
+                const int dlo = DIR == 0 ? max(tc - nz + 1, 0) : max(14 - tc, 0);
+                const int dhi = DIR == 0 ? min(tc, 14) : min(13 - tc + nz, 14);
+                const int lo = lane_first(dlo), hi = lane_first(dhi + 1) - 1;
+#pragma unroll
+                for (int o = 0; o < 2; ++o) {
+                    vt[o] = lane_at(std::integral_constant<int, sizeof(T)>{}, o, lo, hi);
+                    v8[o] = lane_at(std::integral_constant<int, 8>{}, o, lo, hi);
+                }
+            }
+            const uint32_t dst = base + (uint32_t)slot * C::SLOT;
+            sweep_copy<DIR, T, decltype(w)::value>(f, d, v, vt, v8, dst, L);
+            slot = slot + 1 == D ? 0 : slot + 1;
+            if (tl + 1 < nsteps) next_row();   // the empty step copies the last row again
+            ++tl;
+        };
+        auto run = [&](auto w) {
+            constexpr int left = C::per(decltype(w)::value) * (D - 2);   // loads of the last D - 2 steps
+            for (int q = 0; q < D; ++q) copy(w);       // D < nst: all of the first tile
+            wait_loads<left>();
+            lds_barrier();
+            lds_barrier();
+            for (;;) {
+                for (int t = 0; t < nst; ++t) {
+                    if (tl == nst) {
+                        // the next tile was published two steps ago
+                        const int nx = __builtin_amdgcn_readfirstlane(*next);
+                        if (nx >= 0) start(nx);
+                        else tl = nsteps;   // nothing follows: copy the last row again, to keep the count
+                    }
+                    copy(w);   // D steps ahead, into the slot whose operands the step before read
+                    wait_loads<left>();
+                    lds_barrier();
+                }
+                if (__builtin_amdgcn_readfirstlane(*next) < 0) break;
+            }
+            wait_loads<0>();   // no copy outlives the workgroup
+        };
+        if (wave == 4) run(std::integral_constant<int, 0>{});
+        else if (wave == 5) run(std::integral_constant<int, 1>{});
+        else run(std::integral_constant<int, 2>{});
+        return;
+    }
+    // ---------------------------------------------------- face and result waves
+    // lane q < RW holds word q of a face row: half (q >> 3) % W of component
+    // (q >> 3) / W of entry e = q & 7; outgoing words come from the boundary
+    // lane of entry e (x face: i = 7 forward, 0 backward, j = e; y face: i = e)
+    const int fe = L & 7, fp = (L >> 3) / W, fh = (L >> 3) % W;
+    struct Tile {
+        int id;
+        bool ix, iy, ox, oy;             // faces come in from, go out to the x and y neighbour
+        int xs, ys;                      // tiles whose rows are read (its own where there is no neighbour: a dummy)
+    };
+    auto tile = [&](int id) {
+        Tile k;
+        k.id = id;
+        const int bx = (id % g.ntx) % a.btx, by = (id / g.ntx) % a.bty;
+        k.ix = DIR == 0 ? bx > 0 : bx < a.btx - 1;
+        k.iy = DIR == 0 ? by > 0 : by < a.bty - 1;
+        k.ox = DIR == 0 ? bx < a.btx - 1 : bx > 0;
+        k.oy = DIR == 0 ? by < a.bty - 1 : by > 0;
+        const int s = DIR == 0 ? -1 : 1;
+        k.xs = k.ix ? id + s : id;
+        k.ys = k.iy ? id + s * g.ntx : id;
+        return k;
+    };
+    Tile cur = tile(T_);
+    if (wave == 7) {
+        const int fk_in = DIR == 0 ? fe : 7 - fe;
+        const int xin = (fp * 80 + 64 + fe) * W + fh, yin = xin + 8 * W;        // 32-bit places in a buffer
+        // lanes 0 to RW/2 - 1 copy an x row, those from 32 on a y row, 16 bytes each
+        const bool copies = (L & 31) < RW / 2;
+        const uint64_t *fsrc = (L < 32 ? a.faceX : a.faceY) + 2 * (L & 31), *fptr = nullptr;
+        const int32_t *zp = nullptr;
+        const uint32_t fdst = lds_of(fcb), zdst = lds_of(zb);
+        Tile nxt = cur;                  // the tile after this step's
+        int ta = 0, ga = 0;              // step of the next prefetch, in its tile and in all
+        uint64_t tk = 0;
+        bool over = false;               // a wait gave up: the flag is set, no wait lasts any more
+        uint32_t waited = 0;
+        const bool mapped = DIR == 1 && src.zmap != nullptr, tracing = a.trace != nullptr;
+        int zrow = 0;
+        auto face_row = [&](const Tile &k) { return fsrc + (int64_t)(L < 32 ? k.xs : k.ys) * frow; };
+        auto start = [&](const Tile &k) {   // the prefetch goes to tile k
+            ta = 0;
+            fptr = face_row(k);
+            zrow = 13 % nz;
+            if (mapped) zp = src.zmap + ((int64_t)k.id * nz + zrow) * 64 + L;
+        };
+        auto fetch = [&]() {
+            if (copies) lds_copy_face(fptr, fdst + ga % SW_FACE * 1024);
+            if (ta < nz + 6) fptr += RW;      // rows end there; the steps behind need none
+            if (mapped) {
+                lds_copy4(zp, zdst + ga % (2 * SW_FACE) * 256);
+                if (ta + 1 < nsteps) {
+                    zp += zrow == 0 ? (nz - 1) * 64 : -64;
+                    zrow = zrow == 0 ? nz - 1 : zrow - 1;
+                }
+            }
+            ++ta;
+            ++ga;
+        };
+        // the faces of a tile's step t (gt in all) into buffer b: zero where no neighbour or no cell
+        auto bring = [&](const Tile &k, int t, int gt, unsigned char *b) {
+            if (mapped) wait_loads<2 * (SW_FACE - 1)>();
+            else wait_loads<SW_FACE - 1>();
+            const bool need = L < RW && (unsigned)(t - fk_in) < (unsigned)nz;
+            const bool nx = need & k.ix, ny = need & k.iy;
+            const int Lc = L < RW ? L : RW - 1;
+            const uint64_t *xr = (const uint64_t *)(fcb + gt % SW_FACE * 1024) + Lc, *yr = xr + 64;
+            uint64_t x = *xr, y = *yr;
+            auto missing = [&]() {
+                return __ballot((nx & ((uint32_t)(x >> 32) != a.epoch)) | (ny & ((uint32_t)(y >> 32) != a.epoch))) != 0ull;
+            };
+            if (missing() && !over) {
+                ++waited;
                 const uint64_t t0 = wall_clock64();
                 uint32_t n = 0;
-                while (__hip_atomic_load(consumed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < G + 1) {
-                    if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
-                    __builtin_amdgcn_s_sleep(1);
+                do {
+                    if (spin_guard(a.flags, t0, n, a.wait_limit)) { over = true; break; }
+                    wait_loads<0>();
+                    for (int q = 0; q < SW_FACE && t + q < nz + 7; ++q)
+                        if (copies) lds_copy_face(face_row(k) + (t + q) * RW, fdst + (gt + q) % SW_FACE * 1024);
+                    wait_loads<0>();
+                    x = *xr;
+                    y = *yr;
+                } while (missing());
+            }
+            if (L < RW) {
+                ((uint32_t *)b)[xin] = nx ? (uint32_t)x : 0u;
+                ((uint32_t *)b)[yin] = ny ? (uint32_t)y : 0u;
+            }
+        };
+        start(cur);
+        for (int q = 0; q < SW_FACE; ++q) fetch();
+        bring(cur, 0, 0, buf + C::BUF);           // step 0 reads the odd buffer
+        lds_barrier();
+        lds_barrier();
+        if (a.trace && L == 0) a.trace[4 * cur.id + 0] = wall_clock64();
+        // the next tile is published this long before a tile's end: two steps before the first copies
+        // and a step before the first prefetch that need it
+        constexpr int early = D + 2 > SW_FACE + 1 ? D + 2 : SW_FACE + 1;
+        int t = 0;
+        bool done = false;
+        while (!done) {
+            fetch();      // step gs + SW_FACE, into the slot of step gs
+            if (t >= nst - early - 3) {   // near the tile's end: the next one
+                if (t == nst - early - 3 && L == 0) tk = take();
+                if (t == nst - early) {
+                    const int32_t id = __builtin_amdgcn_readfirstlane(L == 0 ? tile_of(tk) : 0);
+                    if (L == 0) *next = id;
+                    nxt.id = id;
+                    if (id >= 0) nxt = tile(id);
+                }
+                if (ta == nst && nxt.id >= 0) start(nxt);
+                if (t + 1 == nst) {
+                    if (tracing && L == 0) {
+                        a.trace[4 * cur.id + 2] = wall_clock64();
+                        a.trace[4 * cur.id + 3] = waited;
+                    }
+                    waited = 0;
+                    done = nxt.id < 0;
+                    cur = nxt;
+                    t = -1;
+                    if (tracing && L == 0 && !done) a.trace[4 * cur.id + 0] = wall_clock64();
                 }
             }
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            store_results(ring + (size_t)(G % D) * slot_elems, prevT, G - G0);
+            // the next step's faces
+            if (!done) bring(cur, t + 1, gs + 1, buf + (gs & 1) * C::BUF);
+            if (t == 8 && tracing && L == 0) a.trace[4 * cur.id + 1] = wall_clock64();
+            lds_barrier();
+            ++gs;
+            ++t;
+        }
+        wait_loads<0>();
+    } else {
+        int li, lj;
+        lane_ij(L, li, lj);
+        const int fb = DIR == 0 ? 7 : 0, fk_out = DIR == 0 ? 7 + fe : 14 - fe;
+        const int fpc = L < RW ? fp : 0;
+        const int xw = (fpc * 80 + ij_lane(fb, fe)) * W + fh, yw = (fpc * 80 + ij_lane(fe, fb)) * W + fh;
+        const int dd = DIR == 0 ? li + lj : 14 - li - lj;
+        const uint64_t ep = (uint64_t)a.epoch << 32;
+        lds_barrier();
+        lds_barrier();
+        for (;;) {
+            // where step t - 1's results and faces go
+            int row = DIR == 0 ? 0 : 13 % nz;
+            int64_t at = ((int64_t)cur.id * nz + row) * 192 + L;
+            uint64_t *fx = a.faceX + (int64_t)cur.id * frow - 7 * RW + L, *fy = a.faceY + (int64_t)cur.id * frow - 7 * RW + L;
+            lds_barrier();      // step 0 has nothing to hand on
+            ++gs;
+            for (int ts = 0; ts < nsteps; ++ts, ++gs) {
+                const unsigned char *b = buf + ((gs + 1) & 1) * C::BUF;
+                const T *res = (const T *)b + L;
+                const T o[3] = {res[0], res[80], res[160]};
+                const uint32_t wx = ((const uint32_t *)b)[xw], wy = ((const uint32_t *)b)[yw];
+                if (L < RW && (unsigned)(ts - fk_out) < (unsigned)nz) {
+                    if (cur.ox) face_st(fx, ep | wx);
+                    if (cur.oy) face_st(fy, ep | wy);
+                }
+                fx += RW;
+                fy += RW;
+                if ((unsigned)(ts - dd) < (unsigned)nz) {
+                    if constexpr (DIR == 0) {
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) __builtin_nontemporal_store(o[p], yout + at + p * 64);
+                    } else {
+                        int64_t to = at;
+                        bool st = true;
+                        if (src.zmap) {
+                            const int32_t zm = zb[(gs - 1) % (2 * SW_FACE) * 64 + L];
+                            to = ((int64_t)(zm >> 6)) * 192 + (zm & 63);
+                            st = zm >= 0;
+                        }
+                        if (st)
+#pragma unroll
+                            for (int p = 0; p < 3; ++p) __builtin_nontemporal_store((double)o[p], zout + to + p * 64);
+                    }
+                }
+                const bool wrap = DIR == 0 ? row + 1 == nz : row == 0;
+                const int m = DIR == 0 ? (wrap ? 1 - nz : 1) : (wrap ? nz - 1 : -1);
+                row += m;
+                at += (int64_t)m * 192;
+                lds_barrier();
+            }
+            const int id = __builtin_amdgcn_readfirstlane(*next);
+            if (id < 0) break;
+            cur = tile(id);
         }
     }
-}
-
-// loader waves: 7, except the FP64 backward sweep whose 39-entry double
-// buffers need the 512-register budget of a 4-wave workgroup
-template <int DIR, typename T> struct NLoad { static constexpr int v = (DIR == 1 && sizeof(T) == 8) ? 3 : 7; };
-
-template <typename T>
-inline size_t sweep_slot_bytes(int dir)
-{
-    const int NS = (dir == 0) ? 30 : 40;   // entries per lane (+ the bwd output map entry)
-    return (size_t)(NS * 64 + 48 + 192) * sizeof(T);   // + faces + the step's results
-}
-// dynamic LDS of a sweep: D ring slots and 64 tag words
-template <typename T>
-inline size_t sweep_lds_bytes(int dir, int D)
-{
-    return (size_t)D * sweep_slot_bytes<T>(dir) + 64 * sizeof(int32_t);
 }
 
 // zero n 64-bit words
@@ -850,10 +889,10 @@ struct Bilu0 : PcImpl {
             face_words = (int64_t)NT * (g.nz + 7) * 24 * W;
             const size_t fb = (size_t)face_words * sizeof(uint64_t);
             // the sweeps keep a multi-slot ring in LDS: allow the full LDS per workgroup
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<0, double, NLoad<0, double>::v>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<1, double, NLoad<1, double>::v>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<0, float, NLoad<0, float>::v>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<1, float, NLoad<1, float>::v>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
+            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<0, double>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
+            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<1, double>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
+            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
+            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
             s = alloc((void **)&faceX, fb);
             if (s == RSV_OK) s = alloc((void **)&faceY, fb);
             if (s == RSV_OK) s = alloc((void **)&tile_order, (size_t)NT * sizeof(int32_t));
@@ -956,41 +995,37 @@ struct Bilu0 : PcImpl {
         const int nw = nwaves();
         if (fp32) {
             SweepArgs a = sweep_args(nw);
-            a.D = (int)sweep_ring_depth(c, 0, 1);
             SweepSrc<float> s0{Lf32, (int64_t)27 * 64, 0, nullptr, 0, 0, r, nullptr, nullptr};
-            size_t sh = sweep_lds_bytes<float>(0, a.D);
+            size_t sh = SweepCfg<0, float>::BYTES;
             int t1 = prof_begin(c, RSV_K_ILU_FWD);
-            hipLaunchKernelGGL((k_sweep<0, float, NLoad<0, float>::v>), dim3(nw), dim3(64 * (1 + NLoad<0, float>::v)), sh, c->stream, a, s0,
+            hipLaunchKernelGGL((k_sweep<0, float>), dim3(nw), dim3(SW_THREADS), sh, c->stream, a, s0,
                                (float *)ybuf, (double *)nullptr);
             prof_end(c, t1);
             RSV_LAUNCH(c);
             SweepArgs b = sweep_args(nw);
-            b.D = (int)sweep_ring_depth(c, 1, 1);
             SweepSrc<float> s1{U32, (int64_t)27 * 64, 0, Dinv32, (int64_t)9 * 64, 0, nullptr, (const float *)ybuf, zmap};
-            sh = sweep_lds_bytes<float>(1, b.D);
+            sh = SweepCfg<1, float>::BYTES;
             int t2 = prof_begin(c, RSV_K_ILU_BWD);
-            hipLaunchKernelGGL((k_sweep<1, float, NLoad<1, float>::v>), dim3(nw), dim3(64 * (1 + NLoad<1, float>::v)), sh, c->stream, b, s1,
+            hipLaunchKernelGGL((k_sweep<1, float>), dim3(nw), dim3(SW_THREADS), sh, c->stream, b, s1,
                                (float *)nullptr, z);
             prof_end(c, t2);
             RSV_LAUNCH(c);
         } else {
             SweepArgs a = sweep_args(nw);
-            a.D = (int)sweep_ring_depth(c, 0, 0);
             SweepSrc<double> s0{Lf, (int64_t)27 * 64, 0, nullptr, 0, 0, r, nullptr, nullptr};
-            size_t sh = sweep_lds_bytes<double>(0, a.D);
+            size_t sh = SweepCfg<0, double>::BYTES;
             int t1 = prof_begin(c, RSV_K_ILU_FWD);
-            hipLaunchKernelGGL((k_sweep<0, double, NLoad<0, double>::v>), dim3(nw), dim3(64 * (1 + NLoad<0, double>::v)), sh, c->stream, a, s0,
+            hipLaunchKernelGGL((k_sweep<0, double>), dim3(nw), dim3(SW_THREADS), sh, c->stream, a, s0,
                                (double *)ybuf, (double *)nullptr);
             prof_end(c, t1);
             RSV_LAUNCH(c);
             dump_trace(0);
             SweepArgs b = sweep_args(nw);
-            b.D = (int)sweep_ring_depth(c, 1, 0);
             SweepSrc<double> s1{M->d_A, (int64_t)63 * 64, (int64_t)36 * 64, Dinv, (int64_t)9 * 64, 0, nullptr,
                                 (const double *)ybuf, zmap};
-            sh = sweep_lds_bytes<double>(1, b.D);
+            sh = SweepCfg<1, double>::BYTES;
             int t2 = prof_begin(c, RSV_K_ILU_BWD);
-            hipLaunchKernelGGL((k_sweep<1, double, NLoad<1, double>::v>), dim3(nw), dim3(64 * (1 + NLoad<1, double>::v)), sh, c->stream, b, s1,
+            hipLaunchKernelGGL((k_sweep<1, double>), dim3(nw), dim3(SW_THREADS), sh, c->stream, b, s1,
                                (double *)nullptr, z);
             prof_end(c, t2);
             RSV_LAUNCH(c);
@@ -1003,11 +1038,10 @@ struct Bilu0 : PcImpl {
 
 }  // namespace
 
-int64_t sweep_ring_depth(const rsv_ctx *c, int dir, int fp32)
+int64_t sweep_ring_depth(const rsv_ctx *, int dir, int fp32)
 {
-    const size_t cap = (size_t)c->lds_max - 64 * sizeof(int32_t);
-    const size_t sb = fp32 ? sweep_slot_bytes<float>(dir) : sweep_slot_bytes<double>(dir);
-    return (int64_t)std::max<size_t>(2, std::min<size_t>(12, cap / sb));
+    if (fp32) return dir == 0 ? SweepCfg<0, float>::D : SweepCfg<1, float>::D;
+    return dir == 0 ? SweepCfg<0, double>::D : SweepCfg<1, double>::D;
 }
 
 rsv_status bilu0_create(rsv_matrix *A, const rsv_pc_params *p, PcImpl **out, int64_t *bad_cell)
