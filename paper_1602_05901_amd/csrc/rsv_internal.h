@@ -351,6 +351,15 @@ __host__ __device__ inline bool inv3(const double *a, double *o)
     return na * ni <= 1e14;
 }
 
+// Block b of nb as a block of one contiguous range per XCD (workgroups are
+// dealt to the eight XCDs in turn, each with its own L2): neighbouring blocks
+// of a kernel whose blocks share cache lines then meet in one L2.
+__device__ inline int64_t xcd_block(int64_t b, int64_t nb)
+{
+    const int64_t x = b & 7, q = nb >> 3, rem = nb & 7;
+    return x * q + (x < rem ? x : rem) + (b >> 3);
+}
+
 // ------------------------------------------------------------------ faces between sweeping tiles
 // A 64-bit face word holds a 32-bit call epoch and one 32-bit half of a value;
 // relaxed agent-scope accesses, valid exactly when the epoch matches.

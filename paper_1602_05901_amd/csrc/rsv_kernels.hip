@@ -168,15 +168,6 @@ __global__ __launch_bounds__(RED_T) void k_reduce(const double *__restrict__ par
     if (threadIdx.x == 0) out[kk] = s;
 }
 
-// Block b of nb as a block of one contiguous range per XCD (workgroups are
-// dealt to the eight XCDs in turn, each with its own L2): neighbouring blocks
-// of a kernel whose blocks share cache lines then meet in one L2.
-__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t nb)
-{
-    const int64_t x = b & 7, q = nb >> 3, rem = nb & 7;
-    return x * q + (x < rem ? x : rem) + (b >> 3);
-}
-
 // Caller order -> tile-lane order and back.  A tile-lane row holds 64 cells of
 // one hyperplane, 64 separate 24-byte pieces of the caller's vector, so one
 // lane per cell made 64 requests of every load or store (567 us in and 1100 us

@@ -471,110 +471,144 @@ hipError_t launch_conv(hipStream_t st, const ConvGeo &g, const uint16_t *X, cons
 // holds A[m = l%16][k = 8*(l/16) .. +7], B[k = 8*(l/16) .. +7][n = l%16], and
 // D[m = 4*(l/16) + i][n = l%16]).  A workgroup owns one 16 x 16 channel pair
 // (ci block, co block) and a chunk of bricks of 16 (x) x 4 (y) x 4 (z)
-// voxels.  Per brick it stages in LDS, channel-major with 16 voxels per row,
-// the input halo three times (shifted by dx = 0, 1, 2, so every A fragment is
-// one aligned 16-byte read) and the gradient tile; wave w then computes the
-// taps t = w, w + 4, ... for all 256 voxels (the B fragment of a k-step serves
-// all its taps).  The next brick's global loads are issued before the MFMAs
-// of the current one.  The rows of a channel are padded so that the 16
-// channels of a fragment fall on distinct LDS banks.
+// voxels.  Per brick it stages in LDS, as they lie in memory (a voxel's 16
+// channels in a row), the input halo and the gradient tile; the fragments, one
+// channel of eight voxels per lane, come from transposing LDS reads: the 16 lanes
+// of a group read four voxels' rows (lane i: voxel i / 4, channels 4 (i % 4) ..
+// + 3), and lane i receives channel i of the four.  k runs over x of two rows, so
+// that a read takes 512 bytes in a line, and a tap's shift is an offset.  Wave w
+// computes the taps t = w, w + 4, ... for all 256 voxels (the B fragment of a
+// k-step serves all its taps).  The next brick's global loads are issued before
+// the MFMAs of the current one.
+//
+// Bound by latency, at two workgroups per CU: of 32 us for 16 x 16 channels on
+// 2^20 voxels (4096 bricks, 67 MB: 14 us), 27 remain without the global loads, the
+// 1 KiB fragments of LDS take 15 at 128 bytes per cycle and the MFMAs 6.  Steps:
+// channel-major staging, one copy per dx, 24 transposing stores and 20 loads of 8
+// bytes per thread and brick, 63 KB: 110 us (32 x 16 channels 199); transposing
+// reads 44 (74); places of the halo's pieces computed once 41; bias sums by
+// shuffles instead of one thread per channel 37; a step's fragments read before
+// the last one's MFMAs 32 (54).  All ten layers of the network, 8 samples of
+// 64 x 64 x 32: 820 -> 260 us.  256 workgroups: 322 us; 1024: 273, and the
+// reduction 77 instead of 59.
 //
 // Split over voxels: each chunk writes one partial (taps, then the bias sums
 // for ci block 0); k_dw_reduce adds them in a fixed order into the gradients.
 // (Summing them inside this kernel, by the last workgroup to finish, needs a
 // device-scope release per workgroup, which writes back the XCD's L2: 5x the
 // time of this kernel and the reduction together at 64x64x32.)
-constexpr int CT_Y = 4, CT_Z = 4, CH_Y = CT_Y + 2, CH_Z = CT_Z + 2;
-constexpr int DW_XS = CH_Z * CH_Y * 16 + 8;   // bf16 per input channel and shift (576 + padding)
-constexpr int DW_GS = CT_Z * CT_Y * 16 + 8;   // bf16 per output channel (256 + padding)
+constexpr int CT_Y = 4, CT_Z = 4, CH_X = 18, CH_Y = CT_Y + 2, CH_Z = CT_Z + 2;
 constexpr int DW_PART = 27 * 256 + 16;        // floats per partial: 27 taps x 16 x 16, then 16 bias sums
-constexpr int DW_MAXCHUNK = 256;              // chunks per pair (16 groups of at most 16 in the reduction)
-constexpr int DW_XU = CH_Z * CH_Y * 2 * 4;    // input staging units: (halo row, x octet, channel quad) = 288
-constexpr size_t DW_LDS = (size_t)(3 * 16 * DW_XS + 16 * DW_GS) * 2;
-static_assert(DW_LDS >= 256 * 16 * sizeof(float), "the bias reduction reuses the staging area");
+constexpr int DW_WGS = 512;                   // workgroups aimed at, so chunks per pair at most
+constexpr int DW_XU = CH_Z * CH_Y * CH_X * 2; // 16-byte pieces of the input halo: (voxel, channel octet)
+constexpr int DW_GU = CT_Z * CT_Y * 16 * 2;   // of the gradient tile
+constexpr int DW_NX = (DW_XU + 255) / 256, DW_NG = DW_GU / 256;
 
-struct DwRegs {
-    v4s x[2][10];   // input units: 10 voxels (x octet + 2) x 4 channels
-    v4s gq[8];      // gradient unit: 8 voxels x 4 channels
-};
+// channel l%16 of the voxels 4 (l/16) .. + 3 of the row of 32-byte voxels at p; p: the lane's own 8 bytes
+__device__ __forceinline__ v4s lds_tr(const unsigned char *p)
+{
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)p);
+}
 
 __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__restrict__ X,
                                                  const uint16_t *__restrict__ G, int npairs,
                                                  int bricks_per_chunk, float *__restrict__ partials)
 {
-    extern __shared__ __align__(16) unsigned char dl[];
-    uint16_t *xs = (uint16_t *)dl;                  // [3 dx][16 ci][DW_XS]
-    uint16_t *gs = xs + 3 * 16 * DW_XS;             // [16 co][DW_GS]
+    __shared__ __align__(16) uint4 xs[DW_XU], gs[DW_GU];   // [z][y][x][16 channels]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int pair = blockIdx.x % npairs, chunk = blockIdx.x / npairs;
+    const int blk = (int)xcd_block(blockIdx.x, gridDim.x);   // a chunk's pairs, and its neighbours, on one die
+    const int pair = blk % npairs, chunk = blk / npairs;
     const int cob_n = g.cout / 16, cib = pair / cob_n, cob = pair % cob_n;
     const int nbricks = brick_count(g, CT_Z);
     const int b_begin = chunk * bricks_per_chunk;
     const int b_end = b_begin + bricks_per_chunk < nbricks ? b_begin + bricks_per_chunk : nbricks;
-    const int m = lane & 15, kx = 8 * ((lane >> 4) & 1), krow = lane >> 5;
-    // gradient unit of threads 0..127: channel quad gq_q, x octet gq_o, row gq_r (y = r & 3, z = r >> 2)
-    const int gq_q = tid & 3, gq_o = (tid >> 2) & 1, gq_r = (tid >> 3) & 15;
+    const bool wide = g.cin % 8 == 0;
+    const int c0 = cib * 16 + 8 * (tid & 1);      // first channel of this thread's pieces
     v4f acc[7];
 #pragma unroll
     for (int j = 0; j < 7; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
-    float bq[4] = {0.f, 0.f, 0.f, 0.f};   // bias sums of channels 4 gq_q .. + 3
-    DwRegs R;
+    float bq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // bias sums of channels 8 (tid & 1) .. + 7
+    uint4 rx[DW_NX], rg[DW_NG];
+    // Places of this thread's pieces from the brick's first voxel; bricks begin at
+    // even coordinates, so halving them (up) is exact.
+    const int sx = g.up ? g.nx >> 1 : g.nx, sy = g.up ? g.ny >> 1 : g.ny;
+    int64_t xo[DW_NX], go[DW_NG];
+    int hc[DW_NX];               // halo coordinates, a byte each; 31 in each byte: no piece
+#pragma unroll
+    for (int k = 0; k < DW_NX; ++k) {
+        const int u = tid + 256 * k, v = u >> 1;
+        const int hx = v % CH_X, hy = (v / CH_X) % CH_Y, hz = v / (CH_X * CH_Y);
+        const bool on = u < DW_XU && c0 < g.cin;
+        hc[k] = on ? hx | hy << 8 | hz << 16 : 31 | 31 << 8 | 31 << 16;
+        xo[k] = ((hx - 1) >> g.up) + (int64_t)sx * (((hy - 1) >> g.up) + (int64_t)sy * ((hz - 1) >> g.up));
+        xo[k] = xo[k] * g.cin + c0;
+    }
+#pragma unroll
+    for (int k = 0; k < DW_NG; ++k) {
+        const int v = (tid + 256 * k) >> 1;
+        go[k] = ((v & 15) + (int64_t)g.nx * (((v >> 4) & 3) + (int64_t)g.ny * (v >> 6))) * g.cout + cob * 16 + 8 * (tid & 1);
+    }
     auto load = [&](int b) {
         const Brick bk = brick_of(g, b, CT_Z);
-        const int x0 = bk.x0, y0 = bk.y0, z0 = bk.z0;
+        // halo coordinates inside the sample: lo .. lo + n - 1
+        const int xl = bk.x0 == 0, xn = min(CH_X, g.nx - bk.x0 + 1) - xl, yl = bk.y0 == 0, yn = min(CH_Y, g.ny - bk.y0 + 1) - yl;
+        const int zl = bk.z0 == bk.zlo, zn = min(CH_Z, bk.zhi - bk.z0 + 1) - zl;
+        const uint16_t *xb =
+            X + ((bk.x0 >> g.up) + (int64_t)sx * ((bk.y0 >> g.up) + (int64_t)sy * (bk.z0 >> g.up))) * g.cin;
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int u = tid + 256 * k;
-            const int q = u & 3, o = (u >> 2) & 1, r = u >> 3;
-            const int hy = r % CH_Y, hz = r / CH_Y;
-            const int c0 = cib * 16 + 4 * q;
-            const bool ok = u < DW_XU && c0 < g.cin;
-#pragma unroll
-            for (int i = 0; i < 10; ++i) {
-                R.x[k][i] = v4s{0, 0, 0, 0};
-                if (ok) {
-                    const int64_t sv = src_voxel(g, x0, y0, z0, 8 * o + i - 1, hy - 1, hz - 1, bk.zlo, bk.zhi);
-                    if (sv >= 0) R.x[k][i] = *(const v4s *)(X + sv * g.cin + c0);
+        for (int k = 0; k < DW_NX; ++k) {
+            rx[k] = uint4{0, 0, 0, 0};
+            const bool in = ((unsigned)((hc[k] & 255) - xl) < (unsigned)xn) & ((unsigned)((hc[k] >> 8 & 255) - yl) < (unsigned)yn) &
+                            ((unsigned)((hc[k] >> 16) - zl) < (unsigned)zn);
+            if (!in) continue;
+            const uint16_t *p = xb + xo[k];
+            if (wide) {
+                rx[k] = *(const uint4 *)p;
+            } else {
+                const uint2 lo = *(const uint2 *)p;
+                rx[k].x = lo.x;
+                rx[k].y = lo.y;
+                if (c0 + 4 < g.cin) {
+                    const uint2 hi = *(const uint2 *)(p + 4);
+                    rx[k].z = hi.x;
+                    rx[k].w = hi.y;
                 }
             }
         }
-        const int y = y0 + (gq_r & 3), z = z0 + (gq_r >> 2);
+        const uint16_t *gb = G + (bk.x0 + (int64_t)g.nx * (bk.y0 + (int64_t)g.ny * bk.z0)) * g.cout;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int x = x0 + 8 * gq_o + i;
-            R.gq[i] = v4s{0, 0, 0, 0};
-            if (tid < 128 && x < g.nx && y < g.ny && z < bk.zhi)
-                R.gq[i] = *(const v4s *)(G + (x + (int64_t)g.nx * (y + (int64_t)g.ny * z)) * g.cout + cob * 16 + 4 * gq_q);
+        for (int k = 0; k < DW_NG; ++k) {
+            const int v = (tid + 256 * k) >> 1;
+            rg[k] = uint4{0, 0, 0, 0};
+            if ((v & 15) < g.nx - bk.x0 && ((v >> 4) & 3) < g.ny - bk.y0 && (v >> 6) < bk.zhi - bk.z0)
+                rg[k] = *(const uint4 *)(gb + go[k]);
         }
     };
     auto store = [&]() {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int u = tid + 256 * k;
-            if (u >= DW_XU) continue;
-            const int q = u & 3, o = (u >> 2) & 1, r = u >> 3;
+        for (int k = 0; k < DW_NX; ++k)
+            if (tid + 256 * k < DW_XU) xs[tid + 256 * k] = rx[k];
 #pragma unroll
-            for (int dx = 0; dx < 3; ++dx)
+        for (int k = 0; k < DW_NG; ++k) {
+            gs[tid + 256 * k] = rg[k];
+            if (cib == 0) {
+                const uint32_t w[4] = {rg[k].x, rg[k].y, rg[k].z, rg[k].w};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    v8s row;
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) row[i] = R.x[k][dx + i][j];
-                    *(v8s *)(xs + (size_t)(dx * 16 + 4 * q + j) * DW_XS + r * 16 + 8 * o) = row;
-                }
-        }
-        if (tid < 128) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v8s row;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    row[i] = R.gq[i][j];
-                    bq[j] += bf2f((uint16_t)R.gq[i][j]);
-                }
-                *(v8s *)(gs + (size_t)(4 * gq_q + j) * DW_GS + gq_r * 16 + 8 * gq_o) = row;
+                for (int i = 0; i < 8; ++i) bq[i] += bf2f((uint16_t)(w[i >> 1] >> (16 * (i & 1))));
             }
         }
+    };
+    // this lane's place in a row of voxels, and with its taps' shifts
+    const int at = (4 * (lane >> 4) + ((lane & 15) >> 2)) * 32 + (lane & 3) * 8;
+    const unsigned char *gp = (const unsigned char *)gs + at, *xp[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        const int t = wave + 4 * j < 27 ? wave + 4 * j : 26;
+        xp[j] = (const unsigned char *)xs + ((t / 9 * CH_Y + (t / 3) % 3) * CH_X + t % 3) * 32 + at;
+    }
+    auto frag = [](const unsigned char *p, int row) {   // two rows, row bytes apart
+        const v4s lo = lds_tr(p), hi = lds_tr(p + row);
+        return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     if (b_begin < b_end) load(b_begin);
     for (int b = b_begin; b < b_end; ++b) {
@@ -582,25 +616,30 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
         store();
         __syncthreads();
         if (b + 1 < b_end) load(b + 1);
-        // k-step s: plane s / 2, rows 2 (s % 2) + krow, x from kx
-#pragma unroll 2
-        for (int s = 0; s < 8; ++s) {
-            const int z = s >> 1, row = 2 * (s & 1) + krow;
-            const v8bf bf = __builtin_bit_cast(v8bf, *(const v8s *)(gs + (size_t)m * DW_GS + (z * CT_Y + row) * 16 + kx));
+        // k-step s: plane s / 2, rows 2 (s % 2) and the next; the next step's
+        // fragments are read before this one's MFMAs
+        struct Frags {
+            v8bf a[7], b;
+        } f[2];
+        auto read = [&](Frags &o, int s) {
+            const int z = s >> 1, row = 2 * (s & 1);
+            o.b = frag(gp + (z * CT_Y + row) * 16 * 32, 16 * 32);
 #pragma unroll
-            for (int j = 0; j < 7; ++j) {
-                const int t = wave + 4 * j;
-                if (t < 27) {
-                    const int tdz = t / 9, tdy = (t / 3) % 3, tdx = t % 3;
-                    const v8bf af = __builtin_bit_cast(
-                        v8bf, *(const v8s *)(xs + (size_t)(tdx * 16 + m) * DW_XS + ((z + tdz) * CH_Y + row + tdy) * 16 + kx));
-                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bf, acc[j], 0, 0, 0);
-                }
-            }
+            for (int j = 0; j < 7; ++j) o.a[j] = frag(xp[j] + (z * CH_Y + row) * CH_X * 32, CH_X * 32);
+        };
+        read(f[0], 0);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if (s < 7) read(f[(s + 1) & 1], s + 1);
+            asm volatile("" ::: "memory");   // not sunk to their uses
+#pragma unroll
+            for (int j = 0; j < 7; ++j)   // wave 3 repeats tap 26: a branch would cost copies of the sums
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[s & 1].a[j], f[s & 1].b, acc[j], 0, 0, 0);
         }
     }
     // this chunk's partial: taps of this wave, then (ci block 0) the bias sums
     float *part = partials + ((int64_t)chunk * npairs + pair) * DW_PART;
+    const int m = lane & 15;
 #pragma unroll
     for (int j = 0; j < 7; ++j) {
         const int t = wave + 4 * j;
@@ -610,15 +649,15 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
     }
     if (cib == 0) {
         __syncthreads();
-        float *red = (float *)dl;   // [16 channels][256 threads]
+        float *red = (float *)xs;   // [wave][16 channels]
 #pragma unroll
-        for (int c = 0; c < 16; ++c) red[c * 256 + tid] = (tid < 128 && c / 4 == gq_q) ? bq[c % 4] : 0.f;
-        __syncthreads();
-        if (tid < 16) {
-            float t = 0.f;
-            for (int q = 0; q < 256; ++q) t += red[tid * 256 + q];
-            part[27 * 256 + tid] = t;
+        for (int c = 0; c < 8; ++c) {   // the lanes of this octet
+#pragma unroll
+            for (int d = 2; d < 64; d *= 2) bq[c] += __shfl_xor(bq[c], d);
+            if (lane < 2) red[wave * 16 + 8 * lane + c] = bq[c];
         }
+        __syncthreads();
+        if (tid < 16) part[27 * 256 + tid] = (red[tid] + red[16 + tid]) + (red[32 + tid] + red[48 + tid]);
     }
 }
 
@@ -636,16 +675,18 @@ __global__ __launch_bounds__(256) void k_dw_reduce(const float *__restrict__ par
     const int cob_n = cout / 16, cib = pair / cob_n, cob = pair % cob_n;
     const int gr = threadIdx.x >> 4, e4 = slice * 16 + (threadIdx.x & 15);
     const int64_t stride = (int64_t)npairs * DW_PART;
-    float4 v[16];
+    float4 s4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int c0 = 0; c0 < nchunks; c0 += 256) {
+        float4 v[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int ch = gr + 16 * i;
-        v[i] = (e4 < NE4 && ch < nchunks) ? *(const float4 *)(partials + ch * stride + (int64_t)pair * DW_PART + 4 * e4)
-                                          : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int i = 0; i < 16; ++i) {
+            const int ch = c0 + gr + 16 * i;
+            v[i] = (e4 < NE4 && ch < nchunks) ? *(const float4 *)(partials + ch * stride + (int64_t)pair * DW_PART + 4 * e4)
+                                              : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) { s4.x += v[i].x; s4.y += v[i].y; s4.z += v[i].z; s4.w += v[i].w; }
     }
-    float4 s4 = v[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) { s4.x += v[i].x; s4.y += v[i].y; s4.z += v[i].z; s4.w += v[i].w; }
     gsum[gr][threadIdx.x & 15] = s4;
     __syncthreads();
     if (threadIdx.x >= 16 || e4 >= NE4) return;
@@ -1213,14 +1254,13 @@ static rsv_status conv_bwd_weight(rsv_net *n, int l, int nx, int ny, int nz, int
     if (g.cout % 16 || g.cin > 64) return set_err(c, RSV_ERR_ARG, "channel count must be 16, 32 or 64");
     const int npairs = ((g.cin + 15) / 16) * (g.cout / 16);
     const int64_t nbricks = brick_count(g, CT_Z);
-    // about 256 workgroups (two per CU fit the 63 KB of LDS) of at least two bricks
-    const int64_t want = std::max<int64_t>(1, std::min<int64_t>((nbricks + 1) / 2, std::max(1, 256 / npairs)));
+    // about DW_WGS workgroups (two per CU) of at least two bricks
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>((nbricks + 1) / 2, std::max(1, DW_WGS / npairs)));
     const int per = (int)((nbricks + want - 1) / want);
     const int nchunks = (int)((nbricks + per - 1) / per);
-    if (nchunks > DW_MAXCHUNK) return set_err(c, RSV_ERR_ARG, "weight gradient: too many voxel chunks");
     rsv_status s = part_reserve(n, (int64_t)nchunks * npairs * DW_PART);
     if (s != RSV_OK) return s;
-    hipLaunchKernelGGL(k_conv_dw, dim3(nchunks * npairs), dim3(256), DW_LDS, c->stream, g, X, G, npairs, per, n->part);
+    hipLaunchKernelGGL(k_conv_dw, dim3(nchunks * npairs), dim3(256), 0, c->stream, g, X, G, npairs, per, n->part);
     constexpr int slices = (DW_PART / 4 + 15) / 16;
     hipLaunchKernelGGL(k_dw_reduce, dim3(npairs * slices), dim3(256), 0, c->stream, (const float *)n->part, npairs, nchunks,
                        g.cin, g.cout, scale, grad_w, grad_b);

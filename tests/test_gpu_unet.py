@@ -463,6 +463,27 @@ def test_staged_conv_edges(rsv, ctx, dims, cin, cout):
     assert np.all(np.abs(dx.cpu().numpy().astype(np.float64) - ref) <= 2e-5 * bound + 1e-30)
 
 
+@pytest.mark.parametrize("dims,cin,cout", [((17, 9, 13), 4, 64), ((31, 12, 6), 12, 16), ((16, 5, 9), 20, 32),
+                                           ((1, 33, 2), 40, 16), ((34, 3, 17), 64, 64), ((64, 64, 64), 16, 16)])
+def test_weight_gradient_edges(rsv, ctx, dims, cin, cout):
+    """Weight and bias gradients at the edges of their bricks, with input
+    channels that end inside a block of 16 or an octet, and (last) with more
+    chunks than the reduction takes at once: the bound of the layer tests."""
+    log("weight gradient", dims, cin, cout)
+    V = dims[0] * dims[1] * dims[2]
+    x = bf16_values(21, 5, V * cin)
+    w = bf16_values(22, 5, 27 * cin * cout, -0.2, 0.2)
+    dy = bf16_values(23, 5, V * cout)
+    dw = torch.zeros(27 * cin * cout, dtype=torch.float32, device="cuda")
+    db = torch.zeros(cout, dtype=torch.float32, device="cuda")
+    rsv.conv3d_bwd(ctx, dims, cin, cout, bf16_bits(x), dev(w.astype(np.float32)), bf16_bits(dy), None, dw, db)
+    _, rdw, rdb = U.conv3d_bwd(dims, cin, cout, x, w, dy)
+    _, bdw, bdb = U.conv3d_bwd(dims, cin, cout, np.abs(x), np.abs(w), np.abs(dy))
+    for got, ref, bound in ((dw, rdw, bdw), (db, rdb, bdb)):
+        err = np.abs(got.cpu().numpy().astype(np.float64) - ref)
+        assert np.all(err <= 2e-5 * bound + 1e-30), float(np.max(err / (bound + 1e-30)))
+
+
 @pytest.mark.parametrize("dims,nb", [((4, 4, 4), 5), ((12, 8, 20), 3), ((64, 64, 64), 10)])
 def test_batch_is_its_samples(rsv, ctx, dims, nb):
     """Samples that share a pass do not see each other: a batch's loss is the
