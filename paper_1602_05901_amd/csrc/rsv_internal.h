@@ -239,6 +239,7 @@ rsv_status launch_reduce_to(rsv_ctx *c, int nblocks, int K, double *out);   // t
 // matrix-independent front ends the Krylov drivers use
 rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, const double *x, double *y,
                         const double *aux, double alpha, double beta, int k0);
+int mat_spmv_blocks(rsv_matrix *M);   // partials of a product with sums; k0 < 0 leaves them at the head of d_partials
 rsv_status mat_spmv(rsv_matrix *M, int mode, const double *x, double *y, const double *aux, double alpha,
                     double beta, int k0);
 rsv_status mat_in(rsv_matrix *M, const double *nat, double *v);                       // ABI order -> solver layout
@@ -257,14 +258,11 @@ rsv_status launch_assemble(rsv_ctx *c, const Geo &g, const double *blocks_nat_de
 // vector ops on length-n arrays
 rsv_status launch_dot(rsv_ctx *c, int64_t n, const double *x, const double *y, int k0);   // x.y -> sc[k0]
 rsv_status launch_copy(rsv_ctx *c, int64_t n, const double *x, double *y);
-rsv_status launch_scale_dev(rsv_ctx *c, int64_t n, double *x, int k_norm2);   // x /= sqrt(sc[k]) (0 -> 0)
 rsv_status launch_axpby(rsv_ctx *c, int64_t n, double a, const double *x, double b, double *y); // y = a x + b y
-rsv_status launch_mdot(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, const double *w, int k0);
-// CGS2's second pass: dots of V_i with w - V c (c = scalars kc..), w unchanged
-rsv_status launch_upd_dot(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, double *w, int kc, int k0);
-// CGS2's third pass: w <- (w - V c1) - V c2 (scalars kc1.., kc2..) and w . w
-rsv_status launch_upd_norm(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, double *w, int kc1, int kc2,
-                           int k0);
+// CGS2 of w against K vectors, dots to SC_H1 and SC_H2, w . w to SC_HN, then w normalised (0 -> 0)
+bool cgs2_folds(int64_t n);
+rsv_status launch_cgs2(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, double *w, int nb0,
+                       int buf);
 rsv_status launch_combine(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, int ky, double *u, int accumulate);
 // Fixed per-device scratch of the entry points that allocate nothing
 // (RSV_NOALLOC_SCRATCH_BYTES in rsv.h), in doubles.

@@ -353,6 +353,34 @@ __global__ __launch_bounds__(BS) void k_scale_dev(int64_t n, double *__restrict_
     for (int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x; e < n; e += (int64_t)gridDim.x * BS) x[e] *= f;
 }
 
+// the same with x . x still in the nb <= BS block partials pin, stored at
+// sc[SC_HN]; block 0 also writes a CGS2 step's scalars (K <= BS vectors) to host
+// (pinned; null: not)
+__global__ __launch_bounds__(BS) void k_scale_sum(int64_t n, double *__restrict__ x, const double *__restrict__ pin, int nb,
+                                                  double *__restrict__ sc, int K, double *__restrict__ host)
+{
+    __shared__ double lds[16], nrm;
+    const double t = block_sum((int)threadIdx.x < nb ? pin[threadIdx.x] : 0.0, lds);
+    if (threadIdx.x == 0) {
+        nrm = t;
+        if (blockIdx.x == 0) {
+            sc[SC_HN] = t;
+            if (host) {
+                host[SC_HN] = t;
+                host[SC_W0] = sc[SC_W0];
+            }
+        }
+    }
+    if (blockIdx.x == 0 && host && (int)threadIdx.x < K) {
+        host[SC_H1 + threadIdx.x] = sc[SC_H1 + threadIdx.x];
+        host[SC_H2 + threadIdx.x] = sc[SC_H2 + threadIdx.x];
+    }
+    __syncthreads();
+    const double nn = nrm;
+    const double f = (nn > 0.0) ? 1.0 / sqrt(nn) : 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x; e < n; e += (int64_t)gridDim.x * BS) x[e] *= f;
+}
+
 __global__ __launch_bounds__(BS) void k_axpby(int64_t n, double a, const double *__restrict__ x, double b,
                                               double *__restrict__ y)
 {
@@ -368,10 +396,28 @@ constexpr int KMAX = 64;   // max vectors in a multi-dot (GMRES restart <= 60)
 // to back instead of one branch -- and one memory round trip -- per vector.
 __device__ __forceinline__ int64_t vrow(int i, int K, int64_t ldv) { return (int64_t)(i < K ? i : K - 1) * ldv; }
 
-// partial dots V_i . w for i < K
+// Final sums of K values over nb <= BS block partials ([nb][K]), formed by the
+// kernel that uses them instead of a k_reduce before it: thread b takes block b's
+// partials, then the block sums of k_reduce, so every block of the consumer gets
+// k_reduce's bits.  sums: LDS, K; out: device, written by block 0.
+template <int KB>
+__device__ inline void sums_of_partials(const double *__restrict__ partials, int nb, int K, double *red, double *sums,
+                                        double *__restrict__ out)
+{
+    double a[KB];
+#pragma unroll
+    for (int i = 0; i < KB; ++i) a[i] = (int)threadIdx.x < nb && i < K ? partials[(int64_t)threadIdx.x * K + i] : 0.0;
+    block_sums<KB>(a, K, red, sums);
+    __syncthreads();
+    if (blockIdx.x == 0 && (int)threadIdx.x < K) out[threadIdx.x] = sums[threadIdx.x];
+}
+
+// partial dots V_i . w for i < K; the last block also sums nb0 partials of the
+// product before (0: none) into w0
 template <int KB>
 __global__ __launch_bounds__(BS) void k_mdot(int64_t n, const double *__restrict__ V, int64_t ldv, int K,
-                                             const double *__restrict__ w, double *__restrict__ partials)
+                                             const double *__restrict__ w, double *__restrict__ partials,
+                                             const double *__restrict__ p0, int nb0, double *__restrict__ w0)
 {
     __shared__ double red[KB * (BS / 64)];
     double acc[KB];
@@ -386,6 +432,10 @@ __global__ __launch_bounds__(BS) void k_mdot(int64_t n, const double *__restrict
         for (int i = 0; i < KB; ++i) acc[i] += v[i] * we;
     }
     block_sums<KB>(acc, K, red, partials + (int64_t)blockIdx.x * K);
+    if (nb0 > 0 && blockIdx.x == gridDim.x - 1) {
+        const double t = block_sum((int)threadIdx.x < nb0 ? p0[threadIdx.x] : 0.0, red);
+        if (threadIdx.x == 0) *w0 = t;
+    }
 }
 
 // The second and third classical Gram-Schmidt passes over the basis, with
@@ -394,21 +444,28 @@ __global__ __launch_bounds__(BS) void k_mdot(int64_t n, const double *__restrict
 //           and the partial dots V_i . u;
 //   MODE 1: w <- (w - sum_i c1_i V_i) - sum_i c2_i V_i (each sum ascending)
 //           and the partial w . w.
+// FOLD: the last set of coefficients is summed here from the partials of the
+// kernel before (pin, one per block of this launch) and stored at c1 (MODE 0) or
+// c2 (MODE 1).
 // The pair gives the same bits as w -= V c1; dots; w -= V c2; norm, but the
 // second pass only reads: a pass that also writes a stream runs at about
 // 5 TB/s on this part, one that only reads at about 6.2.
-template <int KB, int MODE>
+template <int KB, int MODE, bool FOLD>
 __global__ __launch_bounds__(BS) void k_upd(int64_t n, const double *__restrict__ V, int64_t ldv, int K,
-                                            double *__restrict__ w, const double *__restrict__ c1,
-                                            const double *__restrict__ c2, double *__restrict__ partials)
+                                            double *__restrict__ w, double *__restrict__ c1,
+                                            double *__restrict__ c2, double *__restrict__ partials,
+                                            const double *__restrict__ pin)
 {
-    __shared__ double red[(MODE == 0 ? KB : 1) * (BS / 64)];
+    __shared__ double red[(MODE == 0 || FOLD ? KB : 1) * (BS / 64)];
+    __shared__ double sums[FOLD ? KB : 1];
     double coef[KB], coef2[MODE == 1 ? KB : 1];
     double acc[MODE == 0 ? KB : 1];
+    if constexpr (FOLD) sums_of_partials<KB>(pin, gridDim.x, K, red, sums, MODE == 0 ? c1 : c2);
 #pragma unroll
-    for (int i = 0; i < KB; ++i) coef[i] = (i < K) ? c1[i] : 0.0;
+    for (int i = 0; i < KB; ++i) coef[i] = (i < K) ? (FOLD && MODE == 0 ? sums[i] : c1[i]) : 0.0;
 #pragma unroll
-    for (int i = 0; i < (MODE == 1 ? KB : 1); ++i) coef2[i] = (MODE == 1 && i < K) ? c2[i] : 0.0;
+    for (int i = 0; i < (MODE == 1 ? KB : 1); ++i) coef2[i] = (MODE == 1 && i < K) ? (FOLD ? sums[i] : c2[i]) : 0.0;
+    if constexpr (FOLD) __syncthreads();   // red is used again
 #pragma unroll
     for (int i = 0; i < (MODE == 0 ? KB : 1); ++i) acc[i] = 0.0;
     for (int64_t e = (int64_t)blockIdx.x * BS + threadIdx.x; e < n; e += (int64_t)gridDim.x * BS) {
@@ -654,7 +711,7 @@ rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, cons
     }
     prof_end(c, tok);
     RSV_LAUNCH(c);
-    if (mode >= SPMV_RESID) return launch_reduce(c, nb, mode == SPMV_DOT2 ? 2 : 1, k0);
+    if (mode >= SPMV_RESID && k0 >= 0) return launch_reduce(c, nb, mode == SPMV_DOT2 ? 2 : 1, k0);
     return RSV_OK;
 }
 
@@ -708,14 +765,6 @@ rsv_status launch_copy(rsv_ctx *c, int64_t n, const double *x, double *y)
     return RSV_OK;
 }
 
-rsv_status launch_scale_dev(rsv_ctx *c, int64_t n, double *x, int k)
-{
-    ProfScope ps(c, RSV_K_ORTHO);
-    hipLaunchKernelGGL(k_scale_dev, dim3(vec_blocks(n)), dim3(BS), 0, c->stream, n, x, c->d_scal + k);
-    RSV_LAUNCH(c);
-    return RSV_OK;
-}
-
 rsv_status launch_axpby(rsv_ctx *c, int64_t n, double a, const double *x, double b, double *y)
 {
     hipLaunchKernelGGL(k_axpby, dim3(vec_blocks(n)), dim3(BS), 0, c->stream, n, a, x, b, y);
@@ -728,57 +777,98 @@ rsv_status launch_axpby(rsv_ctx *c, int64_t n, double a, const double *x, double
     else if ((K) <= 32) { MACRO(32); } else if ((K) <= 40) { MACRO(40); } else if ((K) <= 48) { MACRO(48); } \
     else if ((K) <= 56) { MACRO(56); } else { MACRO(64); }
 
-rsv_status launch_mdot(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, const double *w, int k0)
+static rsv_status spec_reserve(rsv_ctx *c)
 {
-    if (K < 1 || K > KMAX) return set_err(c, RSV_ERR_ARG, "mdot K");
+    if (c->h_spec) return RSV_OK;
+    RSV_HIP(c, hipHostMalloc((void **)&c->h_spec, 2 * SC_COUNT * sizeof(double), hipHostMallocDefault));
+    for (int b = 0; b < 2; ++b) RSV_HIP(c, hipEventCreateWithFlags(&c->spec_ev[b], hipEventDisableTiming));
+    return RSV_OK;
+}
+
+// At most BS blocks: the consumers can sum the partials themselves.
+bool cgs2_folds(int64_t n) { return mvec_blocks(n) <= BS; }
+
+// Orthogonalises w against V_0 .. V_{K-1} by two classical Gram-Schmidt passes and
+// normalises it: SC_H1 and SC_H2 get the passes' dots, SC_HN w . w before the
+// normalisation.  buf >= 0: these scalars go to that half of h_spec, for scal_wait.
+// nb0 > 0 (cgs2_folds only): the partials of the SPMV_NORM product
+// that made w lie unreduced at the head of d_partials; SC_W0 gets their sum.
+//
+// Long vectors reduce each kernel's partials by a k_reduce.  For short ones that
+// launch, 2.5 to 4 us, is as long as the pass before it (n = 17280: dots 4.7 us,
+// updates 4.1 to 5.2), so the next kernel forms the sums (4.2 us instead of 2.4 for
+// the normalisation, 0.1 to 0.6 more for the others), and the last one writes the
+// scalars to the host's buffer: 12 launches per Arnoldi step become 7, a solve of 12
+// steps on 20 x 20 x 10 cells 1.43 -> 1.35 ms.  Up to BS blocks, where a consumer's
+// thread takes one block's partials; beyond, every block would read a share of
+// them that grows with n.
+rsv_status launch_cgs2(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, double *w, int nb0, int buf)
+{
+    if (K < 1 || K > KMAX) return set_err(c, RSV_ERR_ARG, "cgs2 K");
     const int nb = mvec_blocks(n);
-    rsv_status s = partials_reserve(c, (int64_t)nb * K);
+    const bool fold = cgs2_folds(n);
+    if (nb0 > 0 && (!fold || nb0 > BS)) return set_err(c, RSV_ERR_ARG, "cgs2 partials");
+    // all three kernels' partials behind the product's; the first reservation of
+    // d_partials holds as much, so the product's are not moved here
+    const int64_t per = (int64_t)nb * K;
+    rsv_status s = partials_reserve(c, fold ? BS + 2 * per + nb : per);
     if (s != RSV_OK) return s;
-#define L_MDOT(KB) hipLaunchKernelGGL(k_mdot<KB>, dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, c->d_partials)
+    double *p0 = c->d_partials, *p1 = fold ? p0 + BS : p0, *p2 = fold ? p1 + per : p0, *p3 = fold ? p2 + per : p0;
+    double *h1 = c->d_scal + SC_H1, *h2 = c->d_scal + SC_H2;
+    if (buf >= 0 && (s = spec_reserve(c)) != RSV_OK) return s;
+    double *host = buf >= 0 ? c->h_spec + (size_t)buf * SC_COUNT : nullptr;
+#define L_MDOT(KB)                                                                                              \
+    hipLaunchKernelGGL(k_mdot<KB>, dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, (const double *)w, p1, \
+                       (const double *)p0, nb0, c->d_scal + SC_W0)
+#define L_UPD(KB)                                                                                                       \
+    if (fold)                                                                                                           \
+        hipLaunchKernelGGL((k_upd<KB, 0, true>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p2,         \
+                           (const double *)p1);                                                                         \
+    else                                                                                                                \
+        hipLaunchKernelGGL((k_upd<KB, 0, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p2,        \
+                           (const double *)nullptr)
+#define L_UPDN(KB)                                                                                                      \
+    if (fold)                                                                                                           \
+        hipLaunchKernelGGL((k_upd<KB, 1, true>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3,         \
+                           (const double *)p2);                                                                         \
+    else                                                                                                                \
+        hipLaunchKernelGGL((k_upd<KB, 1, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3,        \
+                           (const double *)nullptr)
     {
         ProfScope ps(c, RSV_K_ORTHO);
         KB_DISPATCH(K, L_MDOT)
     }
-#undef L_MDOT
     RSV_LAUNCH(c);
-    return launch_reduce(c, nb, K, k0);
-}
-
-rsv_status launch_upd_dot(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, double *w, int kc, int k0)
-{
-    if (K < 1 || K > KMAX) return set_err(c, RSV_ERR_ARG, "upd K");
-    const int nb = mvec_blocks(n);
-    rsv_status s = partials_reserve(c, (int64_t)nb * K);
-    if (s != RSV_OK) return s;
-#define L_UPD(KB)                                                                                          \
-    hipLaunchKernelGGL((k_upd<KB, 0>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, c->d_scal + kc, \
-                       c->d_scal + kc, c->d_partials)
+    if (!fold && (s = launch_reduce(c, nb, K, SC_H1)) != RSV_OK) return s;
     {
         ProfScope ps(c, RSV_K_ORTHO);
         KB_DISPATCH(K, L_UPD)
     }
-#undef L_UPD
     RSV_LAUNCH(c);
-    return launch_reduce(c, nb, K, k0);
-}
-
-rsv_status launch_upd_norm(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, double *w, int kc1, int kc2,
-                           int k0)
-{
-    if (K < 1 || K > KMAX) return set_err(c, RSV_ERR_ARG, "upd K");
-    const int nb = mvec_blocks(n);
-    rsv_status s = partials_reserve(c, nb);
-    if (s != RSV_OK) return s;
-#define L_UPDN(KB)                                                                                          \
-    hipLaunchKernelGGL((k_upd<KB, 1>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, c->d_scal + kc1, \
-                       c->d_scal + kc2, c->d_partials)
+    if (!fold && (s = launch_reduce(c, nb, K, SC_H2)) != RSV_OK) return s;
     {
         ProfScope ps(c, RSV_K_ORTHO);
         KB_DISPATCH(K, L_UPDN)
     }
-#undef L_UPDN
     RSV_LAUNCH(c);
-    return launch_reduce(c, nb, 1, k0);
+#undef L_MDOT
+#undef L_UPD
+#undef L_UPDN
+    if (!fold && (s = launch_reduce(c, nb, 1, SC_HN)) != RSV_OK) return s;
+    {
+        ProfScope ps(c, RSV_K_ORTHO);
+        if (fold)
+            hipLaunchKernelGGL(k_scale_sum, dim3(vec_blocks(n)), dim3(BS), 0, c->stream, n, w, (const double *)p3, nb, c->d_scal,
+                               K, host);
+        else
+            hipLaunchKernelGGL(k_scale_dev, dim3(vec_blocks(n)), dim3(BS), 0, c->stream, n, w,
+                               (const double *)(c->d_scal + SC_HN));
+    }
+    RSV_LAUNCH(c);
+    if (buf < 0) return RSV_OK;
+    if (!fold) return scal_to_host_async(c, buf, 0, SC_H2 + K);
+    RSV_HIP(c, hipEventRecord(c->spec_ev[buf], c->stream));
+    return RSV_OK;
 }
 
 rsv_status launch_combine(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int K, int ky, double *u, int accumulate)
@@ -867,10 +957,8 @@ rsv_status scal_to_host(rsv_ctx *c, int k0, int n)
 
 rsv_status scal_to_host_async(rsv_ctx *c, int buf, int k0, int n)
 {
-    if (!c->h_spec) {
-        RSV_HIP(c, hipHostMalloc((void **)&c->h_spec, 2 * SC_COUNT * sizeof(double), hipHostMallocDefault));
-        for (int b = 0; b < 2; ++b) RSV_HIP(c, hipEventCreateWithFlags(&c->spec_ev[b], hipEventDisableTiming));
-    }
+    const rsv_status s = spec_reserve(c);
+    if (s != RSV_OK) return s;
     double *dst = c->h_spec + (size_t)buf * SC_COUNT;
     RSV_HIP(c, hipMemcpyAsync(dst + k0, c->d_scal + k0, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     RSV_HIP(c, hipEventRecord(c->spec_ev[buf], c->stream));

@@ -126,6 +126,7 @@ static rsv_status gmres(Solve &S, PcImpl *P, PcImpl *FB, double theta, int m, in
     double *zt = pool + (int64_t)(flexible ? 2 * m + 1 : m + 1) * n;
     double *ut = zt + n;
     const double nb = S.ctl.nb;
+    const int nb0 = cgs2_folds(n) ? mat_spmv_blocks(S.M) : 0;   // partials of the product that the orthogonalisation sums
     rsv_status rc = RSV_OK;
     int64_t its = 0;
     std::vector<double> H((size_t)(m + 1) * m), cs(m + 1, 0.0), sn(m + 1, 0.0), g(m + 2, 0.0), y(m, 0.0);
@@ -236,12 +237,8 @@ static rsv_status gmres(Solve &S, PcImpl *P, PcImpl *FB, double theta, int m, in
             auto enqueue = [&](int j) -> rsv_status {
                 double *w = V + (int64_t)(j + 1) * n;
                 rsv_status e = pc_apply(c, P, n, V + (int64_t)j * n, zt);
-                if (e == RSV_OK) e = mat_spmv(S.M, SPMV_NORM, zt, w, nullptr, 0, 0, SC_W0);
-                if (e == RSV_OK) e = launch_mdot(c, n, V, n, j + 1, w, SC_H1);
-                if (e == RSV_OK) e = launch_upd_dot(c, n, V, n, j + 1, w, SC_H1, SC_H2);
-                if (e == RSV_OK) e = launch_upd_norm(c, n, V, n, j + 1, w, SC_H1, SC_H2, SC_HN);
-                if (e == RSV_OK) e = launch_scale_dev(c, n, w, SC_HN);
-                if (e == RSV_OK) e = scal_to_host_async(c, j & 1, 0, SC_H2 + j + 1);
+                if (e == RSV_OK) e = mat_spmv(S.M, SPMV_NORM, zt, w, nullptr, 0, 0, nb0 ? -1 : SC_W0);
+                if (e == RSV_OK) e = launch_cgs2(c, n, V, n, j + 1, w, nb0, j & 1);
                 return e;
             };
             double est = beta;
@@ -284,11 +281,8 @@ static rsv_status gmres(Solve &S, PcImpl *P, PcImpl *FB, double theta, int m, in
                 used_fb = want_fb;
                 s = pc_apply(c, use, n, V + (int64_t)j * n, z);
                 if (s != RSV_OK) return s;
-                s = mat_spmv(S.M, SPMV_NORM, z, w, nullptr, 0, 0, SC_W0);
-                if (s == RSV_OK) s = launch_mdot(c, n, V, n, j + 1, w, SC_H1);
-                if (s == RSV_OK) s = launch_upd_dot(c, n, V, n, j + 1, w, SC_H1, SC_H2);
-                if (s == RSV_OK) s = launch_upd_norm(c, n, V, n, j + 1, w, SC_H1, SC_H2, SC_HN);
-                if (s == RSV_OK) s = launch_scale_dev(c, n, w, SC_HN);
+                s = mat_spmv(S.M, SPMV_NORM, z, w, nullptr, 0, 0, nb0 ? -1 : SC_W0);
+                if (s == RSV_OK) s = launch_cgs2(c, n, V, n, j + 1, w, nb0, -1);
                 if (s == RSV_OK) s = scal_to_host(c, 0, SC_H2 + j + 1);
                 if (s != RSV_OK) return s;
                 const double *hs = c->h_scal;

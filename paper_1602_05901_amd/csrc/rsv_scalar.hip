@@ -1041,7 +1041,7 @@ rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, 
     }
     prof_end(c, tok);
     RSV_LAUNCH(c);
-    if (mode >= SPMV_RESID) return launch_reduce(c, nb, mode == SPMV_DOT2 ? 2 : 1, k0);
+    if (mode >= SPMV_RESID && k0 >= 0) return launch_reduce(c, nb, mode == SPMV_DOT2 ? 2 : 1, k0);
     return RSV_OK;
 }
 
@@ -1050,6 +1050,12 @@ rsv_status mat_spmv(rsv_matrix *M, int mode, const double *x, double *y, const d
 {
     if (M->bs == 1) return launch_sspmv(M->g->ctx, M->g->geo, M->d_coef, mode, x, y, aux, alpha, beta, k0);
     return launch_spmv(M->g->ctx, M->g->geo, M->d_A, mode, x, y, aux, alpha, beta, k0);
+}
+
+int mat_spmv_blocks(rsv_matrix *M)
+{
+    const Geo &g = M->g->geo;
+    return M->bs == 1 ? (int)(((int64_t)g.nx * g.ny * g.nz + SB - 1) / SB) : spmv_blocks(g);
 }
 
 rsv_status mat_in(rsv_matrix *M, const double *nat, double *v)
