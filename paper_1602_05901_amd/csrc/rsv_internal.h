@@ -239,6 +239,9 @@ rsv_status launch_reduce_to(rsv_ctx *c, int nblocks, int K, double *out);   // t
 // matrix-independent front ends the Krylov drivers use
 rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, const double *x, double *y,
                         const double *aux, double alpha, double beta, int k0);
+// A product's matrix is loaded without keeping: vectors of n doubles fit the 256 MB
+// cache behind the L2s, which the matrix would push them out of.
+inline bool once_through(int64_t n) { return n * (int64_t)sizeof(double) <= (int64_t)256 << 20; }
 int mat_spmv_blocks(rsv_matrix *M);   // partials of a product with sums; k0 < 0 leaves them at the head of d_partials
 rsv_status mat_spmv(rsv_matrix *M, int mode, const double *x, double *y, const double *aux, double alpha,
                     double beta, int k0);

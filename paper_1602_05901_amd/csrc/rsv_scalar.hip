@@ -77,7 +77,7 @@ __global__ __launch_bounds__(SB) void k_sassemble(Geo g, const double *__restric
     }
 }
 
-template <int MODE>
+template <int MODE, bool NT>
 __global__ __launch_bounds__(SB) void k_sspmv(Geo g, const double *__restrict__ coef, const double *__restrict__ x,
                                               double *__restrict__ y, const double *__restrict__ aux,
                                               double alpha, double beta, double *__restrict__ partials)
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(SB) void k_sspmv(Geo g, const double *__restrict__ 
             dir_off(s, di, dj, dk);
             const int a = i + di, b = j + dj, c = k + dk;
             if (a >= 0 && a < g.nx && b >= 0 && b < g.ny && c >= 0 && c < g.nz)
-                acc += coef[s * n + r] * x[(s == 3) ? r : row_of(g, a, b, c)];
+                acc += (NT ? __builtin_nontemporal_load(coef + s * n + r) : coef[s * n + r]) * x[(s == 3) ? r : row_of(g, a, b, c)];
         }
         double o = acc;
         if (MODE == SPMV_AXPBY) {
@@ -1030,15 +1030,24 @@ rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, 
     double *P = c->d_partials;
     const int tok = prof_begin(c, RSV_K_SPMV);
     const dim3 grid(nb), blk(SB);
+    const bool nt = once_through(n);   // 16.8 M cells: 265 -> 247 us
+#define L_SSPMV(M)                                                                                              \
+    case M:                                                                                                     \
+        if (nt)                                                                                                 \
+            hipLaunchKernelGGL((k_sspmv<M, true>), grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P);  \
+        else                                                                                                    \
+            hipLaunchKernelGGL((k_sspmv<M, false>), grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); \
+        break;
     switch (mode) {
-    case SPMV_Y: hipLaunchKernelGGL(k_sspmv<SPMV_Y>, grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); break;
-    case SPMV_AXPBY: hipLaunchKernelGGL(k_sspmv<SPMV_AXPBY>, grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); break;
-    case SPMV_RESID: hipLaunchKernelGGL(k_sspmv<SPMV_RESID>, grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); break;
-    case SPMV_NORM: hipLaunchKernelGGL(k_sspmv<SPMV_NORM>, grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); break;
-    case SPMV_DOT1: hipLaunchKernelGGL(k_sspmv<SPMV_DOT1>, grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); break;
-    case SPMV_DOT2: hipLaunchKernelGGL(k_sspmv<SPMV_DOT2>, grid, blk, 0, c->stream, g, coef, x, y, aux, alpha, beta, P); break;
+    L_SSPMV(SPMV_Y)
+    L_SSPMV(SPMV_AXPBY)
+    L_SSPMV(SPMV_RESID)
+    L_SSPMV(SPMV_NORM)
+    L_SSPMV(SPMV_DOT1)
+    L_SSPMV(SPMV_DOT2)
     default: return set_err(c, RSV_ERR_ARG, "bad spmv mode");
     }
+#undef L_SSPMV
     prof_end(c, tok);
     RSV_LAUNCH(c);
     if (mode >= SPMV_RESID && k0 >= 0) return launch_reduce(c, nb, mode == SPMV_DOT2 ? 2 : 1, k0);
