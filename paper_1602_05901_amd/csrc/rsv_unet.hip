@@ -410,9 +410,18 @@ hipError_t launch_conv_lds(hipStream_t st, const ConvGeo &g, const uint16_t *X, 
         const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
         if (e != hipSuccess) return e;
     }
-    // a few workgroups per CU, each walking many bricks with its weights staged once
+    // As many workgroups as the 256 CUs hold at once (1 to 5 each, by registers and
+    // LDS), walking the bricks with their weights staged once: more would run as a
+    // second, part-empty round.  1024 in all cases, then resident: 4 -> 16 channels
+    // 22.1 -> 21.2 us at 128x128x64, 16 -> 16 37.6 -> 33.2, 32 -> 16 58.4 -> 55.9,
+    // 32 -> 32 (64x64x32) 20.2 -> 18.1, 64 -> 32 28.2 -> 22.9.
+    static const int resident = [&] {
+        int nb = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void *)fn, C::NT, C::LDS);
+        return e == hipSuccess && nb > 0 ? nb : 2;
+    }();
     const unsigned groups = (unsigned)(g.cout / (16 * NSPLIT * NBW));
-    const unsigned nwg = std::min<unsigned>((unsigned)brick_count(g, TZ), 1024u / groups);
+    const unsigned nwg = std::min<unsigned>((unsigned)brick_count(g, TZ), std::max(1u, 256u * resident / groups));
     hipLaunchKernelGGL(fn, dim3(nwg, groups), dim3(C::NT), C::LDS, st, g, X, Wf, ep);
     return hipGetLastError();
 }
