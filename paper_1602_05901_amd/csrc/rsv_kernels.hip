@@ -431,9 +431,10 @@ __global__ __launch_bounds__(BS) void k_mdot(int64_t n, const double *__restrict
 #pragma unroll
         for (int i = 0; i < KB; ++i) v[i] = V[vrow(i, K, ldv) + e];
         const double we = w[e];
-        // All loads first: left to itself the compiler holds 24 vectors' sums and loads
-        // in 62 registers, a few loads at a time (17 to 24 vectors of 25 M entries: 803
-        // us, 5.3 TB/s, against 706; of 3.1 M: 115 against 95).
+        // All loads first: with the code of the product's sum behind the loop, the
+        // compiler otherwise holds 24 vectors' sums and loads in 62 registers, a few
+        // loads at a time (17 to 24 vectors of 25 M entries: 803 us, 5.3 TB/s, against
+        // 706; of 3.1 M: 115 against 95).
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < KB; ++i) acc[i] += v[i] * we;
