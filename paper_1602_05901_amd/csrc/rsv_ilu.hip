@@ -326,6 +326,7 @@ constexpr int SW_FACE = 2;       // steps a face row is loaded ahead
 constexpr int SW_MAXD = 10;      // ring slots at most: the next tile is claimed D + 5 steps before a tile's end
 constexpr int SW_LDS = 160 * 1024;
 constexpr int SW_THREADS = 64 * 9;
+constexpr int64_t SW_NT_SLOTS = (int64_t)2 << 20;   // FP64 sweeps of this many slots load without keeping
 
 // One step's operands in LDS: factor blocks (27 rows of 64), D^-1 (backward, 9),
 // the right-hand side (3; FP64 forward), each as it lies in memory.
@@ -350,13 +351,19 @@ template <int DIR, typename T> struct SweepCfg {
 
 // 16 (or 4) bytes per lane from src + voff to LDS address dst + 16 (4) lane (both
 // + AT, below 4096); src uniform.  The compiler does not count these loads: the
-// waits are explicit.
-template <int AT> __device__ __forceinline__ void lds_copy(uint32_t voff, const void *src, uint32_t dst)
+// waits are explicit.  NT: nontemporal, the lines are not kept.
+template <int AT, bool NT> __device__ __forceinline__ void lds_copy(uint32_t voff, const void *src, uint32_t dst)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
-                 :
-                 : "v"(voff), "s"(src), "s"(dst), "n"(AT)
-                 : "memory");
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3 nt"
+                     :
+                     : "v"(voff), "s"(src), "s"(dst), "n"(AT)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+                     :
+                     : "v"(voff), "s"(src), "s"(dst), "n"(AT)
+                     : "memory");
 }
 // the same past the caches that other dies do not see, as the face words need it
 __device__ __forceinline__ void lds_copy_face(const void *p, uint32_t dst)
@@ -373,7 +380,7 @@ template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_
 // A loading wave's share of one step's copies: chunks c, c + 3, ... of the slot at
 // LDS address dst.  f, d, v: the step's rows; vt, v8: the lanes' offsets within
 // even and odd KiB of T and of FP64 rows.
-template <int DIR, typename T, int c>
+template <int DIR, typename T, bool NT, int c>
 __device__ __forceinline__ void sweep_copy(const char *f, const char *d, const char *v, const uint32_t (&vt)[2],
                                            const uint32_t (&v8)[2], uint32_t dst, int L)
 {
@@ -386,8 +393,8 @@ __device__ __forceinline__ void sweep_copy(const char *f, const char *d, const c
         constexpr int big = q / 4 * 4096, imm = q % 4 * 1024;
         const char *src = (isf ? f : isd ? d : v) + big;
         const uint32_t vo = (DIR == 0 && !isf) ? v8[q & 1] : vt[q & 1];
-        if (len >= 1024 || L < len / 16) lds_copy<imm>(vo, src, dst + at + big);
-        sweep_copy<DIR, T, c + 3>(f, d, v, vt, v8, dst, L);
+        if (len >= 1024 || L < len / 16) lds_copy<imm, NT>(vo, src, dst + at + big);
+        sweep_copy<DIR, T, NT, c + 3>(f, d, v, vt, v8, dst, L);
     }
 }
 
@@ -402,7 +409,7 @@ template <int Q> __device__ __forceinline__ double quad_get(double v)
                             __builtin_amdgcn_mov_dpp(__double2loint(v), Q * 0x55, 0xf, 0xf, true));
 }
 
-template <int DIR, typename T>
+template <int DIR, typename T, bool NT>
 __global__ __launch_bounds__(SW_THREADS) void k_sweep(SweepArgs a, SweepSrc<T> src, T *__restrict__ yout,
                                                double *__restrict__ zout)
 {
@@ -410,7 +417,7 @@ __global__ __launch_bounds__(SW_THREADS) void k_sweep(SweepArgs a, SweepSrc<T> s
     constexpr int W = C::W, RW = C::RW;
     extern __shared__ __align__(16) unsigned char smem[];
     const Geo &g = a.g;
-    const int nz = g.nz, NT = g.ntx * g.nty, nsteps = nz + 14, nst = nsteps + 1;
+    const int nz = g.nz, ntile = g.ntx * g.nty, nsteps = nz + 14, nst = nsteps + 1;
     constexpr int D = C::D;
     unsigned char *buf = smem + (size_t)D * C::SLOT;        // [parity][3][80]: 64 results, x face, y face
     int32_t *zb = (int32_t *)(buf + 2 * C::BUF);            // backward: [step % (2 SW_FACE)][64]
@@ -421,7 +428,7 @@ __global__ __launch_bounds__(SW_THREADS) void k_sweep(SweepArgs a, SweepSrc<T> s
     const int64_t frow = (int64_t)(nz + 7) * RW;
     auto take = [&]() -> uint64_t { return atomicAdd((unsigned long long *)a.ticket, 1ull) - a.ticket_base; };
     auto tile_of = [&](uint64_t tk) -> int32_t {
-        return tk >= (uint64_t)NT ? -1 : a.tile_order[DIR == 0 ? (int)tk : NT - 1 - (int)tk];
+        return tk >= (uint64_t)ntile ? -1 : a.tile_order[DIR == 0 ? (int)tk : ntile - 1 - (int)tk];
     };
     for (int e = threadIdx.x; e < 2 * C::BUF / 4; e += SW_THREADS) ((uint32_t *)buf)[e] = 0;
     if (threadIdx.x == 448) *next = tile_of(take());
@@ -555,7 +562,7 @@ __global__ __launch_bounds__(SW_THREADS) void k_sweep(SweepArgs a, SweepSrc<T> s
                 }
             }
             const uint32_t dst = base + (uint32_t)slot * C::SLOT;
-            sweep_copy<DIR, T, decltype(w)::value>(f, d, v, vt, v8, dst, L);
+            sweep_copy<DIR, T, NT, decltype(w)::value>(f, d, v, vt, v8, dst, L);
             slot = slot + 1 == D ? 0 : slot + 1;
             if (tl + 1 < nsteps) next_row();   // the empty step copies the last row again
             ++tl;
@@ -889,10 +896,10 @@ struct Bilu0 : PcImpl {
             face_words = (int64_t)NT * (g.nz + 7) * 24 * W;
             const size_t fb = (size_t)face_words * sizeof(uint64_t);
             // the sweeps keep a multi-slot ring in LDS: allow the full LDS per workgroup
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<0, double>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<1, double>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<0, float>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
-            RSV_HIP(c, hipFuncSetAttribute((const void *)k_sweep<1, float>, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
+            const void *fn[6] = {(const void *)k_sweep<0, double, false>, (const void *)k_sweep<1, double, false>,
+                                 (const void *)k_sweep<0, double, true>,  (const void *)k_sweep<1, double, true>,
+                                 (const void *)k_sweep<0, float, false>,  (const void *)k_sweep<1, float, false>};
+            for (const void *f : fn) RSV_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, c->lds_max));
             s = alloc((void **)&faceX, fb);
             if (s == RSV_OK) s = alloc((void **)&faceY, fb);
             if (s == RSV_OK) s = alloc((void **)&tile_order, (size_t)NT * sizeof(int32_t));
@@ -998,7 +1005,7 @@ struct Bilu0 : PcImpl {
             SweepSrc<float> s0{Lf32, (int64_t)27 * 64, 0, nullptr, 0, 0, r, nullptr, nullptr};
             size_t sh = SweepCfg<0, float>::BYTES;
             int t1 = prof_begin(c, RSV_K_ILU_FWD);
-            hipLaunchKernelGGL((k_sweep<0, float>), dim3(nw), dim3(SW_THREADS), sh, c->stream, a, s0,
+            hipLaunchKernelGGL((k_sweep<0, float, false>), dim3(nw), dim3(SW_THREADS), sh, c->stream, a, s0,
                                (float *)ybuf, (double *)nullptr);
             prof_end(c, t1);
             RSV_LAUNCH(c);
@@ -1006,17 +1013,23 @@ struct Bilu0 : PcImpl {
             SweepSrc<float> s1{U32, (int64_t)27 * 64, 0, Dinv32, (int64_t)9 * 64, 0, nullptr, (const float *)ybuf, zmap};
             sh = SweepCfg<1, float>::BYTES;
             int t2 = prof_begin(c, RSV_K_ILU_BWD);
-            hipLaunchKernelGGL((k_sweep<1, float>), dim3(nw), dim3(SW_THREADS), sh, c->stream, b, s1,
+            hipLaunchKernelGGL((k_sweep<1, float, false>), dim3(nw), dim3(SW_THREADS), sh, c->stream, b, s1,
                                (float *)nullptr, z);
             prof_end(c, t2);
             RSV_LAUNCH(c);
         } else {
+            // Factors that no cache holds until the next sweep are loaded without keeping
+            // (forward/backward us: 2.1 M slots 233/279 -> 223/275, 6.1 M 465/551 ->
+            // 423/537, 8.4 M 600/735 -> 558/703; 33.6 M, by placement, 1816 to 2023/2417
+            // to 2688 -> 1907/2470).  Below, 1.8 M in RAS's boxes: 125/160 -> 132/170.
+            // FP32 sweeps gain nothing (8.4 M 397/440 to 419/450, with it 407/445).
+            const bool nt = g.nslot >= SW_NT_SLOTS;
             SweepArgs a = sweep_args(nw);
             SweepSrc<double> s0{Lf, (int64_t)27 * 64, 0, nullptr, 0, 0, r, nullptr, nullptr};
             size_t sh = SweepCfg<0, double>::BYTES;
             int t1 = prof_begin(c, RSV_K_ILU_FWD);
-            hipLaunchKernelGGL((k_sweep<0, double>), dim3(nw), dim3(SW_THREADS), sh, c->stream, a, s0,
-                               (double *)ybuf, (double *)nullptr);
+            const auto fwd = nt ? k_sweep<0, double, true> : k_sweep<0, double, false>;
+            hipLaunchKernelGGL(fwd, dim3(nw), dim3(SW_THREADS), sh, c->stream, a, s0, (double *)ybuf, (double *)nullptr);
             prof_end(c, t1);
             RSV_LAUNCH(c);
             dump_trace(0);
@@ -1025,8 +1038,8 @@ struct Bilu0 : PcImpl {
                                 (const double *)ybuf, zmap};
             sh = SweepCfg<1, double>::BYTES;
             int t2 = prof_begin(c, RSV_K_ILU_BWD);
-            hipLaunchKernelGGL((k_sweep<1, double>), dim3(nw), dim3(SW_THREADS), sh, c->stream, b, s1,
-                               (double *)nullptr, z);
+            const auto bwd = nt ? k_sweep<1, double, true> : k_sweep<1, double, false>;
+            hipLaunchKernelGGL(bwd, dim3(nw), dim3(SW_THREADS), sh, c->stream, b, s1, (double *)nullptr, z);
             prof_end(c, t2);
             RSV_LAUNCH(c);
             dump_trace(1);

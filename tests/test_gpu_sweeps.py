@@ -1,6 +1,7 @@
 """Pipelined block sweeps at the edges of their steps and tiles: columns shorter
 and longer than the ring of operands and than a tile's diagonals, grids of more
-tiles than workgroups (a workgroup then goes from tile to tile), ragged tiles.
+tiles than workgroups (a workgroup then goes from tile to tile), ragged tiles,
+and 2^21 slots (factors loaded without keeping them in the caches).
 Against the sweep by hyperplanes: FP64 runs the same operations in the same
 order, so the bits are the same; FP32 lies within 4e-6 of the largest entry
 (each is allowed 2e-6 against the FP32 oracle)."""
@@ -25,7 +26,7 @@ def ctx():
 @pytest.mark.parametrize("fp32", [0, 1])
 @pytest.mark.parametrize("dims", [(1, 1, 1), (8, 8, 1), (9, 17, 2), (16, 16, 9), (8, 24, 10), (17, 9, 13), (25, 16, 14),
                                   (16, 31, 15), (24, 24, 16), (9, 9, 29), (139, 128, 1), (136, 133, 3), (200, 130, 12),
-                                  (131, 270, 21)])
+                                  (131, 270, 21), (128, 128, 128)])
 def test_steps_and_tiles(ctx, dims, fp32):
     from paper_1602_05901_amd import rsv
     print("sweeps", dims, fp32, flush=True)
