@@ -223,10 +223,13 @@ def hsfc_measure(rsv, ctx, g, dims, levels, nparts, reps=5, cpu=True):
     the equal-count cut, the partition quality), timed with events around
     each library call after one untimed pass; the oracle's keys and partition
     of the same grid timed on one host thread beside it.  Algorithmic bytes:
-    keys write 8 B per cell; each 8-bit pass of the radix sort reads the keys
-    for its histogram (8 B), then reads key and index (12 B, 8 B on the first
-    pass) and writes them (12 B); the cut reads the indices and writes the
-    parts (8 B)."""
+    keys write 8 B per cell; the cut by the digit trie (up to 4096 parts)
+    reads the keys at least twice, to count the root's digits and to give each
+    cell its part, and writes the parts (20 B; every further level that a cut
+    reaches reads them once more).  Above 4096 parts each 8-bit pass of the
+    radix sort reads the keys for its histogram (8 B), then reads key and index
+    (12 B, 8 B on the first pass) and writes them (12 B); the cut reads the
+    indices and writes the parts (8 B)."""
     import numpy as np
     import torch
     n = g.ncell
@@ -249,15 +252,16 @@ def hsfc_measure(rsv, ctx, g, dims, levels, nparts, reps=5, cpu=True):
             t["partition"].append(e[1].elapsed_time(e[2]) * 1e-3)
             t["quality"].append(e[2].elapsed_time(e[3]) * 1e-3)
     med = {k: float(np.median(v)) for k, v in t.items()}
-    part_bytes = n * (passes * 8 + (passes * 24 - 4) + 8)
+    trie = nparts <= 4096
+    part_bytes = n * (20 if trie else passes * 8 + (passes * 24 - 4) + 8)
     out = {"workload": f"Hilbert-curve partition of the {dims[0]}x{dims[1]}x{dims[2]} grid into {nparts} parts, "
-                       f"{levels} levels ({passes} radix passes)",
+                       f"{levels} levels ({'digit trie' if trie else f'{passes} radix passes'})",
            "keys_s": round(med["keys"], 6), "partition_s": round(med["partition"], 6),
            "quality_s": round(med["quality"], 6),
            "cells_per_s": round(n / (med["keys"] + med["partition"]), 1),
            "quality": {"load_imbalance": q[0], "max_local_surface_index": q[1], "global_surface_index": q[2],
                        "average_surface_index": q[3], "max_connectivity": int(q[4])},
-           "roofline": {"bound": "hbm", "kernel": "partition (histograms, scan, scatters, cut)",
+           "roofline": {"bound": "hbm", "kernel": "partition (trie counts, parts)" if trie else "partition (histograms, scan, scatters, cut)",
                         "achieved": round(part_bytes / med["partition"] / 1e9, 1), "peak": HBM_PEAK_GBS,
                         "unit": "GB/s", "frac": round(part_bytes / med["partition"] / 1e9 / HBM_PEAK_GBS, 4),
                         "traffic": None, "algorithmic_bytes": part_bytes}}
