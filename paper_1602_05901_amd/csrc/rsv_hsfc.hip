@@ -222,9 +222,12 @@ __global__ __launch_bounds__(256) void k_assign_parts(const uint32_t *__restrict
 // Each level that has nodes reads the keys once (8 bytes a cell) and the last
 // pass writes the parts, against 4 x 32 bytes a cell and scattered writes for
 // the sort of a 30-bit key, whose 0.8 GB of buffers were allocated and freed in
-// every call: keys and cut of 33.5 M cells into 64 parts 4.23 -> 0.44 ms, of
-// which the keys are 0.22 (there every cut falls on an octant and the root
-// decides it; each further level that is reached adds about 0.06).
+// every call: keys and cut of 33.5 M cells in grid order into 64 parts 4.23 ->
+// 0.44 ms, of which the keys are 0.22 (there every cut falls on an octant and
+// the root decides it; each further level that is reached adds about 0.06).
+// Keys in no order, 30 M at 10 levels, 64 / 4096 parts, sort / trie in ms: spread
+// over the cube 4.5 / 0.36, 4.5 / 2.3; 200 values in five crowds 3.3 / 1.0,
+// 3.2 / 2.9; two values 2.3 / 0.67, 2.3 / 1.1.
 constexpr int TRIE_PARTS = 4096;      // most parts the trie takes
 constexpr int TRIE_TOP = 12;          // digit bits of the root
 constexpr int TRIE_ROWS_BITS = 20;    // log2 of the most entries a level may have
@@ -268,17 +271,24 @@ __global__ __launch_bounds__(256) void k_trie_reset(Trie t, int64_t words)
 
 // The cells' counts at level l.  Cells in grid order change their leading
 // digits rarely, so neighbouring lanes mostly count the same entry: the first
-// lane of each run of equal entries adds the run's length.  The root's 4096
-// entries are counted in LDS first.
+// lane of each run of equal entries adds the run's length.  Counts are gathered
+// in LDS first: the root's 4096 entries one to one, a lower level's through a
+// direct-mapped table of as many (entry, count) pairs, past which an entry goes
+// whose place another one holds.  Keys in no order that crowd under a few cut
+// prefixes would otherwise all meet at a few addresses in memory, about 5 ns an
+// addition (30 M keys of two values at 10 levels, 64 parts: 176 ms, 0.67 with the
+// table).
 template <bool ROOT>
 __global__ __launch_bounds__(512) void k_trie_count(Trie t, int l, int64_t n, const uint64_t *__restrict__ keys)
 {
-    __shared__ uint32_t h[ROOT ? 1 << TRIE_TOP : 1];
+    __shared__ uint32_t h[1 << TRIE_TOP];
+    __shared__ int32_t tag[ROOT ? 1 : 1 << TRIE_TOP];   // entry counted at a place, -1: none
     if (!ROOT && t.nodes[l] == 0) return;
-    if (ROOT) {
-        for (int e = threadIdx.x; e < 1 << TRIE_TOP; e += 512) h[e] = 0;
-        __syncthreads();
+    for (int e = threadIdx.x; e < 1 << TRIE_TOP; e += 512) {
+        h[e] = 0;
+        if (!ROOT) tag[e] = -1;
     }
+    __syncthreads();
     const int lane = threadIdx.x & 63;
     const uint64_t after = lane == 63 ? 0ull : ~0ull << (lane + 1);
     constexpr int U = 4;
@@ -309,17 +319,22 @@ __global__ __launch_bounds__(512) void k_trie_count(Trie t, int l, int64_t n, co
             const uint64_t heads = __ballot(head) & after;
             const uint32_t len = (uint32_t)((heads ? __ffsll((unsigned long long)heads) - 1 : 64) - lane);
             if (head && at >= 0) {
-                if (ROOT) atomicAdd(&h[at], len);
-                else atomicAdd(&t.count[at], len);
+                if (ROOT) {
+                    atomicAdd(&h[at], len);
+                } else {
+                    const uint32_t q = ((uint32_t)at * 2654435761u) >> (32 - TRIE_TOP);
+                    int32_t who = tag[q];
+                    if (who < 0) who = atomicCAS(&tag[q], -1, at);
+                    if (who < 0 || who == at) atomicAdd(&h[q], len);
+                    else atomicAdd(&t.count[at], len);
+                }
             }
         }
     }
-    if (ROOT) {
-        if (above) *t.stray = 1;
-        __syncthreads();
-        for (int e = threadIdx.x; e < 1 << TRIE_TOP; e += 512)
-            if (h[e]) atomicAdd(&t.count[e], h[e]);
-    }
+    if (ROOT && above) *t.stray = 1;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 1 << TRIE_TOP; e += 512)
+        if (h[e]) atomicAdd(&t.count[ROOT ? e : tag[e]], h[e]);
 }
 
 // Entries of a level from its counts, one workgroup per node: ranks by an
@@ -640,8 +655,10 @@ rsv_status rsv_hsfc_partition(rsv_ctx *c, int64_t n, const uint64_t *keys, int32
     if (n > ((int64_t)1 << 31)) return set_err(c, RSV_ERR_ARG, "at most 2^31 keys");
     if (n == 0) return RSV_OK;
     // Up to 4096 parts a node of the trie keeps at least 8 digit bits within
-    // 2^20 entries a level; each level reads all keys once, so with more parts
-    // (fewer bits, more levels) the sort's fixed passes are the better choice.
+    // 2^20 entries a level.  Each level reads all keys once, and more parts mean
+    // fewer bits and more levels: for 30 M keys in five crowds at 10 levels the sort
+    // and the trie take 3.25 and 2.9 ms at 4096 parts, 3.23 and 3.2 at 8192, 3.24
+    // and 4.3 at 16384 (sorted keys: 3.95 and 0.75, 0.80, 0.94).
     if (nparts <= TRIE_PARTS) {
         uint32_t stray = 0;
         const rsv_status st = trie_partition(c, n, keys, levels, nparts, part, &stray);

@@ -6,6 +6,7 @@ quality measures to FP64 rounding of their sums.  Sizes span one tile of the
 radix sort up to the 512x512x128 grid, with heavy key ties (few levels) and
 the longest keys (21 levels, 8 sort passes)."""
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -197,3 +198,35 @@ def test_cut_equals_a_stable_sort(rsv, ctx, n, levels, nparts, kind):
     ref = np.empty(n, np.int32)
     ref[order] = (np.arange(n, dtype=np.int64) * nparts) // n
     assert np.array_equal(part.cpu().numpy(), ref)
+
+
+def test_crowded_keys_in_no_order(rsv, ctx):
+    """Keys in no order that crowd under a few prefixes: the cut is the stable
+    sort's, and its time stays near that of spread keys.  At 10 levels and 3 M
+    cells the trie has five levels (12 + 12 + 6 key bits, 12 + 10 index bits),
+    each one read of the keys; spread keys need at least the first, so five
+    times their time, and as much again for the walk down the levels."""
+    n, levels, nparts = 3_000_000, 10, 64
+    log("crowded keys", n, levels, nparts)
+    r = np.random.default_rng(5)
+    top = 1 << (3 * levels)
+    part = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+
+    def cut(k):
+        keys = torch.from_numpy(k.view(np.int64)).cuda()
+        best = 1e9
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            rsv.hsfc_partition(ctx, keys, levels, nparts, part)
+            best = min(best, time.perf_counter() - t0)
+        ref = np.empty(n, np.int32)
+        ref[np.argsort(k, kind="stable")] = (np.arange(n, dtype=np.int64) * nparts) // n
+        assert np.array_equal(part.cpu().numpy(), ref)
+        return best
+
+    spread = cut(r.integers(0, top, n, dtype=np.uint64))
+    two = cut((r.integers(0, 2, n) * (top // 3) + 5).astype(np.uint64))
+    crowds = cut((r.integers(0, 5, n) * (top // 7) + r.integers(0, 40, n)).astype(np.uint64))
+    log("  us: spread %.0f, two values %.0f, five crowds %.0f" % (spread * 1e6, two * 1e6, crowds * 1e6))
+    assert max(two, crowds) <= 10 * spread
