@@ -659,7 +659,11 @@ rsv_status rsv_hsfc_partition(rsv_ctx *c, int64_t n, const uint64_t *keys, int32
     // fewer bits and more levels: for 30 M keys in five crowds at 10 levels the sort
     // and the trie take 3.25 and 2.9 ms at 4096 parts, 3.23 and 3.2 at 8192, 3.24
     // and 4.3 at 16384 (sorted keys: 3.95 and 0.75, 0.80, 0.94).
-    if (nparts <= TRIE_PARTS) {
+    // The sort reads its own copies after its first pass, so part may lie on keys;
+    // the trie reads keys while it writes part.
+    const uintptr_t k0 = (uintptr_t)keys, p0 = (uintptr_t)part;
+    const bool apart = p0 + (uintptr_t)n * 4 <= k0 || k0 + (uintptr_t)n * 8 <= p0;
+    if (nparts <= TRIE_PARTS && apart) {
         uint32_t stray = 0;
         const rsv_status st = trie_partition(c, n, keys, levels, nparts, part, &stray);
         if (st != RSV_OK || !stray) return st;

@@ -230,3 +230,18 @@ def test_crowded_keys_in_no_order(rsv, ctx):
     crowds = cut((r.integers(0, 5, n) * (top // 7) + r.integers(0, 40, n)).astype(np.uint64))
     log("  us: spread %.0f, two values %.0f, five crowds %.0f" % (spread * 1e6, two * 1e6, crowds * 1e6))
     assert max(two, crowds) <= 10 * spread
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2001, 4000])
+def test_part_on_the_keys(rsv, ctx, offset):
+    """part may lie on the keys' own memory (here `offset` 32-bit words into
+    it): the cut is as with buffers of their own."""
+    n, levels, nparts = 4001, 10, 64
+    log("part on keys", offset)
+    k = np.random.default_rng(6).integers(0, 1 << (3 * levels), n, dtype=np.uint64)
+    keys = torch.from_numpy(k.view(np.int64)).cuda()
+    part = keys.view(torch.int32)[offset:offset + n]
+    rsv.hsfc_partition(ctx, keys, levels, nparts, part)
+    ref = np.empty(n, np.int32)
+    ref[np.argsort(k, kind="stable")] = (np.arange(n, dtype=np.int64) * nparts) // n
+    assert np.array_equal(part.cpu().numpy(), ref)
