@@ -666,7 +666,8 @@ rsv_status rsv_hsfc_partition(rsv_ctx *c, int64_t n, const uint64_t *keys, int32
     if (nparts <= TRIE_PARTS && apart) {
         uint32_t stray = 0;
         const rsv_status st = trie_partition(c, n, keys, levels, nparts, part, &stray);
-        if (st != RSV_OK || !stray) return st;
+        // few cells in many parts: the sort's 24 bytes a cell may still fit
+        if (st != RSV_ERR_OOM && (st != RSV_OK || !stray)) return st;
     }
     const int64_t ntile = (n + RS_TILE - 1) / RS_TILE;
     Tmp t;
