@@ -171,109 +171,196 @@ __global__ __launch_bounds__(RED_T) void k_reduce(const double *__restrict__ par
     if (threadIdx.x == 0) out[kk] = s;
 }
 
-// Caller order -> tile-lane order and back.  A tile-lane row holds 64 cells of
-// one hyperplane, 64 separate 24-byte pieces of the caller's vector, so one
-// lane per cell made 64 requests of every load or store (567 us in and 1100 us
-// out at 512x512x128; 315 and 315 us, 5.1 TB/s, in runs).  A workgroup takes PR rows of a tile and moves the caller's
-// side in x-runs: cells i = 0..7 of a grid line (j, k) are 192 contiguous
-// bytes, and run (j, u) with u = k + j - r0 holds the cells of rows r0 + u + i.
-// LDS turns runs into rows.  Ranges of workgroups are contiguous per XCD: a run
-// cut between two workgroups of a column shares its lines in one L2.
+// Caller order -> tile-lane order and back, one lane per cell: the form of grids
+// whose caller's vector (24 bytes a cell) stays in an L2 of 4 MB, where the length
+// of a workgroup is what counts.
+constexpr int64_t CELL_MOVES = ((int64_t)4 << 20) / 24;   // cells at most
+
+__global__ __launch_bounds__(BS) void k_nat_to_tl_cell(Geo g, const double *__restrict__ nat, double *__restrict__ tl)
+{
+    const int64_t slot = (int64_t)blockIdx.x * BS + threadIdx.x;
+    if (slot >= g.nslot) return;
+    int gx, gy, k;
+    const bool real = cell_of(g, slot, gx, gy, k);
+    const int64_t row = real ? row_of(g, gx, gy, k) : 0;
+    for (int p = 0; p < 3; ++p) tl[vidx(slot, p)] = real ? nat[3 * row + p] : 0.0;
+}
+
+__global__ __launch_bounds__(BS) void k_tl_to_nat_cell(Geo g, const double *__restrict__ tl, double *__restrict__ nat,
+                                                       double alpha, double beta)
+{
+    const int64_t slot = (int64_t)blockIdx.x * BS + threadIdx.x;
+    if (slot >= g.nslot) return;
+    int gx, gy, k;
+    if (!cell_of(g, slot, gx, gy, k)) return;
+    const int64_t row = row_of(g, gx, gy, k);
+    for (int p = 0; p < 3; ++p) {
+        double v = alpha * tl[vidx(slot, p)];
+        if (beta != 0.0) v += beta * nat[3 * row + p];
+        nat[3 * row + p] = v;
+    }
+}
+
+// The same for larger grids.  A tile-lane row holds 64 cells of one hyperplane, 64
+// separate 24-byte pieces of the caller's vector, so one lane per cell makes 64
+// requests of every load or store.  A workgroup takes PR rows of a tile and moves
+// the caller's side in x-runs: cells i = 0..7 of a grid line (j, k) are 192
+// contiguous bytes, which a group of 24 threads moves.  LDS turns runs into rows.
+// Ranges of workgroups are contiguous per XCD: a run cut between two workgroups of
+// a column shares its lines in one L2.
+//
+// WHOLE (at most PR layers): the rows are those of tpw whole tiles, neighbours in x,
+// so every run is used in full, and tiles of a few layers share a workgroup.  Else
+// run (j, u) with u = k + j - r0 holds the cells of rows r0 + u + i, and those at
+// either end are used in part.
+//
+// Bound by memory: in + out 565 + 1105 us by cells and 342 + 317 by runs (4.9 TB/s) at
+// 512 x 512 x 128, 127 + 253 and 89 + 75 at 256 x 256 x 128, 55 + 116 and 41 + 37 at
+// 1024 x 1024 x 4, 37 + 50 and 43 + 36 at 2048 x 2048 x 1.  64 x 64 x 64, 256
+// workgroups: 6.7 + 7.2 by cells, 8.4 + 4.8 by runs with GRP = 32 groups, 9.5 + 5.6 with
+// 16; below, the runs' index arithmetic and barrier are longer than the move: 130 x 130
+// x 5 4.6 + 4.4 and 6.0 + 4.2, 20 x 20 x 10 3.1 + 3.0 and 4.1 + 3.4.
 constexpr int PR = 16;                       // rows per workgroup
 constexpr int PR_U = PR + 7;                 // runs of one grid line that meet them
-constexpr int PR_IT = (8 * PR_U + BS / 24 - 1) / (BS / 24);
 
-// v mod nz for v in [-15, nz + 15]
+// v mod nz for v in [-15, nz + 15], nz >= 16
 __device__ __forceinline__ int wrap_near(int v, int nz)
 {
-    if (nz < 16) return wrap_nz(v, nz);
     v += v < 0 ? nz : 0;
     return v - (v >= nz ? nz : 0);
 }
 
-// Thread part of the runs: entry e of the runs it = 0, 1, ..., eight or more
-// threads' groups taking one run each.  Every index fits 32 bits (a grid has
-// at most 2^31 / 3 padded cells).
-struct Runs {
-    int e, i, first, nr, r0, nx, ny, nz, gx0, gy0, ntop;
+// A workgroup's rows, and its threads' parts of the runs: entry e of the runs it =
+// 0, 1, ..., one run per group.  Every index fits 32 bits (a grid has at most 2^31 / 3
+// padded cells).
+template <int GRP, bool WHOLE> struct Runs {
+    static constexpr int IT = WHOLE ? 8 * PR / GRP : (8 * PR_U + GRP - 1) / GRP;
+    int T0, row0, nrow;                      // first tile; first row, of all tiles'; rows
+    int e, i, first, step, n, tt, r0, rec, nu, nx, ny, nz, ntx, gx0, gy0, ntop;
     bool ok;
-    __device__ __forceinline__ Runs(const Geo &g, int T, int r0_, int nr_)
+    __device__ __forceinline__ Runs(const Geo &g, int nchunk, int tpw)
     {
+        const int wg = (int)xcd_block(blockIdx.x, gridDim.x);
         e = threadIdx.x % 24;
         i = e / 3;
-        first = threadIdx.x / 24;
-        r0 = r0_; nr = nr_;
-        nx = g.nx; ny = g.ny; nz = g.nz;
-        gx0 = (T % g.ntx) * 8;
-        gy0 = (T / g.ntx) * 8;
+        const int grp = threadIdx.x / 24;
+        nx = g.nx; ny = g.ny; nz = g.nz; ntx = g.ntx;
         ntop = g.ordering == RSV_TOP_DOWN ? nz - 1 : -1;
-        ok = threadIdx.x < BS / 24 * 24 && gx0 + i < nx;
+        if constexpr (WHOLE) {
+            T0 = wg * tpw;
+            row0 = T0 * nz;
+            nrow = min(tpw, g.ntx * g.nty - T0) * nz;
+            tt = grp & (tpw - 1);
+            first = grp / tpw;
+            step = GRP / tpw;
+            n = 8 * nz;
+            rec = (65536 + nz - 1) / nz;     // s / nz = s rec >> 16 for the s < 30 here
+            ok = tt * nz < nrow;
+        } else {
+            T0 = wg / nchunk;
+            r0 = (wg - T0 * nchunk) * PR;
+            row0 = T0 * nz + r0;
+            nrow = min(PR, nz - r0);
+            tt = 0;
+            first = grp;
+            step = GRP;
+            nu = nrow + 7;
+            n = min(8, ny - T0 / ntx * 8) * nu;
+            rec = (65536 + nu - 1) / nu;     // exact for the q < 192 here
+            ok = true;
+        }
+        gx0 = (T0 + tt) % ntx * 8;
+        gy0 = (T0 + tt) / ntx * 8;
+        ok = ok && gx0 + i < nx;
     }
     // place of the entry of iteration `it` in the rows' LDS copy [row][cell 8 j + i][3]
     // and in the caller's vector; false outside the rows or the grid
     __device__ __forceinline__ bool at(int it, int &lds, int &nat) const
     {
-        const int q = it * (BS / 24) + first, j = q / PR_U, u = q - j * PR_U - 7, v = u + i;
-        int k = wrap_near(r0 + u - j, nz);
+        const int q = first + it * step;
+        int j, k, v;
+        bool in = ok && q < n;
+        if constexpr (WHOLE) {
+            j = q & 7;
+            k = q >> 3;
+            v = k + i + j;
+            v += (tt - (v * rec >> 16)) * nz;
+            in = in && gy0 + j < ny;
+        } else {
+            j = q * rec >> 16;
+            const int u = q - j * nu;
+            v = u - 7 + i;
+            k = wrap_near(r0 + u - 7 - j, nz);
+            in = in && (unsigned)v < (unsigned)nrow;
+        }
         if (ntop >= 0) k = ntop - k;
         lds = (v * 64 + j * 8) * 3 + e;
         nat = 3 * ((k * ny + gy0 + j) * nx + gx0) + e;
-        return ok && j < 8 && v >= 0 && v < nr && gy0 + j < ny;
+        return in;
     }
+    // iteration `it` has a run (for some thread)
+    __device__ __forceinline__ bool any(int it) const { return it * step < n; }
+    // cells of the thread's tile in x, and in y in the next byte
+    __device__ __forceinline__ int cells() const { return min(8, nx - gx0) | min(8, ny - gy0) << 8; }
 };
 
-__global__ __launch_bounds__(BS) void k_nat_to_tl(Geo g, int nchunk, const double *__restrict__ nat,
-                                                  double *__restrict__ tl)
+template <int GRP, bool WHOLE>
+__global__ __launch_bounds__(24 * GRP) void k_nat_to_tl(Geo g, int nchunk, int tpw, const double *__restrict__ nat,
+                                                        double *__restrict__ tl)
 {
+    using R_ = Runs<GRP, WHOLE>;
     __shared__ double rows[PR * 64 * 3];
-    const int64_t wg = xcd_block(blockIdx.x, gridDim.x);
-    const int T = (int)(wg / nchunk), r0 = (int)(wg - (int64_t)T * nchunk) * PR, nr = min(PR, g.nz - r0);
-    const Runs R(g, T, r0, nr);
-    double v[PR_IT];
-    int at[PR_IT];
+    __shared__ int cells[PR];    // of each tile
+    const R_ R(g, nchunk, tpw);
+    double v[R_::IT];
+    int at[R_::IT];
 #pragma unroll
-    for (int q = 0; q < PR_IT; ++q) {
-        int src, a;
-        const bool in = R.at(q, a, src);
+    for (int q = 0; q < R_::IT; ++q) {
+        int src = 0, a = 0;
+        const bool in = R.any(q) && R.at(q, a, src);
         at[q] = in ? a : -1;
         v[q] = in ? nat[src] : 0.0;
     }
+    const int L = threadIdx.x & 63;
+    int i, j;
+    lane_ij(L, i, j);
+    if (WHOLE && R.e == 0 && R.first == 0) cells[R.tt] = R.cells();
 #pragma unroll
-    for (int q = 0; q < PR_IT; ++q)
+    for (int q = 0; q < R_::IT; ++q)
         if (at[q] >= 0) rows[at[q]] = v[q];
     __syncthreads();
-    const int L = threadIdx.x & 63;
-    int i, j;
-    lane_ij(L, i, j);
-    const bool real = R.gx0 + i < g.nx && R.gy0 + j < g.ny;
-    for (int r = threadIdx.x >> 6; r < nr; r += BS / 64)
+    for (int r = threadIdx.x >> 6; r < R.nrow; r += 24 * GRP / 64) {
+        const int m = WHOLE ? cells[r * R.rec >> 16] : R.cells();
+        const bool real = i < (m & 255) && j < m >> 8;
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            tl[((int64_t)T * g.nz + r0 + r) * 192 + c * 64 + L] = real ? rows[(r * 64 + j * 8 + i) * 3 + c] : 0.0;
+            tl[(int64_t)(R.row0 + r) * 192 + c * 64 + L] = real ? rows[(r * 64 + j * 8 + i) * 3 + c] : 0.0;
+    }
 }
 
-__global__ __launch_bounds__(BS) void k_tl_to_nat(Geo g, int nchunk, const double *__restrict__ tl,
-                                                  double *__restrict__ nat, double alpha, double beta)
+template <int GRP, bool WHOLE>
+__global__ __launch_bounds__(24 * GRP) void k_tl_to_nat(Geo g, int nchunk, int tpw, const double *__restrict__ tl,
+                                                        double *__restrict__ nat, double alpha, double beta)
 {
+    using R_ = Runs<GRP, WHOLE>;
+    constexpr int NW = 24 * GRP / 64;
     __shared__ double rows[PR * 64 * 3];
-    const int64_t wg = xcd_block(blockIdx.x, gridDim.x);
-    const int T = (int)(wg / nchunk), r0 = (int)(wg - (int64_t)T * nchunk) * PR, nr = min(PR, g.nz - r0);
+    const R_ R(g, nchunk, tpw);
     const int L = threadIdx.x & 63;
     int i, j;
     lane_ij(L, i, j);
 #pragma unroll
-    for (int q = 0; q < PR / (BS / 64); ++q) {
-        const int r = (threadIdx.x >> 6) + q * (BS / 64);
+    for (int q = 0; q < (PR + NW - 1) / NW; ++q) {
+        const int r = (threadIdx.x >> 6) + q * NW;
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            if (r < nr) rows[(r * 64 + j * 8 + i) * 3 + c] = tl[((int64_t)T * g.nz + r0 + r) * 192 + c * 64 + L];
+            if (r < R.nrow) rows[(r * 64 + j * 8 + i) * 3 + c] = tl[(int64_t)(R.row0 + r) * 192 + c * 64 + L];
     }
     __syncthreads();
-    const Runs R(g, T, r0, nr);
-#pragma unroll 5
-    for (int q = 0; q < PR_IT; ++q) {
+#pragma unroll
+    for (int q = 0; q < R_::IT; ++q) {
         int dst, a;
-        if (!R.at(q, a, dst)) continue;
+        if (!R.any(q) || !R.at(q, a, dst)) continue;
         double v = alpha * rows[a];
         if (beta != 0.0) v += beta * nat[dst];
         nat[dst] = v;
@@ -746,18 +833,48 @@ rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, cons
     return RSV_OK;
 }
 
+// Launch shape of the moves by runs: tiles per workgroup (whole tiles) or chunks of
+// PR rows per tile, workgroups, and whether these are few (two per CU).
+struct MoveShape {
+    int nchunk, tpw, nwg;
+    bool whole, wide;
+};
+static MoveShape move_shape(const rsv_ctx *c, const Geo &g)
+{
+    MoveShape m{(g.nz + PR - 1) / PR, 1, 0, g.nz <= PR, false};
+    const int nt = g.ntx * g.nty, few = 2 * c->num_cu;
+    if (m.whole)
+        while (2 * m.tpw * g.nz <= PR && nt / (2 * m.tpw) >= few) m.tpw *= 2;
+    m.nwg = m.whole ? (nt + m.tpw - 1) / m.tpw : nt * m.nchunk;
+    m.wide = m.nwg < few;
+    return m;
+}
+
 rsv_status launch_nat_to_tl(rsv_ctx *c, const Geo &g, const double *nat, double *tl)
 {
-    const int nchunk = (g.nz + PR - 1) / PR;
-    hipLaunchKernelGGL(k_nat_to_tl, dim3((unsigned)(g.ntx * g.nty * nchunk)), dim3(BS), 0, c->stream, g, nchunk, nat, tl);
+    if (g.nslot <= CELL_MOVES) {
+        hipLaunchKernelGGL(k_nat_to_tl_cell, dim3(spmv_blocks(g)), dim3(BS), 0, c->stream, g, nat, tl);
+    } else {
+        const MoveShape m = move_shape(c, g);
+        const auto fn = m.whole ? (m.wide ? k_nat_to_tl<32, true> : k_nat_to_tl<16, true>)
+                                : (m.wide ? k_nat_to_tl<32, false> : k_nat_to_tl<16, false>);
+        hipLaunchKernelGGL(fn, dim3((unsigned)m.nwg), dim3(m.wide ? 768 : 384), 0, c->stream, g, m.nchunk, m.tpw, nat, tl);
+    }
     RSV_LAUNCH(c);
     return RSV_OK;
 }
 
 rsv_status launch_tl_to_nat(rsv_ctx *c, const Geo &g, const double *tl, double *nat, double alpha, double beta)
 {
-    const int nchunk = (g.nz + PR - 1) / PR;
-    hipLaunchKernelGGL(k_tl_to_nat, dim3((unsigned)(g.ntx * g.nty * nchunk)), dim3(BS), 0, c->stream, g, nchunk, tl, nat, alpha, beta);
+    if (g.nslot <= CELL_MOVES) {
+        hipLaunchKernelGGL(k_tl_to_nat_cell, dim3(spmv_blocks(g)), dim3(BS), 0, c->stream, g, tl, nat, alpha, beta);
+    } else {
+        const MoveShape m = move_shape(c, g);
+        const auto fn = m.whole ? (m.wide ? k_tl_to_nat<32, true> : k_tl_to_nat<16, true>)
+                                : (m.wide ? k_tl_to_nat<32, false> : k_tl_to_nat<16, false>);
+        hipLaunchKernelGGL(fn, dim3((unsigned)m.nwg), dim3(m.wide ? 768 : 384), 0, c->stream, g, m.nchunk, m.tpw, tl, nat,
+                           alpha, beta);
+    }
     RSV_LAUNCH(c);
     return RSV_OK;
 }
