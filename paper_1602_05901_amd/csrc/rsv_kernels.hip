@@ -806,10 +806,7 @@ rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, cons
     dim3 grid(nb), block(BS);
     double *P = c->d_partials;
     const int tok = prof_begin(c, RSV_K_SPMV);
-    // Matrices are read once per product: where the vectors around it fit the 256 MB
-    // cache behind the L2s, the matrix is loaded without keeping (1 M cells 109 -> 97
-    // us, 8.4 M, 201 MB per vector, 836 -> 818; 33.5 M 3422 -> 3471).
-    const bool nt = once_through(g.nslot * 3);
+    const bool nt = once_through(g.nslot * 3, (int64_t)g.nx * g.ny * g.nz * 504);
 #define L_SPMV(M)                                                                                          \
     case M:                                                                                                \
         if (nt)                                                                                            \
