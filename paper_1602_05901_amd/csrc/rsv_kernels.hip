@@ -545,7 +545,8 @@ __global__ __launch_bounds__(BS) void k_mdot(int64_t n, const double *__restrict
 // The pair gives the same bits as w -= V c1; dots; w -= V c2; norm, but the
 // second pass only reads: a pass that also writes a stream runs at about
 // 5 TB/s on this part, one that only reads at about 6.2.
-template <int KB, int MODE, bool FOLD>
+// NT (MODE 1): the basis is loaded without keeping.
+template <int KB, int MODE, bool FOLD, bool NT>
 __global__ __launch_bounds__(BS) void k_upd(int64_t n, const double *__restrict__ V, int64_t ldv, int K,
                                             double *__restrict__ w, double *__restrict__ c1,
                                             double *__restrict__ c2, double *__restrict__ partials,
@@ -567,16 +568,14 @@ __global__ __launch_bounds__(BS) void k_upd(int64_t n, const double *__restrict_
     // first one read last, and the third with what the second read last: as much of
     // the basis as the 256 MB cache behind the dies' L2s still holds is not read
     // from HBM again.  Same elements and partials per block, so the same bits.
-    // 3.1 M entries, 17 to 24 vectors: second pass 93 -> 86 us, third 107 -> 96.  Nobody
-    // reads the basis soon after the third: it loads without keeping (25 M entries:
-    // 902 -> 857 us).
+    // 3.1 M entries, 17 to 24 vectors: second pass 93 -> 86 us, third 107 -> 96.
     const int64_t bx = MODE == 0 ? (int64_t)gridDim.x - 1 - blockIdx.x : (int64_t)blockIdx.x;
     for (int64_t e = bx * BS + threadIdx.x; e < n; e += (int64_t)gridDim.x * BS) {
         double v[KB];
 #pragma unroll
         for (int i = 0; i < KB; ++i) {
             const double *p = V + vrow(i, K, ldv) + e;
-            v[i] = MODE == 1 ? __builtin_nontemporal_load(p) : *p;
+            v[i] = NT ? __builtin_nontemporal_load(p) : *p;
         }
         double we = w[e];
 #pragma unroll
@@ -967,17 +966,26 @@ rsv_status launch_cgs2(rsv_ctx *c, int64_t n, const double *V, int64_t ldv, int 
                        (const double *)p0, nb0, c->d_scal + SC_W0)
 #define L_UPD(KB)                                                                                                       \
     if (fold)                                                                                                           \
-        hipLaunchKernelGGL((k_upd<KB, 0, true>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p2,         \
+        hipLaunchKernelGGL((k_upd<KB, 0, true, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p2,         \
                            (const double *)p1);                                                                         \
     else                                                                                                                \
-        hipLaunchKernelGGL((k_upd<KB, 0, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p2,        \
+        hipLaunchKernelGGL((k_upd<KB, 0, false, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p2,        \
                            (const double *)nullptr)
+    // A basis beyond the 256 MB cache is gone before the next step's first pass comes to
+    // it, so the third loads it without keeping (25 M entries, 17 to 24 vectors: 902 ->
+    // 857 us); a smaller one is kept for it (mean of a step's kernels over 30 steps, us,
+    // kept and not: 262 k entries 11.1 and 11.5, 786 k 19.4 and 20.4, 1 M 21.9 and 23.1;
+    // 4.1 M 78.2 and 77.5).
+    const bool nt = (int64_t)K * n * (int64_t)sizeof(double) > (int64_t)256 << 20;
 #define L_UPDN(KB)                                                                                                      \
     if (fold)                                                                                                           \
-        hipLaunchKernelGGL((k_upd<KB, 1, true>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3,         \
+        hipLaunchKernelGGL((k_upd<KB, 1, true, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3,  \
                            (const double *)p2);                                                                         \
+    else if (nt)                                                                                                        \
+        hipLaunchKernelGGL((k_upd<KB, 1, false, true>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3,  \
+                           (const double *)nullptr);                                                                    \
     else                                                                                                                \
-        hipLaunchKernelGGL((k_upd<KB, 1, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3,        \
+        hipLaunchKernelGGL((k_upd<KB, 1, false, false>), dim3(nb), dim3(BS), 0, c->stream, n, V, ldv, K, w, h1, h2, p3, \
                            (const double *)nullptr)
     {
         ProfScope ps(c, RSV_K_ORTHO);
