@@ -77,35 +77,43 @@ __device__ __forceinline__ void bwd_cell(const T *u, const T *dd, const T *vx, c
 
 // ---------------------------------------------------------------- hyperplanes
 // Hyperplane p of a grid of boxes: the cells with (i mod mx) + (j mod my) +
-// (k mod mz) = p.  Thread t of a launch takes column t mod (64 tiles) of the
-// boxes' layer t / (64 tiles), which holds at most one cell of p; a wave's
-// columns are one tile's lanes, whose cells of p share a row.  (Lists of each
-// plane's slots, built on the host with every grid and auxiliary grid, were 12
-// of the 14.7 ms of a RAS setup at 128x128x64, which takes 2.4 ms without.)
+// (k mod mz) = p.  A wave of a launch takes one tile of one box (plane_tiles), whose
+// cells of p share a row.  (Lists of each plane's slots, built on the host with every
+// grid and auxiliary grid, were 12 of the 14.7 ms of a RAS setup at 128x128x64,
+// which takes 2.4 ms without.)
 struct Planes {
     Geo g;
-    int mx, my, mz, p;
+    PlaneTiles t;
+    int mz, p, d;            // d: first row of the launch
+    int nbx, nbox, nunit;    // boxes in x, in a layer of boxes, in all
 };
-inline unsigned plane_blocks(const rsv_grid *G)
-{
-    const int64_t n = (int64_t)G->geo.ntx * G->geo.nty * 64 * ((G->geo.nz + G->mz - 1) / G->mz);
-    return (unsigned)((n + BS - 1) / BS);
-}
 __device__ inline bool plane_cell(const Planes &P, int &gx, int &gy, int &k, int64_t &slot)
 {
-    const int64_t t = (int64_t)blockIdx.x * BS + threadIdx.x, layer = (int64_t)P.g.ntx * P.g.nty * 64;
-    const int zb = (int)(t / layer), T = (int)((t - zb * layer) >> 6);
-    const int x0 = (T % P.g.ntx) * 8, y0 = (T / P.g.ntx) * 8;
-    const int q = P.p - x0 % P.mx - y0 % P.my;   // k mod mz of the tile's lane (0, 0)
+    int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (BS / 64) + (threadIdx.x >> 6)));
+    int unit = 0, zb = 0, tx, ty;
+    if (P.nunit > 1) {
+        unit = w / P.t.row;
+        w -= unit * P.t.row;
+        if (unit >= P.nunit) return false;
+    }
+    if (!plane_tile(P.t, w, P.d + (int)blockIdx.y, tx, ty)) return false;
+    const int q = P.p - 8 * (tx + ty);   // k mod mz of the tile's lane (0, 0)
     if (q < 0 || q >= P.mz + 14) return false;
+    if (P.nunit > 1) {
+        zb = unit / P.nbox;
+        const int box = unit - zb * P.nbox, by = box / P.nbx;
+        tx += (box - by * P.nbx) * P.t.btx;
+        ty += by * P.t.bty;
+    }
     int i, j;
-    lane_ij((int)(t & 63), i, j);
-    gx = x0 + i;
-    gy = y0 + j;
+    lane_ij((int)(threadIdx.x & 63), i, j);
+    gx = tx * 8 + i;
+    gy = ty * 8 + j;
     const int kk = q - i - j;
     k = zb * P.mz + kk;
     if (kk < 0 || kk >= P.mz || gx >= P.g.nx || gy >= P.g.ny || k >= P.g.nz) return false;
-    slot = slot_of(P.g, gx, gy, k);
+    // slot_of, whose row k + i + j is the wave's
+    slot = ((int64_t)(ty * P.g.ntx + tx) * P.g.nz + wrap_nz(zb * P.mz + q, P.g.nz)) * 64 + (threadIdx.x & 63);
     return true;
 }
 
@@ -861,9 +869,10 @@ struct Bilu0 : PcImpl {
         s = flags_reset(c);
         if (s != RSV_OK) return s;
         ProfScope ps(c, RSV_K_FACTOR);
-        const unsigned pb = plane_blocks(M->g);
         for (int p = 0; p < M->g->nplanes; ++p) {
-            hipLaunchKernelGGL(k_factor_plane, dim3(pb), dim3(BS), 0, c->stream, planes(p), M->d_A, Lf, Dinv, c->d_flags);
+            on_plane(p, [&](const Planes &P, dim3 grid) {
+                hipLaunchKernelGGL(k_factor_plane, grid, dim3(BS), 0, c->stream, P, M->d_A, Lf, Dinv, c->d_flags);
+            });
             RSV_LAUNCH(c);
         }
         s = flags_check(c, bad_cell);
@@ -922,19 +931,32 @@ struct Bilu0 : PcImpl {
         return RSV_OK;
     }
 
-    Planes planes(int p) const { return Planes{M->g->geo, M->g->mx, M->g->my, M->g->mz, p}; }
+    template <class F> void on_plane(int p, const F &launch) const
+    {
+        const rsv_grid *G = M->g;
+        // tiles per plane box: the grid's own, whatever boxes the sweeps have
+        const int tx = std::min((G->mx + 7) / 8, G->geo.ntx), ty = std::min((G->my + 7) / 8, G->geo.nty);
+        const int nbx = (G->geo.ntx + tx - 1) / tx, nby = (G->geo.nty + ty - 1) / ty, nbz = (G->geo.nz + G->mz - 1) / G->mz;
+        Planes P{G->geo, plane_tiles(p, std::min(G->mz, G->geo.nz), tx, ty), G->mz, p, 0, nbx, nbx * nby, nbx * nby * nbz};
+        plane_launch(P.t, P.nunit, BS / 64, [&](int d, dim3 grid) {
+            P.d = d;
+            launch(P, grid);
+        });
+    }
 
     template <typename T>
     rsv_status apply_plane(const double *r, double *z, const T *L_, const T *D_, const T *U_, T *zt)
     {
         T *y = (T *)ybuf;
-        const unsigned pb = plane_blocks(M->g);
         for (int p = 0; p < M->g->nplanes; ++p)
-            hipLaunchKernelGGL(k_fwd_plane<T>, dim3(pb), dim3(BS), 0, c->stream, planes(p), L_, r, y);
+            on_plane(p, [&](const Planes &P, dim3 grid) {
+                hipLaunchKernelGGL(k_fwd_plane<T>, grid, dim3(BS), 0, c->stream, P, L_, r, y);
+            });
         RSV_LAUNCH(c);
         for (int p = M->g->nplanes - 1; p >= 0; --p)
-            hipLaunchKernelGGL(k_bwd_plane<T>, dim3(pb), dim3(BS), 0, c->stream, planes(p), D_, U_, M->d_A, (const T *)y, zt,
-                               z);
+            on_plane(p, [&](const Planes &P, dim3 grid) {
+                hipLaunchKernelGGL(k_bwd_plane<T>, grid, dim3(BS), 0, c->stream, P, D_, U_, M->d_A, (const T *)y, zt, z);
+            });
         RSV_LAUNCH(c);
         return RSV_OK;
     }

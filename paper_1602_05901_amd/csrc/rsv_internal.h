@@ -40,7 +40,8 @@ __host__ __device__ inline int ij_lane(int i, int j)
 __host__ __device__ inline void lane_ij(int L, int &i, int &j)
 {
     int d = 0;
-    while (d < 14 && lane_first(d + 1) <= L) ++d;
+#pragma unroll
+    for (int t = 1; t <= 14; ++t) d += lane_first(t) <= L;
     j = (d > 7 ? d - 7 : 0) + (L - lane_first(d));
     i = d - j;
 }
@@ -369,6 +370,45 @@ __device__ inline int64_t xcd_block(int64_t b, int64_t nb)
 {
     const int64_t x = b & 7, q = nb >> 3, rem = nb & 7;
     return x * q + (x < rem ? x : rem) + (b >> 3);
+}
+
+// ------------------------------------------------------------------ tiles of a hyperplane
+// Hyperplane p of boxes of btx x bty tiles and mz layers meets the tiles (bx, by) whose
+// lane (0, 0) lies on its layer p - 8 (bx + by) in [0, mz + 14): some of the boxes'
+// anti-diagonals bx + by = s0, s0 + 1, ...  A launch gives a wave to each of m places on
+// each of those (m = min(btx, bty), the longest), or to each tile where that is fewer (m = 0).
+// Launched for every tile, a wide flat grid's planes cost more than their cells: set-up
+// of BILU0 at 2048 x 2048 x 1 59 ms with lists of each plane's cells, 72 for all tiles, 43 so.
+struct PlaneTiles {
+    int btx, bty, s0, m;
+    int row, rows;           // waves of a box per row of the launch; rows (blockIdx.y): diagonals or tile rows
+};
+inline PlaneTiles plane_tiles(int p, int mz, int btx, int bty)
+{
+    const int lo = p - mz - 13, s0 = lo > 0 ? (lo + 7) / 8 : 0, s1 = p / 8 < btx + bty - 2 ? p / 8 : btx + bty - 2;
+    const int m = btx < bty ? btx : bty;
+    if ((int64_t)(s1 - s0 + 1) * m < (int64_t)btx * bty) return PlaneTiles{btx, bty, s0, m, m, s1 - s0 + 1};
+    return PlaneTiles{btx, bty, 0, 0, btx, bty};
+}
+// tile (bx, by) of place w of a box in row d of the launch; false where there is none
+// (places from t.row on too)
+__device__ inline bool plane_tile(const PlaneTiles &t, int w, int d, int &bx, int &by)
+{
+    if (t.m == 0) {
+        bx = w;
+        by = d;
+    } else {
+        const int s = t.s0 + d;
+        bx = (s < t.bty ? 0 : s - t.bty + 1) + w;
+        by = s - bx;
+    }
+    return bx < t.btx && by >= 0;
+}
+// calls launch(first row, grid) for the rows in pieces that a grid's y takes; boxes: of all
+template <class F> inline void plane_launch(const PlaneTiles &t, int boxes, int waves_per_block, const F &launch)
+{
+    const unsigned x = (unsigned)(((int64_t)boxes * t.row + waves_per_block - 1) / waves_per_block);
+    for (int d = 0; d < t.rows; d += 65535) launch(d, dim3(x, (unsigned)(t.rows - d < 65535 ? t.rows - d : 65535)));
 }
 
 // ------------------------------------------------------------------ faces between sweeping tiles

@@ -46,3 +46,31 @@ def test_steps_and_tiles(ctx, dims, fp32):
         else:
             assert torch.equal(z1, z0)
     M1.close(); M0.close(); A.close(); g.close()
+
+
+@pytest.mark.parametrize("dims", [(100, 9, 2), (65, 130, 1), (9, 200, 3), (250, 3, 1), (41, 33, 12), (1, 1, 40),
+                                  (120, 120, 5), (17, 90, 30)])
+def test_planes_of_wide_grids(ctx, dims):
+    """Hyperplanes that meet some of the grid's diagonals of tiles, and all of
+    them: the factors and the sweeps by hyperplanes against the oracle's, and
+    the pipelined sweeps on the same factors.  Entries to 1e-12 of the largest:
+    at most 21 products and one 3x3 inverse per cell, in another order, of
+    factors whose rows are diagonally dominant."""
+    import numpy as np
+    import oracle as O
+    from paper_1602_05901_amd import rsv
+    print("planes", dims, flush=True)
+    cfg = I.GenConfig(*dims, I.LNK_IID, 1.0, 0.0, 2.0, 0, 1e3, 1.0, 6)
+    B = I.blocks(cfg)
+    g = rsv.Grid(ctx, *dims)
+    A = rsv.Matrix(g, torch.from_numpy(B).cuda())
+    r = I.test_vector(10, 3 * cfg.ncell)
+    ref = O.ILU(O.BCSR.from_stencil(*dims, B)).apply(r)
+    rd = torch.from_numpy(r).cuda()
+    for pipelined in (0, 1):
+        M = rsv.Precond(A, type=rsv.PC_BILU0, pipelined=pipelined)
+        z = torch.full_like(rd, float("nan"))
+        M.apply(rd, z)
+        assert np.max(np.abs(z.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
+        M.close()
+    A.close(); g.close()
