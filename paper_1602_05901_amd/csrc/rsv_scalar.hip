@@ -456,27 +456,21 @@ struct STDev {
     double *y;                   // [row][64]
 };
 
-// the column of auxiliary cell (X, Y): its box, its grid column, the range
-// [klo, khi) of its layers in Omega_s and [olo, ohi) of those the box owns
+// the column of a box's cell (x, y): its grid column, the range [klo, khi) of its layers
+// in Omega_s and [olo, ohi) of those the box owns (all empty outside Omega_s)
 struct STColumn {
     int gx, gy, ez, klo, khi, olo, ohi;
 };
-__device__ inline STColumn st_column(const STDev &d, int X, int Y)
+__device__ inline STColumn st_column(const STDev &d, const STBox &q, int x, int y)
 {
-    STColumn c{0, 0, 0, 0, 0, 0, 0};
-    const int bx = X / (8 * d.btx), by = Y / (8 * d.bty), s = by * d.SX + bx;
-    if (s >= d.nsub) return c;
-    const STBox q = d.box[s];
-    c.gx = q.ex + X - bx * 8 * d.btx;
-    c.gy = q.ey + Y - by * 8 * d.bty;
-    c.ez = q.ez;
-    const int dx = c.gx < q.x0 ? q.x0 - c.gx : (c.gx >= q.x1 ? c.gx - q.x1 + 1 : 0);
-    const int dy = c.gy < q.y0 ? q.y0 - c.gy : (c.gy >= q.y1 ? c.gy - q.y1 + 1 : 0);
+    STColumn c{0, 0, q.ez, 0, 0, 0, 0};
+    const int gx = q.ex + x, gy = q.ey + y;
+    const int dx = gx < q.x0 ? q.x0 - gx : (gx >= q.x1 ? gx - q.x1 + 1 : 0);
+    const int dy = gy < q.y0 ? q.y0 - gy : (gy >= q.y1 ? gy - q.y1 + 1 : 0);
     const int64_t rest = (int64_t)d.ov - dx - dy;
-    if (c.gx >= d.g.nx || c.gy >= d.g.ny || rest < 0) {
-        c.gx = c.gy = 0;
-        return c;
-    }
+    if (x < 0 || y < 0 || gx >= d.g.nx || gy >= d.g.ny || rest < 0) return c;
+    c.gx = gx;
+    c.gy = gy;
     c.klo = (int)max((int64_t)0, q.z0 - rest) - q.ez;
     c.khi = (int)min((int64_t)d.g.nz, q.z1 + rest) - q.ez;
     if (dx == 0 && dy == 0) {
@@ -486,33 +480,36 @@ __device__ inline STColumn st_column(const STDev &d, int X, int Y)
     return c;
 }
 
-// one hyperplane of every box's factorisation (the planes before p are final)
-__global__ __launch_bounds__(SB) void k_st_factor(STDev d, int p, const double *__restrict__ coef, int32_t *flags)
+// The layers [klo, khi) of the columns toward -y, -x, +x, +y of a box's cell (x, y).
+struct STNear {
+    int klo[4], khi[4];
+};
+__device__ inline STNear st_near(const STDev &d, const STBox &q, int x, int y)
+{
+    const int dx[4] = {0, -1, 1, 0}, dy[4] = {-1, 0, 0, 1};
+    STNear m;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const STColumn c = st_column(d, q, x + dx[e], y + dy[e]);
+        const bool in = x + dx[e] < 8 * d.btx && y + dy[e] < 8 * d.bty;
+        m.klo[e] = in ? c.klo : 0;
+        m.khi[e] = in ? c.khi : 0;
+    }
+    return m;
+}
+
+// factors of layer k of column c, cell (X, Y) (those it depends on are final)
+__device__ inline void st_factor_cell(const STDev &d, const STColumn &c, const STNear &m, int X, int Y, int k,
+                                      const double *__restrict__ coef, int32_t *flags)
 {
     const int64_t n = (int64_t)d.g.nx * d.g.ny * d.g.nz;
-    const int64_t t = (int64_t)blockIdx.x * SB + threadIdx.x;
-    const int T = (int)(t >> 6), L = (int)(t & 63);
-    if (T >= d.a.ntx * d.a.nty) return;
-    const int tx = T % d.a.ntx, ty = T / d.a.ntx;
-    const int q = p - 8 * (tx % d.btx) - 8 * (ty % d.bty);
-    if (q < 0 || q >= d.a.nz + 14) return;
-    int i, j;
-    lane_ij(L, i, j);
-    const int X = 8 * tx + i, Y = 8 * ty + j, k = q - i - j;
-    const STColumn c = st_column(d, X, Y);
-    if (k < c.klo || k >= c.khi) return;
     const int64_t r = row_of(d.g, c.gx, c.gy, c.ez + k);
     const int64_t slot = slot_of(d.a, X, Y, k), e = (slot >> 6), la = slot & 63;
     double dd = coef[3 * n + r];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {        // -z, -y, -x
         const int dX = a == 2 ? -1 : 0, dY = a == 1 ? -1 : 0, dk = a == 0 ? -1 : 0;
-        // a lower neighbour of the box lies in the same box, so its column is one of it
-        bool in = a == 0 ? k > c.klo : (a == 1 ? Y % (8 * d.bty) > 0 : X % (8 * d.btx) > 0);
-        if (in && a > 0) {
-            const STColumn m = st_column(d, X + dX, Y + dY);
-            in = k >= m.klo && k < m.khi;
-        }
+        const bool in = a == 0 ? k > c.klo : k >= m.klo[a - 1] && k < m.khi[a - 1];
         double lv = 0.0;
         if (in) {
             const int64_t ns = slot_of(d.a, X + dX, Y + dY, k + dk);
@@ -525,12 +522,7 @@ __global__ __launch_bounds__(SB) void k_st_factor(STDev d, int p, const double *
     }
 #pragma unroll
     for (int a = 0; a < 3; ++a) {        // +x, +y, +z
-        const int dX = a == 0, dY = a == 1;
-        bool in = a == 2 ? k + 1 < c.khi : (a == 1 ? (Y + 1) % (8 * d.bty) > 0 : (X + 1) % (8 * d.btx) > 0);
-        if (in && a < 2) {
-            const STColumn m = st_column(d, X + dX, Y + dY);
-            in = k >= m.klo && k < m.khi;
-        }
+        const bool in = a == 2 ? k + 1 < c.khi : k >= m.klo[a + 2] && k < m.khi[a + 2];
         d.u[e * 256 + a * 64 + la] = in ? coef[HI_SLOT[a] * n + r] : 0.0;
     }
     double di = 0.0;
@@ -541,6 +533,46 @@ __global__ __launch_bounds__(SB) void k_st_factor(STDev d, int p, const double *
         di = 1.0 / dd;
     }
     d.u[e * 256 + 192 + la] = di;
+}
+
+// One hyperplane p of every box's factorisation (the planes before p are final): a wave
+// per tile that it meets.  d0: first row of the launch.
+__global__ __launch_bounds__(SB) void k_st_factor(STDev d, PlaneTiles t, int p, int d0, const double *__restrict__ coef,
+                                                  int32_t *flags)
+{
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (SB / 64) + (threadIdx.x >> 6)));
+    const int box = w / t.row;
+    int bx, by, i, j;
+    if (box >= d.nsub || !plane_tile(t, w - box * t.row, d0 + (int)blockIdx.y, bx, by)) return;
+    const int q = p - 8 * (bx + by);
+    if (q < 0 || q >= d.a.nz + 14) return;
+    lane_ij((int)(threadIdx.x & 63), i, j);
+    const STBox b = d.box[box];
+    const int x = 8 * bx + i, y = 8 * by + j, k = q - i - j;
+    const STColumn c = st_column(d, b, x, y);
+    if (k < c.klo || k >= c.khi) return;
+    st_factor_cell(d, c, st_near(d, b, x, y), 8 * (box % d.SX * d.btx) + x, 8 * (box / d.SX * d.bty) + y, k, coef, flags);
+}
+
+// All hyperplanes of one box of at most 16 tiles: a workgroup per box, a wave per tile,
+// a barrier between planes.  A plane costs 1 to 3 us, a launch per plane 4 and more: set-up
+// of one column of 50000 cells 204 -> 49 ms, 64 x 64 x 64 in 8 x 8 x 8 boxes 1.02 -> 0.48.
+__global__ __launch_bounds__(1024) void k_st_factor_box(STDev d, int nplane, const double *__restrict__ coef, int32_t *flags)
+{
+    const int T = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), box = blockIdx.x;
+    int i, j;
+    lane_ij((int)(threadIdx.x & 63), i, j);
+    const int bx = T % d.btx, by = T / d.btx;
+    const STBox b = d.box[box];
+    const int x = 8 * bx + i, y = 8 * by + j, k0 = x + y;
+    const int X = 8 * (box % d.SX * d.btx) + x, Y = 8 * (box / d.SX * d.bty) + y;
+    const STColumn c = st_column(d, b, x, y);
+    const STNear m = st_near(d, b, x, y);
+    for (int p = 0; p < nplane; ++p) {
+        const int k = p - k0;
+        if (k >= c.klo && k < c.khi) st_factor_cell(d, c, m, X, Y, k, coef, flags);
+        __syncthreads();
+    }
 }
 
 struct STSweep {
@@ -598,7 +630,8 @@ __global__ __launch_bounds__(64) void k_st_sweep(STDev d, STSweep a, double *__r
         const int Tn = !fin ? T : (DIR == 0 ? (fy ? T - d.a.ntx : T - 1) : (fy ? T + d.a.ntx : T + 1));
         const uint64_t *fsp = a.face + Tn * frow + lq;
         uint64_t *fdp = a.face + T * frow + lq;
-        const STColumn c = st_column(d, 8 * tx + li, 8 * ty + lj);
+        const int box = ty / d.bty * d.SX + tx / d.btx;   // the last places of the square of boxes may be empty
+        const STColumn c = box < d.nsub ? st_column(d, d.box[box], 8 * bx + li, 8 * by + lj) : STColumn{0, 0, 0, 0, 0, 0, 0};
         // the caller's entry of layer k is cv[k * ck]
         const bool td = d.g.ordering == RSV_TOP_DOWN;
         const int64_t ck = td ? -plane : plane;
@@ -937,14 +970,20 @@ struct STile final : PcImpl {
             const int ey = (int)std::min<int64_t>(G.ny, (int64_t)b.y1 + ov) - b.ey;
             const int ez = (int)std::min<int64_t>(G.nz, (int64_t)b.z1 + ov) - b.ez;
             EX = std::max(EX, ex); EY = std::max(EY, ey); EZ = std::max(EZ, ez);
-            for (int y = 0; y < ey; ++y)
-                for (int x = 0; x < ex; ++x) {
-                    const int gx = b.ex + x, gy = b.ey + y;
-                    const int64_t rest = (int64_t)ov - (gx < b.x0 ? b.x0 - gx : (gx >= b.x1 ? gx - b.x1 + 1 : 0)) -
-                                         (gy < b.y0 ? b.y0 - gy : (gy >= b.y1 ? gy - b.y1 + 1 : 0));
-                    if (rest >= 0)
-                        ncell += std::min<int64_t>(G.nz, b.z1 + rest) - std::max<int64_t>(0, b.z0 - rest);
+            // columns at distance a + b from the box (a in x, b in y) are as high as its z range
+            // widened by what is left of the overlap
+            auto columns = [](int64_t lo_, int64_t hi_, int64_t nn, int64_t at) {
+                return at == 0 ? hi_ - lo_ : (int64_t)(lo_ - at >= 0) + (hi_ - 1 + at < nn);
+            };
+            for (int64_t a = 0; a <= ov; ++a) {
+                const int64_t nc = columns(b.x0, b.x1, G.nx, a);
+                if (nc == 0) break;
+                for (int64_t e = 0; a + e <= ov; ++e) {
+                    const int64_t nr = columns(b.y0, b.y1, G.ny, e), rest = ov - a - e;
+                    if (nr == 0) break;
+                    ncell += nc * nr * (std::min<int64_t>(G.nz, b.z1 + rest) - std::max<int64_t>(0, b.z0 - rest));
                 }
+            }
         }
         d.btx = (EX + 7) / 8;
         d.bty = (EY + 7) / 8;
@@ -977,21 +1016,29 @@ struct STile final : PcImpl {
         if (st == RSV_OK) st = alloc(&face, (int64_t)NT * (EZ + 7) * 32, true);   // no word may carry a tag (epochs are never 0)
         if (st != RSV_OK) return st;
         d.box = dbox;
-        std::vector<int32_t> ord(NT);
-        for (int t = 0; t < NT; ++t) ord[t] = t;
-        const int w = ntx, btx = d.btx, bty = d.bty;
-        std::stable_sort(ord.begin(), ord.end(), [=](int32_t p, int32_t q) {
-            return (p % w) % btx + (p / w) % bty < (q % w) % btx + (q / w) % bty;
-        });
+        // tiles by their diagonal inside the box
+        std::vector<int32_t> ord(NT), at(d.btx + d.bty);
+        for (int y = 0; y < d.bty; ++y)
+            for (int x = 0; x < d.btx; ++x) at[x + y + 1] += (int32_t)(SX * SY);
+        for (int q = 1; q < d.btx + d.bty; ++q) at[q] += at[q - 1];
+        for (int y = 0, t = 0; y < nty; ++y)
+            for (int x = 0, by = y % d.bty, bx = 0; x < ntx; ++x, ++t, bx = bx + 1 == d.btx ? 0 : bx + 1) ord[at[bx + by]++] = t;
         RSV_HIP(c, hipMemcpyAsync(dbox, B.data(), (size_t)nsub * sizeof(STBox), hipMemcpyHostToDevice, c->stream));
         RSV_HIP(c, hipMemcpyAsync(tile_order, ord.data(), (size_t)NT * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
         st = flags_reset(c);   // synchronises: the host arrays may be released after it
         if (st != RSV_OK) return st;
         {
             ProfScope ps(c, RSV_K_FACTOR);
-            for (int p = 0; p < nplane; ++p)
-                hipLaunchKernelGGL(k_st_factor, dim3((unsigned)(((int64_t)NT * 64 + SB - 1) / SB)), dim3(SB), 0, c->stream, d,
-                                   p, M->d_coef, c->d_flags);
+            if (d.btx * d.bty <= 16)
+                hipLaunchKernelGGL(k_st_factor_box, dim3((unsigned)nsub), dim3((unsigned)(64 * d.btx * d.bty)), 0, c->stream, d,
+                                   nplane, M->d_coef, c->d_flags);
+            else
+                for (int p = 0; p < nplane; ++p) {
+                    const PlaneTiles t = plane_tiles(p, EZ, d.btx, d.bty);
+                    plane_launch(t, (int)nsub, SB / 64, [&](int d0, dim3 grid) {
+                        hipLaunchKernelGGL(k_st_factor, grid, dim3(SB), 0, c->stream, d, t, p, d0, M->d_coef, c->d_flags);
+                    });
+                }
         }
         RSV_LAUNCH(c);
         return flags_check(c, bad_cell);

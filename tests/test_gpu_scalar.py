@@ -273,3 +273,41 @@ def test_scalar_wait_limit_reports_timeout_and_recovers(rsv, ctx):
     ref = S.ILU(T.Ao).apply(r)
     assert np.max(np.abs(z.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
     M.close(); T.close()
+
+
+@pytest.mark.parametrize("dims,parts,ov,ordering", [
+    ((200, 150, 1), (1, 1, 1), 0, 0), ((150, 140, 2), (2, 1, 1), 2, 0),      # planes over some diagonals of tiles
+    ((60, 60, 40), (1, 1, 1), 0, 1), ((100, 90, 9), (2, 2, 1), 1, 1),        # over all tiles of a box
+    ((32, 32, 7), (1, 1, 1), 0, 1), ((70, 66, 6), (2, 2, 1), 1, 0), ((1, 1, 300), (1, 1, 3), 2, 0)])   # one workgroup per box
+def test_scalar_factor_planes(rsv, ctx, dims, parts, ov, ordering):
+    """The factorisation's launches at the shapes of their rules."""
+    test_scalar_ras_tile_columns(rsv, ctx, dims, parts, ov, ordering, 1)
+
+
+def test_scalar_set_up_of_wide_grids(rsv, ctx):
+    """Set-up of the tile columns on one wide layer takes at most twice that of
+    the form with one workgroup per subdomain."""
+    import time
+    n = 4096
+    C = torch.full((n * n, 7), -1.0, device="cuda", dtype=torch.float64)
+    C[:, 3] = 6.0
+    C[:, 0] = C[:, 6] = 0.0
+    C = C.view(n, n, 7)
+    C[0, :, 1] = C[-1, :, 5] = 0.0
+    C[:, 0, 2] = C[:, -1, 4] = 0.0
+    g = rsv.Grid(ctx, n, n, 1)
+    A = rsv.Matrix(g, C.view(-1, 7), scalar=True)
+
+    def set_up(pipelined):
+        best = 1e9
+        for _ in range(3):
+            t0 = time.perf_counter()
+            M = rsv.Precond(A, type=rsv.PC_RAS, ras_px=4, ras_py=4, ras_pz=1, ras_overlap=1, pipelined=pipelined)
+            best = min(best, time.perf_counter() - t0)
+            M.close()
+        return best
+
+    tiles, chunks = set_up(1), set_up(0)
+    log("set-up ms: tile columns %.1f, one workgroup per subdomain %.1f" % (tiles * 1e3, chunks * 1e3))
+    assert tiles <= 2 * chunks
+    A.close(); g.close()
