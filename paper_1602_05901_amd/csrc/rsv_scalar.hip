@@ -926,7 +926,7 @@ struct STile final : PcImpl {
     std::vector<void *> mem;
     int32_t *tile_order = nullptr;
     uint64_t *face = nullptr;
-    bool unfit = false;                     // the boxes exceed the index range
+    bool unfit = false;                     // the chunk form is the better one, or the boxes exceed the index range
 
     ~STile() override
     {
@@ -993,8 +993,24 @@ struct STile final : PcImpl {
         // Small boxes pad much (64 slots per layer however few of its columns a
         // box has), but the tile columns stay ahead of the chunk form down to
         // single-cell boxes (64^3 in 64^3 boxes: 6.5 against 21 ms an apply; 96^3
-        // in 31^3: 0.85 against 4.5).  The chunk form, with up to a fifth of the
-        // memory, takes what exceeds the slots' index range or the memory.
+        // in 31^3: 0.85 against 4.5).  They fall behind where a box is a few layers
+        // thin and long in x, so that its diagonals of tiles are the chain (6.1 us a
+        // diagonal, 0.375 a step; a tile occupies a wave for 7.2 us and its steps), while
+        // the other form has a plane per eight cells of x (2.1 us a plane and 0.0135 a
+        // chunk, a box per CU at a time).  These figures give each form's time within
+        // about 25 % and the choice (apply, chunk form against tile columns, ms): 100000
+        // x 1 x 1 52 and 153, in 64 boxes 0.87 and 2.5, 20000 x 8 x 1 11.2 and 30.4, 4096 x
+        // 4096 x 1 in 64 x 64 boxes 5.4 and 8.3; in 4 x 4 boxes 6.8 and 7.1, one box 77 and
+        // 14, 1024 x 1024 x 1 5.9 and 3.4.  The chunk form, with up to a fifth of the
+        // memory, also takes what exceeds the slots' index range or the memory.
+        const double planes = (EX + SW - 1) / SW + EY + EZ - 2, chunks = (double)((EX + SW - 1) / SW) * EY * EZ;
+        const double t_chunk = (double)((nsub + c->num_cu - 1) / c->num_cu) * (2.1 * planes + 0.0135 * chunks);
+        const double steps = 0.375 * (EZ + 14), tiles = (double)slots / 64 / EZ;
+        const double t_tile = std::max(6.1 * (d.btx + d.bty - 2) + steps, tiles * (7.2 + steps) / (ST_WAVES * c->num_cu));
+        if (t_chunk < t_tile) {
+            unfit = true;
+            return RSV_OK;
+        }
         if (3 * slots >= ((int64_t)1 << 31)) {
             unfit = true;
             return RSV_OK;

@@ -311,3 +311,30 @@ def test_scalar_set_up_of_wide_grids(rsv, ctx):
     log("set-up ms: tile columns %.1f, one workgroup per subdomain %.1f" % (tiles * 1e3, chunks * 1e3))
     assert tiles <= 2 * chunks
     A.close(); g.close()
+
+
+@pytest.mark.parametrize("dims,parts", [((20000, 8, 1), (1, 1, 1)), ((100000, 1, 1), (64, 1, 1)), ((64, 64, 64), (4, 4, 4))])
+def test_scalar_apply_of_thin_boxes(rsv, ctx, dims, parts):
+    """The default form's apply takes at most 1.5 times that of one workgroup
+    per subdomain, also on boxes a layer thin and long in x."""
+    import time
+    T = Sys(rsv, ctx, dims, 0.0, 14)
+    r = dev(I.test_vector(23, T.n))
+    z = torch.zeros_like(r)
+
+    def apply_time(pipelined):
+        M = rsv.Precond(T.A, type=rsv.PC_RAS, ras_px=parts[0], ras_py=parts[1], ras_pz=parts[2], ras_overlap=1,
+                        pipelined=pipelined)
+        best = 1e9
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            M.apply(r, z)
+            best = min(best, time.perf_counter() - t0)
+        M.close()
+        return best
+
+    default, chunks = apply_time(1), apply_time(0)
+    log("thin boxes", dims, parts, "us: default %.0f, one workgroup per subdomain %.0f" % (default * 1e6, chunks * 1e6))
+    assert default <= 1.5 * chunks
+    T.close()
