@@ -616,6 +616,7 @@ __global__ __launch_bounds__(64) void k_st_sweep(STDev d, STSweep a, double *__r
         double f[NF], v;
         uint64_t w;
     };
+    bool over = false;   // a wait gave up: the flag is set, no wait lasts any more
     for (;;) {
         uint64_t tk = 0;
         if (L == 0) tk = atomicAdd((unsigned long long *)a.ticket, 1ull) - a.ticket_base;
@@ -659,13 +660,16 @@ __global__ __launch_bounds__(64) void k_st_sweep(STDev d, STSweep a, double *__r
             // the faces this step's boundary lanes need
             const bool need = fin && (unsigned)(t - fk_in) < (unsigned)nz;
             uint64_t w = R.w;
-            if (__ballot(need && (uint32_t)(w >> 32) != a.epoch) != 0ull) {
+            if (!over && __ballot(need && (uint32_t)(w >> 32) != a.epoch) != 0ull) {
                 const uint64_t t0 = wall_clock64();
                 uint32_t n = 0;
                 for (;;) {
                     if (need) w = face_ld(fsp + (int64_t)t * 32);
                     if (__ballot(need && (uint32_t)(w >> 32) != a.epoch) == 0ull) break;
-                    if (spin_guard(a.flags, t0, n, a.wait_limit)) break;
+                    if (spin_guard(a.flags, t0, n, a.wait_limit)) {
+                        over = true;
+                        break;
+                    }
                     __builtin_amdgcn_s_sleep(1);
                 }
             }

@@ -338,3 +338,39 @@ def test_scalar_apply_of_thin_boxes(rsv, ctx, dims, parts):
     log("thin boxes", dims, parts, "us: default %.0f, one workgroup per subdomain %.0f" % (default * 1e6, chunks * 1e6))
     assert default <= 1.5 * chunks
     T.close()
+
+
+def test_scalar_wait_that_gave_up_is_remembered(rsv, ctx):
+    """After one wait has given up the sweeps go on without waiting: with a
+    bound of 0.1 us an apply comes back with its error sooner than an ordinary
+    apply with its result, whose tiles wait for one another's faces."""
+    import time
+    T = Sys(rsv, ctx, (128, 128, 128), 0.0, 15)
+    M = rsv.Precond(T.A, type=rsv.PC_BILU0)
+    r = dev(I.test_vector(24, T.n))
+    z = torch.zeros_like(r)
+
+    def apply_time(status):
+        best = 1e9
+        for _ in range(8):
+            got = 0
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            try:
+                M.apply(r, z)
+            except rsv.RsvError as e:
+                got = e.status
+            best = min(best, time.perf_counter() - t0)
+            assert got == status
+        return best
+
+    whole = apply_time(0)
+    ctx.set_wait_limit(1e-7)
+    try:
+        error = apply_time(rsv.ERR_TIMEOUT)
+    finally:
+        ctx.set_wait_limit(2.0)
+    log("us: apply %.0f, to the error %.0f" % (whole * 1e6, error * 1e6))
+    assert error <= 0.8 * whole
+    assert apply_time(0) < 1e9
+    M.close(); T.close()
