@@ -28,6 +28,11 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+// a caller's BF16 input is at least 8-byte aligned
+typedef short v8su __attribute__((ext_vector_type(8), aligned(8)));
+typedef uint32_t v4wu __attribute__((ext_vector_type(4), aligned(8)));
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint16_t v4hu __attribute__((ext_vector_type(4), aligned(4)));
 
 namespace {
 
@@ -255,9 +260,6 @@ template <int CIN, int NBW, int NSPLIT, int TZ> struct ConvCfg {
     static constexpr size_t LDS = WBYTES + (size_t)HN * VS * 2;
 };
 
-typedef short v8su __attribute__((ext_vector_type(8), aligned(8)));    // a caller's input is at least 8-byte aligned
-typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint16_t v4hu __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int CIN, int NBW, int NSPLIT, int TZ, bool OUT_BF16>
 __global__ __launch_bounds__(64 * TZ * NSPLIT) void k_conv_lds(ConvGeo g, const uint16_t *__restrict__ X,
@@ -537,7 +539,7 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
 #pragma unroll
     for (int j = 0; j < 7; ++j) acc[j] = v4f{0.f, 0.f, 0.f, 0.f};
     float bq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // bias sums of channels 8 (tid & 1) .. + 7
-    uint4 rx[DW_NX], rg[DW_NG];
+    v4wu rx[DW_NX], rg[DW_NG];
     // Places of this thread's pieces from the brick's first voxel; bricks begin at
     // even coordinates, so halving them (up) is exact.
     const int sx = g.up ? g.nx >> 1 : g.nx, sy = g.up ? g.ny >> 1 : g.ny;
@@ -566,13 +568,13 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
             X + ((bk.x0 >> g.up) + (int64_t)sx * ((bk.y0 >> g.up) + (int64_t)sy * (bk.z0 >> g.up))) * g.cin;
 #pragma unroll
         for (int k = 0; k < DW_NX; ++k) {
-            rx[k] = uint4{0, 0, 0, 0};
+            rx[k] = v4wu{0, 0, 0, 0};
             const bool in = ((unsigned)((hc[k] & 255) - xl) < (unsigned)xn) & ((unsigned)((hc[k] >> 8 & 255) - yl) < (unsigned)yn) &
                             ((unsigned)((hc[k] >> 16) - zl) < (unsigned)zn);
             if (!in) continue;
             const uint16_t *p = xb + xo[k];
             if (wide) {
-                rx[k] = *(const uint4 *)p;
+                rx[k] = *(const v4wu *)p;
             } else {
                 const uint2 lo = *(const uint2 *)p;
                 rx[k].x = lo.x;
@@ -588,18 +590,18 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvGeo g, const uint16_t *__re
 #pragma unroll
         for (int k = 0; k < DW_NG; ++k) {
             const int v = (tid + 256 * k) >> 1;
-            rg[k] = uint4{0, 0, 0, 0};
+            rg[k] = v4wu{0, 0, 0, 0};
             if ((v & 15) < g.nx - bk.x0 && ((v >> 4) & 3) < g.ny - bk.y0 && (v >> 6) < bk.zhi - bk.z0)
-                rg[k] = *(const uint4 *)(gb + go[k]);
+                rg[k] = *(const v4wu *)(gb + go[k]);
         }
     };
     auto store = [&]() {
 #pragma unroll
         for (int k = 0; k < DW_NX; ++k)
-            if (tid + 256 * k < DW_XU) xs[tid + 256 * k] = rx[k];
+            if (tid + 256 * k < DW_XU) xs[tid + 256 * k] = uint4{rx[k].x, rx[k].y, rx[k].z, rx[k].w};
 #pragma unroll
         for (int k = 0; k < DW_NG; ++k) {
-            gs[tid + 256 * k] = rg[k];
+            gs[tid + 256 * k] = uint4{rg[k].x, rg[k].y, rg[k].z, rg[k].w};
             if (cib == 0) {
                 const uint32_t w[4] = {rg[k].x, rg[k].y, rg[k].z, rg[k].w};
 #pragma unroll

@@ -526,3 +526,26 @@ def test_input_channel_statistics(rsv, ctx):
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
     assert torch.equal(out[3], out[4]) and not torch.equal(out[0], out[3])
     net.close(); g.close()
+
+
+@pytest.mark.parametrize("cin,cout", [(16, 16), (32, 64), (4, 16), (12, 32)])
+def test_weight_gradient_of_inputs_aligned_to_8_bytes(rsv, ctx, cin, cout):
+    """x and dy that start 8 bytes into an allocation: the same bits as from its
+    start."""
+    log("dw alignment", cin, cout)
+    dims = (19, 10, 6)
+    V = dims[0] * dims[1] * dims[2]
+    g = torch.Generator().manual_seed(cin + cout)
+    got = []
+    x, dy = (torch.randn(V * c, generator=g).bfloat16().view(torch.int16) for c in (cin, cout))
+    w = torch.zeros(27 * cin * cout, device="cuda")
+    for shift in (0, 4):
+        xs, ys = (torch.zeros(t.numel() + 8, dtype=torch.int16, device="cuda")[shift:shift + t.numel()] for t in (x, dy))
+        xs.copy_(x)
+        ys.copy_(dy)
+        assert xs.data_ptr() % 16 == ys.data_ptr() % 16 == 2 * shift
+        dw, db = torch.full((27 * cin * cout,), -1.0, device="cuda"), torch.full((cout,), -1.0, device="cuda")
+        rsv.conv3d_bwd(ctx, dims, cin, cout, xs, w, ys, None, dw, db)
+        got.append((dw, db))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert float(got[0][0].abs().max()) > 1.0
