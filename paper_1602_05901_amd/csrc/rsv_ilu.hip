@@ -359,29 +359,34 @@ template <int DIR, typename T> struct SweepCfg {
 
 // 16 (or 4) bytes per lane from src + voff to LDS address dst + 16 (4) lane (both
 // + AT, below 4096); src uniform.  The compiler does not count these loads: the
-// waits are explicit.  NT: nontemporal, the lines are not kept.
+// waits are explicit.  NT: nontemporal, the lines are not kept.  m0 is named as written,
+// so that no use of it by the compiler is moved across; it warns that it reserves m0 for
+// itself, as it does for LDS addresses like these.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int AT, bool NT> __device__ __forceinline__ void lds_copy(uint32_t voff, const void *src, uint32_t dst)
 {
     if constexpr (NT)
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3 nt"
                      :
                      : "v"(voff), "s"(src), "s"(dst), "n"(AT)
-                     : "memory");
+                     : "memory", "m0");
     else
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
                      :
                      : "v"(voff), "s"(src), "s"(dst), "n"(AT)
-                     : "memory");
+                     : "memory", "m0");
 }
 // the same past the caches that other dies do not see, as the face words need it
 __device__ __forceinline__ void lds_copy_face(const void *p, uint32_t dst)
 {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc1" ::"v"(p), "s"(dst) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc1" ::"v"(p), "s"(dst) : "memory", "m0");
 }
 __device__ __forceinline__ void lds_copy4(const void *p, uint32_t dst)
 {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(p), "s"(dst) : "memory");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(p), "s"(dst) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
