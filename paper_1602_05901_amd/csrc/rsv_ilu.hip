@@ -89,7 +89,7 @@ struct Planes {
 };
 __device__ inline bool plane_cell(const Planes &P, int &gx, int &gy, int &k, int64_t &slot)
 {
-    int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (BS / 64) + (threadIdx.x >> 6)));
+    int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     int unit = 0, zb = 0, tx, ty;
     if (P.nunit > 1) {
         unit = w / P.t.row;
@@ -875,8 +875,8 @@ struct Bilu0 : PcImpl {
         if (s != RSV_OK) return s;
         ProfScope ps(c, RSV_K_FACTOR);
         for (int p = 0; p < M->g->nplanes; ++p) {
-            on_plane(p, [&](const Planes &P, dim3 grid) {
-                hipLaunchKernelGGL(k_factor_plane, grid, dim3(BS), 0, c->stream, P, M->d_A, Lf, Dinv, c->d_flags);
+            on_plane(p, [&](const Planes &P, dim3 grid, dim3 blk) {
+                hipLaunchKernelGGL(k_factor_plane, grid, blk, 0, c->stream, P, M->d_A, Lf, Dinv, c->d_flags);
             });
             RSV_LAUNCH(c);
         }
@@ -943,9 +943,9 @@ struct Bilu0 : PcImpl {
         const int tx = std::min((G->mx + 7) / 8, G->geo.ntx), ty = std::min((G->my + 7) / 8, G->geo.nty);
         const int nbx = (G->geo.ntx + tx - 1) / tx, nby = (G->geo.nty + ty - 1) / ty, nbz = (G->geo.nz + G->mz - 1) / G->mz;
         Planes P{G->geo, plane_tiles(p, std::min(G->mz, G->geo.nz), tx, ty), G->mz, p, 0, nbx, nbx * nby, nbx * nby * nbz};
-        plane_launch(P.t, P.nunit, BS / 64, [&](int d, dim3 grid) {
+        plane_launch(c, P.t, P.nunit, [&](int d, dim3 grid, dim3 blk) {
             P.d = d;
-            launch(P, grid);
+            launch(P, grid, blk);
         });
     }
 
@@ -954,13 +954,13 @@ struct Bilu0 : PcImpl {
     {
         T *y = (T *)ybuf;
         for (int p = 0; p < M->g->nplanes; ++p)
-            on_plane(p, [&](const Planes &P, dim3 grid) {
-                hipLaunchKernelGGL(k_fwd_plane<T>, grid, dim3(BS), 0, c->stream, P, L_, r, y);
+            on_plane(p, [&](const Planes &P, dim3 grid, dim3 blk) {
+                hipLaunchKernelGGL(k_fwd_plane<T>, grid, blk, 0, c->stream, P, L_, r, y);
             });
         RSV_LAUNCH(c);
         for (int p = M->g->nplanes - 1; p >= 0; --p)
-            on_plane(p, [&](const Planes &P, dim3 grid) {
-                hipLaunchKernelGGL(k_bwd_plane<T>, grid, dim3(BS), 0, c->stream, P, D_, U_, M->d_A, (const T *)y, zt, z);
+            on_plane(p, [&](const Planes &P, dim3 grid, dim3 blk) {
+                hipLaunchKernelGGL(k_bwd_plane<T>, grid, blk, 0, c->stream, P, D_, U_, M->d_A, (const T *)y, zt, z);
             });
         RSV_LAUNCH(c);
         return RSV_OK;

@@ -540,7 +540,7 @@ __device__ inline void st_factor_cell(const STDev &d, const STColumn &c, const S
 __global__ __launch_bounds__(SB) void k_st_factor(STDev d, PlaneTiles t, int p, int d0, const double *__restrict__ coef,
                                                   int32_t *flags)
 {
-    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (SB / 64) + (threadIdx.x >> 6)));
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     const int box = w / t.row;
     int bx, by, i, j;
     if (box >= d.nsub || !plane_tile(t, w - box * t.row, d0 + (int)blockIdx.y, bx, by)) return;
@@ -1055,8 +1055,8 @@ struct STile final : PcImpl {
             else
                 for (int p = 0; p < nplane; ++p) {
                     const PlaneTiles t = plane_tiles(p, EZ, d.btx, d.bty);
-                    plane_launch(t, (int)nsub, SB / 64, [&](int d0, dim3 grid) {
-                        hipLaunchKernelGGL(k_st_factor, grid, dim3(SB), 0, c->stream, d, t, p, d0, M->d_coef, c->d_flags);
+                    plane_launch(c, t, (int)nsub, [&](int d0, dim3 grid, dim3 blk) {
+                        hipLaunchKernelGGL(k_st_factor, grid, blk, 0, c->stream, d, t, p, d0, M->d_coef, c->d_flags);
                     });
                 }
         }
