@@ -404,7 +404,7 @@ __global__ __launch_bounds__(64 * TZ * NSPLIT) void k_conv_lds(ConvGeo g, const 
 }
 
 template <int CIN, int NBW, int NSPLIT, int TZ, bool OUT_BF16>
-hipError_t launch_conv_lds(hipStream_t st, const ConvGeo &g, const uint16_t *X, const void *Wf, const Epilogue &ep)
+hipError_t launch_conv_lds(const rsv_ctx *c, const ConvGeo &g, const uint16_t *X, const void *Wf, const Epilogue &ep)
 {
     using C = ConvCfg<CIN, NBW, NSPLIT, TZ>;
     auto *fn = &k_conv_lds<CIN, NBW, NSPLIT, TZ, OUT_BF16>;
@@ -412,7 +412,7 @@ hipError_t launch_conv_lds(hipStream_t st, const ConvGeo &g, const uint16_t *X, 
         const hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::LDS);
         if (e != hipSuccess) return e;
     }
-    // As many workgroups as the 256 CUs hold at once (1 to 5 each, by registers and
+    // As many workgroups as the CUs hold at once (1 to 5 each, by registers and
     // LDS), walking the bricks with their weights staged once: more would run as a
     // second, part-empty round.  1024 in all cases, then resident: 4 -> 16 channels
     // 22.1 -> 21.2 us at 128x128x64, 16 -> 16 37.6 -> 33.2, 32 -> 16 58.4 -> 55.9,
@@ -423,34 +423,34 @@ hipError_t launch_conv_lds(hipStream_t st, const ConvGeo &g, const uint16_t *X, 
         return e == hipSuccess && nb > 0 ? nb : 2;
     }();
     const unsigned groups = (unsigned)(g.cout / (16 * NSPLIT * NBW));
-    const unsigned nwg = std::min<unsigned>((unsigned)brick_count(g, TZ), std::max(1u, 256u * resident / groups));
-    hipLaunchKernelGGL(fn, dim3(nwg, groups), dim3(C::NT), C::LDS, st, g, X, Wf, ep);
+    const unsigned nwg = std::min<unsigned>((unsigned)brick_count(g, TZ), std::max(1u, (unsigned)c->num_cu * resident / groups));
+    hipLaunchKernelGGL(fn, dim3(nwg, groups), dim3(C::NT), C::LDS, c->stream, g, X, Wf, ep);
     return hipGetLastError();
 }
 
 // Convolution launch: the staged kernels for the network's channel counts, else
 // the general one (rsv_conv3d alone: FP32 out, bias).
 template <bool OUT_BF16>
-hipError_t launch_conv(hipStream_t st, const ConvGeo &g, const uint16_t *X, const void *Wf, int KB, const Epilogue &ep)
+hipError_t launch_conv(const rsv_ctx *c, const ConvGeo &g, const uint16_t *X, const void *Wf, int KB, const Epilogue &ep)
 {
     const int NB = g.cout / 16;
     if (g.cout % 16 || (NB != 1 && NB != 2 && NB != 4)) return hipErrorInvalidValue;
     const bool staged = (int64_t)g.nx * g.ny < (1 << 28);   // the staged kernel's halo offsets are 32-bit
     if (!staged) {
     } else if (g.cin == 4) {
-        if (NB == 1) return launch_conv_lds<4, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
-        if (NB == 2) return launch_conv_lds<4, 2, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
-        return launch_conv_lds<4, 4, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        if (NB == 1) return launch_conv_lds<4, 1, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
+        if (NB == 2) return launch_conv_lds<4, 2, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
+        return launch_conv_lds<4, 4, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
     } else if (g.cin == 16) {
-        if (NB == 1) return launch_conv_lds<16, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
-        if (NB == 2) return launch_conv_lds<16, 2, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
-        return launch_conv_lds<16, 4, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        if (NB == 1) return launch_conv_lds<16, 1, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
+        if (NB == 2) return launch_conv_lds<16, 2, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
+        return launch_conv_lds<16, 4, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
     } else if (g.cin == 32) {
-        if (NB == 1) return launch_conv_lds<32, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
-        return launch_conv_lds<32, 2, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
+        if (NB == 1) return launch_conv_lds<32, 1, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
+        return launch_conv_lds<32, 2, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
     } else if (g.cin == 64) {
-        if (NB == 1) return launch_conv_lds<64, 1, 1, 4, OUT_BF16>(st, g, X, Wf, ep);
-        return launch_conv_lds<64, 1, 2, 2, OUT_BF16>(st, g, X, Wf, ep);
+        if (NB == 1) return launch_conv_lds<64, 1, 1, 4, OUT_BF16>(c, g, X, Wf, ep);
+        return launch_conv_lds<64, 1, 2, 2, OUT_BF16>(c, g, X, Wf, ep);
     }
     if (OUT_BF16 || ep.skip || ep.relu || ep.mask || ep.copy || g.up || g.nz != g.nzs) return hipErrorInvalidValue;
     const int MB = g.V >= 131072 ? 4 : 1;   // four voxel blocks per wave reuse the weights; small levels need the waves
@@ -459,9 +459,9 @@ hipError_t launch_conv(hipStream_t st, const ConvGeo &g, const uint16_t *X, cons
 #define RSV_CONV(mb, nb)                                                                                             \
     do {                                                                                                             \
         if (g.cin % 8 == 0)                                                                                          \
-            hipLaunchKernelGGL((k_conv<mb, nb, true>), grid, blk, 0, st, g, X, Wf, KB, ep.bias, (float *)ep.out);    \
+            hipLaunchKernelGGL((k_conv<mb, nb, true>), grid, blk, 0, c->stream, g, X, Wf, KB, ep.bias, (float *)ep.out);    \
         else                                                                                                         \
-            hipLaunchKernelGGL((k_conv<mb, nb, false>), grid, blk, 0, st, g, X, Wf, KB, ep.bias, (float *)ep.out);   \
+            hipLaunchKernelGGL((k_conv<mb, nb, false>), grid, blk, 0, c->stream, g, X, Wf, KB, ep.bias, (float *)ep.out);   \
     } while (0)
     if (MB == 4) {
         if (NB == 1) RSV_CONV(4, 1);
@@ -1236,7 +1236,7 @@ static rsv_status conv_fwd(rsv_net *n, int l, int nx, int ny, int nz, int nzs, i
     rsv_ctx *c = n->c;
     ConvGeo g{nx, ny, nz, nzs, up, n->a.cin[l], n->a.cout[l], (int64_t)nx * ny * nz};
     const Epilogue ep{n->P + n->a.boff[l], skip, 1, nullptr, nullptr, out};
-    const hipError_t e = launch_conv<true>(c->stream, g, X, n->wf[l], n->a.kb(l), ep);
+    const hipError_t e = launch_conv<true>(c, g, X, n->wf[l], n->a.kb(l), ep);
     if (e != hipSuccess) return set_err(c, RSV_ERR_HIP, std::string("conv launch: ") + hipGetErrorString(e));
     return RSV_OK;
 }
@@ -1250,8 +1250,8 @@ static rsv_status conv_bwd_data(rsv_net *n, int l, int nx, int ny, int nz, int n
     ConvGeo g{nx, ny, nz, nzs, 0, n->a.cout[l], n->a.cin[l], (int64_t)nx * ny * nz};
     if (g.cout % 16) return set_err(c, RSV_ERR_ARG, "channel count must be 16, 32 or 64");
     const Epilogue ep{nullptr, nullptr, 0, mask, copy, mask ? (void *)dX16 : (void *)dX32};
-    const hipError_t e = mask ? launch_conv<true>(c->stream, g, G, n->wt[l], n->a.kbt(l), ep)
-                              : launch_conv<false>(c->stream, g, G, n->wt[l], n->a.kbt(l), ep);
+    const hipError_t e = mask ? launch_conv<true>(c, g, G, n->wt[l], n->a.kbt(l), ep)
+                              : launch_conv<false>(c, g, G, n->wt[l], n->a.kbt(l), ep);
     if (e != hipSuccess) return set_err(c, RSV_ERR_HIP, std::string("conv launch: ") + hipGetErrorString(e));
     return RSV_OK;
 }
@@ -1708,7 +1708,7 @@ rsv_status rsv_conv3d(rsv_ctx *c, int32_t nx, int32_t ny, int32_t nz, int32_t ci
     hipLaunchKernelGGL(k_pack, dim3(nblk((int64_t)KB * NB * 64)), dim3(256), 0, c->stream, w, cin, cout, 0, KB, NB,
                        conv_kw(cin), wf);
     ConvGeo g{nx, ny, nz, nz, 0, cin, cout, (int64_t)nx * ny * nz};
-    hipError_t e = launch_conv<false>(c->stream, g, x, wf, KB, Epilogue{b, nullptr, 0, nullptr, nullptr, y});
+    hipError_t e = launch_conv<false>(c, g, x, wf, KB, Epilogue{b, nullptr, 0, nullptr, nullptr, y});
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     dev_free(wf);
     if (e != hipSuccess) return set_err(c, RSV_ERR_HIP, std::string("conv3d: ") + hipGetErrorString(e));
