@@ -123,7 +123,13 @@ typedef struct rsv_pc_params {
                           * subdomain (type RAS: the local solver; type BILU0: the whole grid) */
     int32_t pipelined;   /* 1 (default): sync-free tiled wavefront sweeps (RAS: every subdomain's local
                           * system in one auxiliary grid of boxes, swept together); 0: BILU0 one launch
-                          * per hyperplane, RAS one workgroup per subdomain (reference mappings) */
+                          * per hyperplane, RAS one workgroup per subdomain (reference mappings).
+                          * Scalar systems, BILU0 (one subdomain) and RAS alike: 1: every subdomain's
+                          * columns in whole 8 x 8 tiles, 64 slots of 64 bytes and 256 bytes of face
+                          * words per layer of a tile however few of its columns a box has (64^3 cells
+                          * in 64^3 boxes: 3.9 GB); boxes that are thin and long in x, and those whose
+                          * slots exceed 2^31 / 3 or the memory, take the form of 0; 0: one workgroup
+                          * per subdomain, about 80 bytes per cell of all Omega_s */
     rsv_net *net;        /* LEARNED: trained network (not owned) */
     const float *lnk;    /* LEARNED: DEVICE pointer, ln k per cell in block-row order (not copied; must outlive the precond) */
     double theta;        /* LEARNED: fallback when a step's residual estimate exceeds theta * previous (default 0.9, the
@@ -371,7 +377,10 @@ rsv_status rsv_net_forward(rsv_net *net, rsv_grid *g, const double *r, const flo
 /* One Adam step on a batch of `nb` samples on grid g: inputs r[nb][3*ncell]
  * (device FP64), targets e[nb][3*ncell] (device FP64), lnk[nb][ncell]
  * (device FP32).  Loss = mean_b ||N(r_b/s_b) - e_b/s_b||^2 / ||e_b/s_b||^2
- * with s_b = rms(r_b).  The loss is written to *loss_out (host). */
+ * with s_b = rms(r_b).  The loss is written to *loss_out (host).  Samples run
+ * together as long as they hold at most 2^21 voxels; the network keeps the
+ * buffers of such a pass, about 600 bytes per voxel (up to 1.3 GB), and those of
+ * one sample where that does not fit the memory. */
 rsv_status rsv_net_train_step(rsv_net *net, rsv_grid *g, int32_t nb, const double *r, const double *e,
                               const float *lnk, float lr, float *loss_out);
 /* Forward + backward without the update: loss and the gradient of every
@@ -442,8 +451,12 @@ rsv_status rsv_grid_hsfc_keys(rsv_grid *g, int32_t levels, uint64_t *keys);
 /* The equal-count cut of the curve (step 3 of that algorithm): with the n
  * keys (DEVICE, from rsv_*hsfc_keys with the same levels) in increasing
  * order, equal keys by index, the entry of rank r goes to part
- * floor(r * nparts / n); part DEVICE int32 [n].  n <= 2^31.  Allocates its
- * sort buffers (24 n bytes plus histograms) for the call. */
+ * floor(r * nparts / n); part DEVICE int32 [n], also on the keys' own memory.
+ * n <= 2^31.  Up to 4096 parts it counts cells in a workspace of at most 48 MB,
+ * which the context keeps until rsv_destroy; more parts, keys with bits above
+ * their 3*levels, part overlapping keys and a workspace that cannot be had
+ * take a sort, whose buffers (24 n bytes plus histograms) are allocated for the
+ * call.  Synchronises the stream. */
 rsv_status rsv_hsfc_partition(rsv_ctx *ctx, int64_t n, const uint64_t *keys, int32_t levels, int32_t nparts,
                               int32_t *part);
 /* Partition quality (Partition Quality subsection) of part (DEVICE int32

@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void k_assign_parts(const uint32_t *__restrict
 constexpr int TRIE_PARTS = 4096;      // most parts the trie takes
 constexpr int TRIE_TOP = 12;          // digit bits of the root
 constexpr int TRIE_ROWS_BITS = 20;    // log2 of the most entries a level may have
-constexpr int TRIE_MAXLEV = 14;
+constexpr int TRIE_MAXLEV = 12;       // 12 bits, then 51 of the key and 31 of the index by 8
 
 struct Trie {
     int nlev;                         // levels, the root first
@@ -542,9 +542,10 @@ rsv_status scan_counts(rsv_ctx *c, const uint32_t *in, uint32_t *out, int64_t m,
     return RSV_OK;
 }
 
-// The cut by the trie.  The context keeps the workspace (at most 2^20 entries a
-// level: 4 MiB x 13 levels and the counts); every call waits for its last
-// kernel, so the next one, on whatever stream, finds it idle.
+// The cut by the trie.  The context keeps the workspace: at most 2^20 entries a level
+// below the root and as many counts, 48 MB for the longest word, 63 + 31 bits in
+// 12 levels.  Every call waits for its last kernel, so the next one, on whatever
+// stream, finds it idle.
 // *stray: some key has bits above its 3*levels, which the sort's whole bytes
 // count in part; those keys are left to it.
 rsv_status trie_partition(rsv_ctx *c, int64_t n, const uint64_t *keys, int levels, int32_t nparts, int32_t *part,

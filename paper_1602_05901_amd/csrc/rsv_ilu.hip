@@ -13,13 +13,14 @@
 //
 // Two executions of the sweeps:
 //  * one launch per hyperplane (reference; also the factorisation);
-//  * a pipelined tile-lane kernel: each wavefront owns an 8x8 column of cells,
-//    lane (i,j) walks up the column skewed by i+j steps, lanes exchange the
-//    previous step's values by cross-lane shuffles, and neighbouring tiles
+//  * pipelined tiles: a workgroup of nine waves sweeps an 8x8 column of cells, cell
+//    (i,j) walking up the column skewed by i+j steps, so that a step's 64 cells
+//    lie on one hyperplane; updating, loading and handing on are different waves'
+//    work, exchanged through LDS with one barrier per step.  Neighbouring tiles
 //    hand over their boundary faces through epoch-tagged 64-bit words (value
 //    and tag in one single-copy-atomic word, so no fences are needed).  Tiles
 //    are taken from an atomic ticket in topological order, so a tile only
-//    ever waits on tiles already held by running wavefronts (no deadlock);
+//    ever waits on tiles already held by running workgroups (no deadlock);
 //    every wait is bounded by a wall-clock limit that raises an error flag.
 #include "rsv_internal.h"
 
@@ -34,11 +35,10 @@ constexpr int BS = 256;
 
 __device__ inline int64_t fidx(int64_t slot, int e, int ne) { return ((slot >> 6) * ne + e) * 64 + (slot & 63); }
 
-// Per-cell arithmetic shared by the per-hyperplane and the pipelined sweeps,
-// so that both executions produce bitwise-identical results.
-// forward: out = r - (L_-z vz + L_-y vy + L_-x vx)   (ascending column order)
-// explicit fused multiply-adds: the same operation sequence in every kernel
-// that inlines these helpers, whatever the contraction choices around them
+// Arithmetic of a cell in the sweeps by hyperplanes.  The pipelined sweeps form the
+// same chains, a component per lane, so that FP64 gives the same bits either way:
+// explicit fused multiply-adds, the same operation sequence whatever the
+// contraction choices around them.
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 // forward: out = r - (L_-z vz + L_-y vy + L_-x vx), one FMA chain per
@@ -1025,7 +1025,6 @@ struct Bilu0 : PcImpl {
             if (fp32) return apply_plane<float>(r, z, Lf32, Dinv32, U32, zt32);
             return apply_plane<double>(r, z, Lf, Dinv, nullptr, zt64);
         }
-        const Geo &g = M->g->geo;
         const int nw = nwaves();
         if (fp32) {
             SweepArgs a = sweep_args(nw);
@@ -1045,12 +1044,13 @@ struct Bilu0 : PcImpl {
             prof_end(c, t2);
             RSV_LAUNCH(c);
         } else {
-            // Factors that no cache holds until the next sweep are loaded without keeping
-            // (forward/backward us: 2.1 M slots 233/279 -> 223/275, 6.1 M 465/551 ->
-            // 423/537, 8.4 M 600/735 -> 558/703; 33.6 M, by placement, 1816 to 2023/2417
-            // to 2688 -> 1907/2470).  Below, 1.8 M in RAS's boxes: 125/160 -> 132/170.
-            // FP32 sweeps gain nothing (8.4 M 397/440 to 419/450, with it 407/445).
-            const bool nt = g.nslot >= SW_NT_SLOTS;
+            // From 2 M slots the factors are loaded without keeping: up to there some of
+            // them are still found in the 256 MB cache.  Forward/backward us, kept and not, one box:
+            // 2.1 M slots 233/279 and 223/275, 2.5 M 254/308 and 254/306, 4.1 M 337/421 and 321/411,
+            // 8.4 M 590/731 and 548/704.  RAS in 4 x 4 x 4 boxes (apply): 1.7 M slots 292 and 295, 1.8 M 320
+            // and 334, 3.8 M 681 and 652, 11 M 1781 and 1692, 512 x 512 x 128 5620 and 5422.
+            // FP32 sweeps gain nothing (8.4 M 397/440 to 419/450, not kept 407/445).
+            const bool nt = M->g->geo.nslot >= SW_NT_SLOTS;
             SweepArgs a = sweep_args(nw);
             SweepSrc<double> s0{Lf, (int64_t)27 * 64, 0, nullptr, 0, 0, r, nullptr, nullptr};
             size_t sh = SweepCfg<0, double>::BYTES;
@@ -1071,7 +1071,6 @@ struct Bilu0 : PcImpl {
             RSV_LAUNCH(c);
             dump_trace(1);
         }
-        (void)g;
         return RSV_OK;
     }
 };

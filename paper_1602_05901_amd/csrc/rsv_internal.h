@@ -427,10 +427,6 @@ __device__ inline void face_st(uint64_t *p, uint64_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// 32-bit half h of a value's bits (h = 0 for FP32)
-__device__ inline uint32_t half_bits(double v, int h) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> (32 * h)); }
-__device__ inline uint32_t half_bits(float v, int) { return __float_as_uint(v); }
-
 // Spin-loop guard: checks the clock and the shared error flag only every 256th
 // call (the flag read is a device-scope load, which waits for every memory
 // operation the wave still has in flight).

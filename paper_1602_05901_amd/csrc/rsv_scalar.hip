@@ -13,10 +13,11 @@
 // (L1 distance on the lattice: faces, no edges or corners for overlap 1).
 // The local ILU(0) in ascending global order has no fill on the 7-point graph
 // (two neighbours of a cell are never neighbours), so D_c = a_cc -
-// sum_{k lower} a_ck a_kc / D_k.  One workgroup per subdomain walks planes of
-// x-chunks (each depending only on the plane before) with a barrier between
-// them, for the factorisation and for both sweeps of an apply; only the
-// owner of a cell writes its result.
+// sum_{k lower} a_ck a_kc / D_k.  Two forms: tile columns, swept by waves that
+// exchange faces (the default but for thin boxes that are long in x), and one
+// workgroup per subdomain, which walks planes of x-chunks (each depending only on
+// the plane before) with a barrier between them, for the factorisation and for
+// both sweeps of an apply.  Only the owner of a cell writes its result.
 #include "rsv_internal.h"
 
 #include <algorithm>
