@@ -930,7 +930,9 @@ struct Bilu0 : PcImpl {
                 const int da = (a % g.ntx) % btx + (a / g.ntx) % bty, db = (b % g.ntx) % btx + (b / g.ntx) % bty;
                 return da < db;
             });
-            RSV_HIP(c, hipMemcpy(tile_order, ord.data(), NT * sizeof(int32_t), hipMemcpyHostToDevice));
+            // on the stream: behind the clearing of the same memory, whatever kind of stream it is
+            RSV_HIP(c, hipMemcpyAsync(tile_order, ord.data(), NT * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+            RSV_HIP(c, hipStreamSynchronize(c->stream));   // ord is read
         }
         RSV_HIP(c, hipStreamSynchronize(c->stream));
         return RSV_OK;
