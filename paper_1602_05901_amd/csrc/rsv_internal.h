@@ -242,16 +242,18 @@ rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, 
                         const double *aux, double alpha, double beta, int k0);
 // A product's matrix (mat_bytes of real cells) is loaded without keeping where one
 // vector of n doubles is at most the 256 MB of the cache behind the L2s, which the
-// matrix would push the vectors out of, and the matrix is more than about half of them:
-// a smaller one stays there from one product to the next.  Products in solves, us kept
-// and not: blocks 20 x 20 x 10 8.0 and 8.9, 32^3 (17 MB) 8.7 and 9.7, 64^3 (132 MB) 28.6
-// and 32.2 alone, 27.7 and 27.0 behind BILU0, whose forward sweep takes 100 and 97 then,
-// 96^3 (446 MB) 88.5 and 77.8, 128 x 128 x 64 104 and 92, 256 x 256 x 128 (201 MB per
-// vector) 850 and 826; 512 x 512 x 128 (805 MB) 3422 and 3471; scalar 64^3 9.3 and 10.1,
-// 128^3 (117 MB) 33.6 and 35.8, 160^3 (229 MB) 66.7 and 64.3, 256^3 260 and 242.
-inline bool once_through(int64_t n, int64_t mat_bytes)
+// matrix would push the vectors out of, and the matrix is more than `stays`: a smaller
+// one is found there by the next product.  Thirty steps, us kept and not, blocks, GMRES +
+// BILU0 and BiCGSTAB + RAS in 8 boxes: 32^3 (17 MB) 4731 and 4814, 6472 and 6581; 48^3
+// (56 MB) 7066 and 7128, 8508 and 8669; 56^3 (89 MB) 8439 and 8481, 9420 and 9367; 60^3
+// (109 MB) 9892 and 9802, 10219 and 9952; 72 x 72 x 64 (167 MB) 11638 and 11510, 13155 and
+// 12711.  Products alone: 128 x 128 x 64 104 and 92, 256 x 256 x 128 (201 MB per vector) 850
+// and 826; 512 x 512 x 128 (805 MB) 3422 and 3471; scalar 64^3 9.3 and 10.1, 128^3 (117 MB)
+// 33.6 and 35.8, 160^3 (229 MB) 66.7 and 64.3, 256^3 260 and 242.
+constexpr int64_t STAYS_BLOCK = (int64_t)96 << 20, STAYS_SCALAR = (int64_t)128 << 20;
+inline bool once_through(int64_t n, int64_t mat_bytes, int64_t stays)
 {
-    return n * (int64_t)sizeof(double) <= (int64_t)256 << 20 && mat_bytes > (int64_t)120 << 20;
+    return n * (int64_t)sizeof(double) <= (int64_t)256 << 20 && mat_bytes > stays;
 }
 int mat_spmv_blocks(rsv_matrix *M);   // partials of a product with sums; k0 < 0 leaves them at the head of d_partials
 rsv_status mat_spmv(rsv_matrix *M, int mode, const double *x, double *y, const double *aux, double alpha,

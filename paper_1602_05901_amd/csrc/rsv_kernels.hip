@@ -805,7 +805,7 @@ rsv_status launch_spmv(rsv_ctx *c, const Geo &g, const double *A, int mode, cons
     dim3 grid(nb), block(BS);
     double *P = c->d_partials;
     const int tok = prof_begin(c, RSV_K_SPMV);
-    const bool nt = once_through(g.nslot * 3, (int64_t)g.nx * g.ny * g.nz * 504);
+    const bool nt = once_through(g.nslot * 3, (int64_t)g.nx * g.ny * g.nz * 504, STAYS_BLOCK);
 #define L_SPMV(M)                                                                                          \
     case M:                                                                                                \
         if (nt)                                                                                            \

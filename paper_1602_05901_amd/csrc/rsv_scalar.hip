@@ -1098,7 +1098,7 @@ rsv_status launch_sspmv(rsv_ctx *c, const Geo &g, const double *coef, int mode, 
     double *P = c->d_partials;
     const int tok = prof_begin(c, RSV_K_SPMV);
     const dim3 grid(nb), blk(SB);
-    const bool nt = once_through(n, n * 56);
+    const bool nt = once_through(n, n * 56, STAYS_SCALAR);
 #define L_SSPMV(M)                                                                                              \
     case M:                                                                                                     \
         if (nt)                                                                                                 \
