@@ -243,12 +243,15 @@ __global__ __launch_bounds__(256) void k_conv(ConvGeo g, const uint16_t *__restr
 // every K block cost about as many cycles as its MFMAs, and an epilogue through
 // LDS as many again.  Measured at 128x128x64, before and after: 4->16 33 -> 22
 // us, 16->16 67 -> 37, up-sampled 32->16 118 -> 58 (500 TFLOP/s); at 64x64x32:
-// 16->32 18 -> 13, up-sampled 64->32 75 -> 28.  The bound is the LDS reads: one
-// 16-byte operand per lane and MFMA with 16 output channels.)  The weights are
+// 16->32 18 -> 13, up-sampled 64->32 75 -> 28.  With 16 output channels an MFMA
+// takes one 16-byte operand per lane from LDS, which is active in 60 % of the
+// cycles with 16 inputs and 40 % with 32, the MFMAs in 23 %.)  The weights are
 // staged in LDS once per workgroup; those of 64 channels do not fit beside a
-// halo and come through the L1 from the L2.  VS, the LDS stride of a voxel, is
-// an odd number of 16-byte units, so that the 16 voxels of a fragment read
-// fall on distinct banks.
+// halo and come through the L1 from the L2 (460 registers, one workgroup per CU:
+// LDS 20 %, MFMAs 18 %).  VS, the LDS stride of a voxel, is an odd number of
+// 16-byte units, so that the 16 voxels of a quad's read fall on distinct banks;
+// the quads', which are other taps or channels, still meet: bank conflicts are 45 %
+// of the LDS cycles.
 template <int CIN, int NBW, int NSPLIT, int TZ> struct ConvCfg {
     static constexpr int NT = 64 * TZ * NSPLIT;
     static constexpr int KB = conv_kblocks(CIN);
@@ -259,7 +262,6 @@ template <int CIN, int NBW, int NSPLIT, int TZ> struct ConvCfg {
     static constexpr size_t WBYTES = WLDS ? (size_t)KB * NSPLIT * NBW * 64 * FB : 0;
     static constexpr size_t LDS = WBYTES + (size_t)HN * VS * 2;
 };
-
 
 template <int CIN, int NBW, int NSPLIT, int TZ, bool OUT_BF16>
 __global__ __launch_bounds__(64 * TZ * NSPLIT) void k_conv_lds(ConvGeo g, const uint16_t *__restrict__ X,
@@ -500,7 +502,7 @@ hipError_t launch_conv(const rsv_ctx *c, const ConvGeo &g, const uint16_t *X, co
 // reads 44 (74); places of the halo's pieces computed once 41; bias sums by
 // shuffles instead of one thread per channel 37; a step's fragments read before
 // the last one's MFMAs 32 (54).  All ten layers of the network, 8 samples of
-// 64 x 64 x 32: 820 -> 260 us.  256 workgroups: 322 us; 1024: 273, and the
+// 64 x 64 x 32: 820 -> 236 us.  256 workgroups: 322 us; 1024: 273, and the
 // reduction 77 instead of 59.
 //
 // Split over voxels: each chunk writes one partial (taps, then the bias sums
