@@ -1010,8 +1010,8 @@ struct STile final : PcImpl {
         // memory, also takes what exceeds the slots' index range or the memory.
         const double planes = (EX + SW - 1) / SW + EY + EZ - 2, chunks = (double)((EX + SW - 1) / SW) * EY * EZ;
         const double t_chunk = (double)((nsub + c->num_cu - 1) / c->num_cu) * (2.1 * planes + 0.0135 * chunks);
-        const double steps = 0.375 * (EZ + 14), tiles = (double)slots / 64 / EZ;
-        const double t_tile = std::max(6.1 * (d.btx + d.bty - 2) + steps, tiles * (7.2 + steps) / (ST_WAVES * c->num_cu));
+        const double steps = 0.375 * (EZ + 14), rounds = std::ceil((double)slots / 64 / EZ / (ST_WAVES * c->num_cu));
+        const double t_tile = std::max(6.1 * (d.btx + d.bty - 2) + steps, rounds > 1 ? rounds * (7.2 + steps) : 0.0);
         if (t_chunk < t_tile) {
             unfit = true;
             return RSV_OK;
